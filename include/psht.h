@@ -97,10 +97,10 @@ typedef struct {
     size_t workspace_bytes_per_map; /* workspace psht_synth/psht_adjoint need per map */
     double kernel_poly_err;  /* largest error of the polynomial ES kernel taps (inner taps) */
     /* Legendre adjoint work decomposition: degree segments of adj_segment
-     * degrees per order, adj_waves wavefronts per work item (together holding
-     * every active ring of the order, at most adj_rings_per_lane rings per
-     * lane); adj_states recurrence states (40 bytes each) stored by the plan
-     * for the segment starts. */
+     * degrees per order, up to adj_waves wavefronts per work item (together
+     * holding every started ring of the order, at most adj_rings_per_lane rings
+     * per lane); adj_states recurrence states (32 bytes each, 16 for spin 0)
+     * stored by the plan for the ring bands' starts and the segment starts. */
     int32_t adj_segment, adj_waves, adj_rings_per_lane;
     int64_t adj_states;
     /* Lmax_rule: Lmax from eq. Lmax2; Lmax differs from it when the plan was
@@ -116,7 +116,7 @@ typedef struct {
     size_t shared_bytes;
     /* Legendre synthesis work decomposition: 0, or (for plans whose per-order
      * work items would leave most of the GPU idle) segments of syn_segment
-     * degrees per order, started from the adjoint's stored states, with
+     * degrees per order, started from the plan's stored states, with
      * syn_parts partial copies of the ring coefficients in the workspace */
     int32_t syn_segment, syn_parts;
 } psht_plan_info;

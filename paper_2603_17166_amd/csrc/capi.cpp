@@ -146,203 +146,311 @@ struct ScopedDevFree {
     }
 };
 
-// Degree-segmented synthesis.  The synthesis runs one wave per (order m,
-// chunk of 64 R rings) over all degrees of m; a small cap at high lmax has few
-// such items (a few hundred orders), each thousands of sequential steps long,
-// and leaves most of the GPU idle.  Such a plan cuts the degrees of every order
-// into segments of Ssyn = 2^k S degrees, S the adjoint's segment length, so
-// that every segment start has a state stored for the adjoint; segment k >= 1
-// of an order writes its own partial copy of F, which a second kernel adds in.
-// Ssyn is the largest such length for which the longest item costs at most a
-// third of the average work per wave slot (two waves per SIMD), as for the
-// adjoint, lengthened where needed to at most 33 segments per order (32
-// partial copies); a plan whose longest order would get fewer than three
-// segments is not segmented.
-// The items use two rings per lane (one when PSHT_LEG_R fixes one): with
-// the parallelism from the segments, the longer per-step work beats the one
-// ring per lane of the plain list of such plans (lmax 4096, 5-degree disc:
-// 0.135 against 0.162 ms; equal within 2 us on the smallest plans).
-bool build_synth_segments(psht_plan_s &p, int ncu, const std::vector<int> &first, const std::vector<int> &last,
-                          const std::vector<int64_t> &soff_m, int S, hipStream_t st) {
-    const psht::Geometry &g = p.g;
+// Segment length of the synthesis.  The synthesis runs one wave per (order m,
+// group of bands) over the degrees of m; a small cap at high lmax has few such
+// items (a few hundred orders), each thousands of sequential steps long, and
+// leaves most of the GPU idle.  Such a plan cuts the degrees of every order
+// into segments; segment k >= 1 of an order writes its own partial copy of F,
+// which a second kernel adds in.  The length is the largest power of two (at
+// least 64) for which the longest item costs at most a third of the average
+// work per wave slot (two waves per SIMD), lengthened where needed to at most
+// 33 segments per order (32 partial copies).  Orders shorter than three segments
+// of less than 256 degrees are not segmented (the partial-sum launch costs what
+// they gain: lmax 128 cap 10.3 against 9.7 us); longer ones are, from two
+// segments on (lmax 3000, 1000 deg^2: 0.45 -> 0.32 ms; lmax 4096, 1500 deg^2:
+// 1.00 -> 0.97 ms), unless their copies would enlarge the workspace.  The work is counted over all
+// degrees l >= m, in steps of 128 rings, so that the size of the workspace does
+// not depend on where the bands start.  Returns 0 for no segments.
+int synth_segment_length(const psht::Geometry &g, int ncu, const std::vector<int> &first, const std::vector<int> &last) {
     const int lmax = g.lmax, s = g.spin, M = g.mmax;
-    p.syn_seg = 0;
-    p.syn_parts = 0;
-    p.n_syn_items = 0;
-    const int R = psht::leg_rings_per_lane() == 1 ? 1 : 2, chunk = 64 * R;
-    auto steps_cost = [&](int nr) { return (R > 1 && nr <= 64) ? 1.0 / R : 1.0; };
-    double total = 0.0;
+    double total = 0.0, adj_total = 0.0;
+    int nrmax = 1, G = 1, rmax = 1;
+    for (int m = 0; m <= M; ++m)
+        if (first[m] >= 0) nrmax = std::max(nrmax, last[m] - first[m] + 1);
+    while (G < 4 && 384 * G < nrmax) G *= 2;
     for (int m = 0; m <= M; ++m) {
         if (first[m] < 0 || std::max(m, s) > lmax) continue;
-        const int steps = lmax + 1 - std::max(m, s);
-        for (int jb = first[m]; jb <= last[m]; jb += chunk)
-            total += steps * steps_cost(std::min(chunk, last[m] + 1 - jb));
+        const int steps = lmax + 1 - std::max(m, s), nr = last[m] - first[m] + 1;
+        for (int r = nr; r > 0; r -= 128) total += r <= 64 ? 0.5 * steps : steps;
+        const int groups = (nr + 384 * G - 1) / (384 * G), gsize = (nr + groups - 1) / groups;
+        const int R = (gsize + 64 * G - 1) / (64 * G);
+        rmax = std::max(rmax, R);
+        adj_total += (double)steps * R * G;
     }
     const double slots = (double)std::max(ncu, 1) * 4 * 2;
-    int Ssyn = S;
-    while ((double)Ssyn * 2 <= total / slots / 3.0) Ssyn *= 2;
-    // at most 32 partial copies of F (a tiny cap at very high lmax would
-    // otherwise take hundreds, each as large as F, in the workspace)
-    while ((int64_t)33 * Ssyn < (int64_t)lmax + 1 - s) Ssyn *= 2;
-    if (const char *e = getenv("PSHT_SYN_SEG")) {  // tuning runs: a power-of-two multiple of S, 0 for none
+    int S = 64;
+    while (S * 2 <= lmax + 1 && (double)(S * 2) * rmax <= adj_total / slots / 3.0) S *= 2;
+    while ((double)S * 2 <= total / slots / 3.0) S *= 2;
+    while ((int64_t)33 * S < (int64_t)lmax + 1 - s) S *= 2;
+    if (const char *e = getenv("PSHT_SYN_SEG")) {  // tests and tuning runs: a power of two, at least 64; 0 for none
         const int v = atoi(e);
-        if (v == 0) Ssyn = lmax + 1;
-        else if (v >= S && v % S == 0 && ((v / S) & (v / S - 1)) == 0) Ssyn = v;
+        if (v == 0) return 0;
+        if (v >= 64 && (v & (v - 1)) == 0) return v;
     }
-    // at most two segments for the longest order: the plain work list (two
-    // measured within the noise of one, and cost the partial-sum launch)
-    if (3 * Ssyn > lmax + 1 - s) return true;
-    const int q = Ssyn / S;
-    std::vector<psht::SynSegItem> items;
-    int parts = 0;
-    for (int m = 0; m <= M; ++m) {
-        const int l0 = std::max(m, s);
-        if (first[m] < 0 || l0 > lmax) continue;
-        const int nr = last[m] - first[m] + 1;
-        const int nseg = (lmax + 1 - l0 + Ssyn - 1) / Ssyn;
-        parts = std::max(parts, nseg - 1);
-        for (int k = 0; k < nseg; ++k) {
-            const int la = l0 + k * Ssyn, lb = std::min(lmax + 1, la + Ssyn);
-            for (int jb = first[m]; jb <= last[m]; jb += chunk) {
-                const int je = std::min(jb + chunk, last[m] + 1);
-                // segment k starts at the adjoint's segment k q >= 1 (stored when nseg_adj > 1)
-                const int64_t so = k == 0 ? -1 : soff_m[m] + (int64_t)(k * q - 1) * nr + (jb - first[m]);
-                items.push_back(psht::SynSegItem{m, jb, je, la, lb, k, so});
-            }
-        }
-    }
-    // longest first (blocks are issued in order and dealt round-robin to the XCDs)
-    std::stable_sort(items.begin(), items.end(), [&](const psht::SynSegItem &u, const psht::SynSegItem &v) {
-        return (u.lb - u.la) * steps_cost(u.je - u.jb) > (v.lb - v.la) * steps_cost(v.je - v.jb);
-    });
-    if (!upload(p, p.d_syn_items, items, st)) return false;
-    p.n_syn_items = (int)items.size();
-    p.syn_seg = Ssyn;
-    p.syn_parts = parts;
-    p.syn_r = R;
-    return true;
+    const int n = lmax + 1 - s;
+    if (3 * S <= n) return S;
+    while (S >= 2048 && S >= n) S /= 2;
+    if (S < 256 || S >= n) return 0;
+    // two or three segments, where the copies fit the V and U region
+    const size_t cs = g.fp32 ? 8 : 16, ldv = 2 * (size_t)M + 1;
+    const size_t copies = (size_t)((n + S - 1) / S - 1) * ldv * g.nring * 16;
+    return copies <= (size_t)g.rows_used * (ldv + g.Nphi) * cs ? S : 0;
 }
 
-// Work list and recurrence states of the segmented Legendre adjoint.
+// Bands, stored states and work lists of the Legendre stages.
 //
-// Order m has the active rings [first_m, last_m] (ring_mmax >= m) and the
-// degrees l0 .. lmax, l0 = max(m, s).  The plan takes the smallest G of 1, 2, 4
-// waves per workgroup with 384 G >= rings (at most 6 rings per lane; whole
-// workgroups then fill a CU's eight wave slots) and splits each order's ring
-// range evenly over them (R_m rings per lane).  The segment length S is the
-// largest power of two (at least 64) for which the longest item costs at most
-// a third of the average work per wave slot (two waves per SIMD): with
-// longest-first placement the last items then finish close together.
-// Segments k >= 1 start from stored states (40 bytes per ring and segment).
-// An order with more active rings than one item holds (1536 at G = 4: the
-// full sky above lmax ~ 3000, the partial sky near lmax 10000) is cut into
-// ring groups; their items add into the output, which is cleared first.
-bool build_adjoint_segments(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
+// Adjoint.  The plan takes the smallest G of 1, 2, 4 waves per workgroup with
+// 512 G >= rings (at most 8 bands per wave).  An item covers every started band
+// of its order over one segment of S degrees: S is the largest power of two (at
+// least 64) for which the longest item costs at most a third of the average
+// work per wave slot (two waves per SIMD): with longest-first placement the
+// last items then finish close together.  An order with more bands than one
+// item holds (32 at G = 4) is cut into band groups; their items add into the
+// output, which is cleared first.
+bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     const psht::Geometry &g = p.g;
     const int lmax = g.lmax, s = g.spin, M = g.mmax;
+    auto nomem = [&](const char *what) {
+        err = {PSHT_ERR_NOMEM, what};
+        return false;
+    };
+    auto device = [&](hipError_t e, const char *what) {
+        err = {e == hipErrorOutOfMemory ? PSHT_ERR_NOMEM : PSHT_ERR_DEVICE,
+               std::string(what) + ": " + hipGetErrorString(e)};
+        return false;
+    };
     std::vector<int> first(M + 1, -1), last(M + 1, -1);
     for (int j = 0; j < g.nring; ++j)
         for (int m = 0; m <= std::min(M, (int)g.ring_mmax[j]); ++m) {
             if (first[m] < 0) first[m] = j;
             last[m] = j;
         }
+    // bands of each order from its last ring downwards
+    std::vector<psht::LegBand> geo;
+    std::vector<psht::LegOrder> orders(M + 2);
     int nrmax = 1;
-    for (int m = 0; m <= M; ++m)
-        if (first[m] >= 0) nrmax = std::max(nrmax, last[m] - first[m] + 1);
-    int G = 1;
-    while (G < psht::kAdjMaxWavesHost && 64 * psht::kAdjMaxRings * G < nrmax) G *= 2;
-    if (const char *e = getenv("PSHT_ADJ_WAVES")) {  // tuning runs: 1, 2 or 4, as long as the rings fit
-        const int v = atoi(e);
-        if ((v == 1 || v == 2 || v == 4) && 64 * psht::kAdjMaxRings * v >= nrmax) G = v;
-    }
-    auto rings_per_lane = [&](int m) {
-        if (first[m] < 0) return 0;
-        const int nr = last[m] - first[m] + 1, gm = 64 * psht::kAdjMaxRings * G;
-        const int ng = (nr + gm - 1) / gm, gsize = (nr + ng - 1) / ng;
-        return (gsize + 64 * G - 1) / (64 * G);
-    };
-    double total = 0.0;
-    int rmax = 1;
     for (int m = 0; m <= M; ++m) {
-        const int R = rings_per_lane(m);
-        rmax = std::max(rmax, R);
-        total += (double)(lmax + 1 - std::max(m, s)) * R * G;
+        orders[m] = psht::LegOrder{last[m], (int32_t)geo.size()};
+        if (first[m] < 0 || std::max(m, s) > lmax) continue;
+        nrmax = std::max(nrmax, last[m] - first[m] + 1);
+        for (int top = last[m]; top >= first[m]; top -= 64)
+        {
+            uint64_t mask = 0;
+            for (int i = 0; i < 64; ++i) {
+                const int j = top - 63 + i;
+                if (j >= first[m] && g.ring_mmax[j] >= m) mask |= uint64_t(1) << i;
+            }
+            geo.push_back(psht::LegBand{top - 63, 0, 0, m, mask});
+        }
     }
+    orders[M + 1] = psht::LegOrder{-1, (int32_t)geo.size()};
+    const int nbands = (int)geo.size();
+    std::vector<int32_t> bs(nbands);
+    ScopedDevFree d_init, d_lost;
+    hipError_t e = hipMalloc(&d_init.p, sizeof(psht::LegBand) * (size_t)std::max(nbands, 1));
+    if (e == hipSuccess) e = hipMalloc(&d_lost.p, sizeof(int32_t));
+    if (e != hipSuccess) return device(e, "Legendre bands");
+    auto *init = static_cast<psht::LegBand *>(d_init.p);
+    if (!dalloc(p, p.d_band_bs, nbands) || !upload(p, p.d_orders, orders, st)) return nomem("Legendre bands");
+    if (nbands > 0) {
+        e = hipMemcpy(init, geo.data(), sizeof(geo[0]) * nbands, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = psht::launch_leg_starts(p, init, nbands, p.d_band_bs, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(bs.data(), p.d_band_bs, sizeof(int32_t) * nbands, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return device(e, "Legendre start degrees");
+    }
+    // by start degree within each order
+    std::vector<int> by(nbands);
+    for (int i = 0; i < nbands; ++i) by[i] = i;
+    double total = 0.0;
+    for (int m = 0; m <= M; ++m)
+        std::stable_sort(by.begin() + orders[m].band0, by.begin() + orders[m + 1].band0,
+                         [&](int u, int v) { return bs[u] < bs[v]; });
+    for (int i = 0; i < nbands; ++i) total += lmax + 1 - bs[i];
+
+    int G = 1;
+    while (G < psht::kAdjMaxWaves && 64 * psht::kAdjMaxBands * G < nrmax) G *= 2;
+    int group_max = psht::kAdjMaxBands * G;  // bands per item
+    if (const char *v = getenv("PSHT_ADJ_GROUP"))  // tests and tuning runs: smaller groups (in rings)
+        if (atoi(v) >= 1) group_max = std::min(group_max, std::max(1, atoi(v) / 64));
+    const int rmax = (std::min((nrmax + 63) / 64, group_max) + G - 1) / G;
     const double slots = (double)std::max(ncu, 1) * 4 * 2;
     int S = 64;
     while (S * 2 <= lmax + 1 && (double)(S * 2) * rmax <= total / slots / 3.0) S *= 2;
-    if (const char *e = getenv("PSHT_ADJ_SEG")) {  // tuning runs
-        const int v = atoi(e);
-        if (v >= 8 && v <= 1 << 16) S = v;
+    if (const char *v = getenv("PSHT_ADJ_SEG")) {  // tuning runs: a power of two, at least 64
+        const int x = atoi(v);
+        if (x >= 64 && x <= 1 << 15 && (x & (x - 1)) == 0) S = x;
     }
-    // Orders with more rings than one item holds (64 x 6 x G) are cut into
-    // ring groups whose items add into a cleared output (see adj_accumulate).
-    int group_max = 64 * psht::kAdjMaxRings * G;
-    if (const char *e = getenv("PSHT_ADJ_GROUP")) {  // tests and tuning runs: smaller ring groups
-        const int v = atoi(e);
-        if (v >= 1 && v < group_max) group_max = v;
+    p.syn_seg = synth_segment_length(g, ncu, first, last);
+    if (p.syn_seg > 0) S = std::min(S, p.syn_seg);
+
+    // stored states; a state that leaves the double range although it matters
+    // later in its segment (never seen below spins in the hundreds) shortens
+    // the segments to 64 degrees, in which no value grows from 2^-960 to 2^-64
+    std::vector<psht::LegBand> bands(nbands);
+    if (!dalloc(p, p.d_bands, nbands)) return nomem("Legendre bands");
+    for (;;) {
+        int64_t blk = 0;
+        for (int i = 0; i < nbands; ++i) {
+            bands[i] = geo[by[i]];
+            const int l0 = std::max(bands[i].order, s), at = bs[by[i]];
+            bands[i].bs = at;
+            bands[i].blk = (int32_t)blk;
+            blk += 1 + (lmax - l0) / S - (at - l0) / S;
+        }
+        p.adj_seg = S;
+        p.n_adj_states = blk * 64;
+        const size_t held = p.allocations.size(), resident = p.resident;
+        if (!dalloc(p, p.d_st_p, (size_t)blk * 128) || (s > 0 && !dalloc(p, p.d_st_m, (size_t)blk * 128)))
+            return nomem("Legendre recurrence states");
+        int32_t lost = 0;
+        if (nbands > 0) {
+            e = hipMemcpy(p.d_bands, bands.data(), sizeof(bands[0]) * nbands, hipMemcpyHostToDevice);
+            if (e == hipSuccess) e = psht::launch_fill_zero(d_lost.p, sizeof(int32_t), st);
+            if (e == hipSuccess)
+                e = psht::launch_leg_states(p, nbands, static_cast<int32_t *>(d_lost.p), st);
+            if (e == hipSuccess) e = hipMemcpyAsync(&lost, d_lost.p, sizeof(lost), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return device(e, "Legendre recurrence states");
+        }
+        if (lost == 0) break;
+        if (S == 64) {
+            err = {PSHT_ERR_UNSUPPORTED, "Legendre recurrence leaves the double range within 64 degrees"};
+            return false;
+        }
+        while (p.allocations.size() > held) {
+            (void)hipFree(p.allocations.back());
+            p.allocations.pop_back();
+        }
+        p.resident = resident;
+        S = 64;
     }
-    bool accumulate = false;
+
+    // adjoint items
     std::vector<psht::AdjItem> items;
-    std::vector<psht::StateItem> sitems;
-    std::vector<int64_t> soff_m(M + 1, -1);  // first stored state of order m
-    int64_t off = 0;
+    std::vector<double> cost;
+    bool accumulate = false;
+    int rused = 1;
     for (int m = 0; m <= M; ++m) {
-        const int l0 = std::max(m, s);
-        if (first[m] < 0) {
-            items.push_back(psht::AdjItem{m, 0, 0, m, lmax + 1, 0, -1});
+        const int l0 = std::max(m, s), b0 = orders[m].band0, nb = orders[m + 1].band0 - b0;
+        if (nb == 0) {
+            if (m <= lmax) items.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1}), cost.push_back(0.0);
             continue;
         }
-        const int jb = first[m], je = last[m] + 1, nr = je - jb;
-        const int ng = (nr + group_max - 1) / group_max, gsize = (nr + ng - 1) / ng;
-        accumulate |= ng > 1;
-        const int nseg = (lmax + 1 - l0 + S - 1) / S;
-        for (int k = 0; k < nseg; ++k) {
+        accumulate |= nb > group_max;
+        for (int k = 0; l0 + k * S <= lmax; ++k) {
             const int la = l0 + k * S, lb = std::min(lmax + 1, la + S);
-            for (int q = 0; q < ng; ++q) {
-                const int gb = jb + q * gsize, ge = std::min(je, gb + gsize);
-                const int R = (ge - gb + 64 * G - 1) / (64 * G);
-                items.push_back(psht::AdjItem{m, gb, ge, la, lb, R,
-                                              k == 0 ? -1 : off + (int64_t)(k - 1) * nr + (gb - jb)});
+            int on = 0;
+            while (on < nb && bands[b0 + on].bs < lb) ++on;
+            for (int q = 0; q < std::max(on, 1); q += group_max) {
+                const int n = std::min(group_max, on - q);
+                const int waves = n <= psht::kAdjMaxBands ? 1 : G;
+                double c = 0.0;  // per wave: band steps, and the reduction's share of every step
+                for (int i = 0; i < n; ++i) c += lb - std::max(la, bands[b0 + q + i].bs);
+                c /= waves;
+                if (n > 0) c += 1.6 * (lb - std::max(la, bands[b0 + q].bs));
+                items.push_back(psht::AdjItem{m, k == 0 ? m : la, lb, b0 + q, n, waves});
+                cost.push_back(c);
+                rused = std::max(rused, (n + waves - 1) / waves);
             }
         }
-        if (nseg > 1) {
-            for (int j0 = jb; j0 < je; j0 += 64) sitems.push_back(psht::StateItem{m, j0, jb, je, nseg, S, off});
-            soff_m[m] = off;
-            off += (int64_t)(nseg - 1) * nr;
-        }
     }
+    // orders above mmax have no ring: their outputs are zero
+    std::vector<psht::AdjItem> zeros;
+    if (!accumulate)
+        for (int m = M + 1; m <= lmax; ++m) zeros.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1});
     // longest first (blocks are issued in order and dealt round-robin to the XCDs)
-    std::stable_sort(items.begin(), items.end(), [](const psht::AdjItem &u, const psht::AdjItem &v) {
-        return (int64_t)(u.lb - u.la) * std::max(u.R, 1) > (int64_t)(v.lb - v.la) * std::max(v.R, 1);
-    });
+    auto longest_first = [](auto &list, const std::vector<double> &c) {
+        std::vector<int> at(list.size());
+        for (size_t i = 0; i < at.size(); ++i) at[i] = (int)i;
+        std::stable_sort(at.begin(), at.end(), [&](int u, int v) { return c[u] > c[v]; });
+        auto out = list;
+        for (size_t i = 0; i < at.size(); ++i) out[i] = list[at[i]];
+        list.swap(out);
+    };
+    longest_first(items, cost);
+    {
+        // one entry per wave: single-wave items fill workgroups of G with their neighbours in cost
+        // in cost; the zeros are spread evenly among them, so that their stores run
+        // beside the sums (as fills of their own they took 40 of 221 us at lmax
+        // 4000 on a 7-degree disc)
+        std::vector<psht::AdjItem> waves, group, zgroup;
+        size_t iz = 0, n = 0;
+        auto put = [&](std::vector<psht::AdjItem> &g, const psht::AdjItem &it) {
+            g.push_back(it);
+            if ((int)g.size() < G) return;
+            waves.insert(waves.end(), g.begin(), g.end());
+            g.clear();
+        };
+        for (const psht::AdjItem &it : items) {
+            ++n;
+            while (iz * items.size() < n * zeros.size()) put(zgroup, zeros[iz++]);
+            for (int w = 0; w < (it.waves > 1 ? G : 0); ++w) waves.push_back(it);
+            if (it.waves == 1) put(group, it);
+        }
+        for (auto *g : {&group, &zgroup})
+            while (!g->empty()) put(*g, psht::AdjItem{0, 0, 0, 0, 0, 1});
+        items.swap(waves);
+    }
     p.adj_waves = G;
-    p.adj_rmax = rmax;
+    p.adj_rmax = rused;
     p.adj_accumulate = accumulate;
-    p.adj_seg = S;
-    p.n_adj_states = off;
-    p.alm_tail = (int64_t)(M + 1) * (2 * lmax + 1 - (M + 1)) / 2 + (M + 1);  // index(l = M + 1, m = M + 1)
-    if (!dalloc(p, p.d_adj_mu, (size_t)std::max<int64_t>(off, 1) * 4) ||
-        !dalloc(p, p.d_adj_k, (size_t)std::max<int64_t>(off, 1) * 2)) {
-        err = {PSHT_ERR_NOMEM, "allocating the adjoint recurrence states"};
-        return false;
-    }
-    psht::StateItem *d_sitems = nullptr;
-    if (!upload(p, p.d_adj_items, items, st) || !upload(p, d_sitems, sitems, st)) {
-        err = {PSHT_ERR_NOMEM, "uploading the adjoint work list"};
-        return false;
-    }
     p.n_adj_items = (int)items.size();
-    if (!build_synth_segments(p, ncu, first, last, soff_m, S, st)) {
-        err = {PSHT_ERR_NOMEM, "uploading the synthesis work list"};
-        return false;
+    if (!upload(p, p.d_adj_items, items, st)) return nomem("uploading the adjoint work list");
+
+    // synthesis items: seg degrees per segment (0: one segment), R bands per wave
+    auto synth_items = [&](int seg, int R, int x, std::vector<psht::SynthItem> &list, std::vector<double> &c) {
+        int parts = 0;
+        for (int m = x < 0 ? 0 : x; m <= M; m += x < 0 ? 1 : 8) {
+            const int l0 = std::max(m, s), b0 = orders[m].band0, nb = orders[m + 1].band0 - b0;
+            const int len = seg > 0 ? seg : lmax + 1;
+            for (int q = 0; q < nb; q += R)
+                for (int k = 0; l0 + k * len <= lmax; ++k) {
+                    const int la = l0 + k * len, lb = std::min(lmax + 1, la + len);
+                    int n = 0;
+                    double w = 0.0;
+                    while (n < std::min(R, nb - q) && bands[b0 + q + n].bs < lb)
+                        w += lb - std::max(la, bands[b0 + q + n++].bs);
+                    if (n == 0) continue;
+                    list.push_back(psht::SynthItem{m, la, lb, b0 + q, n, k});
+                    c.push_back(w + 0.3 * (lb - std::max(la, bands[b0 + q].bs)));
+                    parts = std::max(parts, k);
+                }
+        }
+        return parts;
+    };
+    const int fixed = psht::leg_bands_per_wave();
+    {
+        std::vector<psht::SynthItem> syn;
+        std::vector<double> c;
+        p.syn_r = fixed ? fixed : 4;
+        p.syn_parts = 0;
+        if (p.syn_seg > 0) {
+            (void)synth_items(p.syn_seg, p.syn_r, -1, syn, c);
+            longest_first(syn, c);
+            // copies for every segment of the longest order
+            p.syn_parts = (lmax + 1 - s + p.syn_seg - 1) / p.syn_seg - 1;
+            if (!upload(p, p.d_syn_items, syn, st)) return nomem("uploading the synthesis work list");
+        }
+        p.n_syn_items = (int)syn.size();
     }
-    hipError_t e = psht::launch_leg_adj_states(p, d_sitems, (int)sitems.size(), st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        err = {PSHT_ERR_DEVICE, std::string("adjoint recurrence states: ") + hipGetErrorString(e)};
-        return false;
+    // plain list: the items of an order on one XCD (blocks are dealt round-robin
+    // to the eight), so that they share its L2, each XCD's longest first
+    p.leg_r = fixed ? fixed : (nbands >= 10 * slots ? 4 : nbands >= slots ? 2 : 1);
+    std::vector<psht::SynthItem> per[8], plain;
+    size_t most = 0;
+    for (int x = 0; x < 8; ++x) {
+        std::vector<double> c;
+        (void)synth_items(0, p.leg_r, x, per[x], c);
+        longest_first(per[x], c);
+        most = std::max(most, per[x].size());
     }
+    for (size_t i = 0; i < most; ++i)
+        for (int x = 0; x < 8; ++x)
+            plain.push_back(i < per[x].size() ? per[x][i] : psht::SynthItem{0, 0, 0, 0, 0, 0});
+    p.n_leg_items = (int)plain.size();
+    if (!upload(p, p.d_leg_items, plain, st)) return nomem("uploading the synthesis work list");
     return true;
 }
 
@@ -421,93 +529,36 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
         !upload(p, p.d_ring_w, g.ring_w, st) || !upload(p, p.d_ring_mmax, g.ring_mmax, st))
         return fail(PSHT_ERR_NOMEM, "uploading ring tables");
 
-    // Legendre work items: `group` chunks of `chunk` rings per order m, groups
-    // padded to a multiple of 8.  One list for the per-map kernels (64 R rings
-    // per wave) and one of 64-ring chunks for the batched-maps kernel.
+    // Legendre bands, states and work lists; and the list of 64-ring chunks of
+    // the batched-maps kernel (groups padded to a multiple of 8)
     {
-        auto build_items = [&](int chunk, std::vector<psht::LegItem> &items) {
-            const int group = (g.nring + chunk - 1) / chunk;
-            const int ngroups = ((g.mmax + 1) + 7) / 8 * 8;
-            items.assign((size_t)ngroups * group, psht::LegItem{0, 0, 0});
-            for (int m = 0; m <= g.mmax; ++m) {
-                int first = -1, last = -1;
-                for (int j = 0; j < g.nring; ++j)
-                    if (g.ring_mmax[j] >= m) {
-                        if (first < 0) first = j;
-                        last = j;
-                    }
-                for (int c = 0; c < group; ++c) {
-                    psht::LegItem &it = items[(size_t)m * group + c];
-                    it.m = m;
-                    if (first < 0) continue;
-                    int jb = first + c * chunk, je = std::min(first + (c + 1) * chunk, last + 1);
-                    if (jb < je) {
-                        it.jb = jb;
-                        it.je = je;
-                    }
+        const int group = (g.nring + 63) / 64;
+        std::vector<psht::LegItem> items((size_t)(((g.mmax + 1) + 7) / 8 * 8) * group, psht::LegItem{0, 0, 0});
+        for (int m = 0; m <= g.mmax; ++m) {
+            int first = -1, last = -1;
+            for (int j = 0; j < g.nring; ++j)
+                if (g.ring_mmax[j] >= m) {
+                    if (first < 0) first = j;
+                    last = j;
+                }
+            for (int c = 0; c < group; ++c) {
+                psht::LegItem &it = items[(size_t)m * group + c];
+                it.m = m;
+                if (first < 0) continue;
+                const int jb = first + c * 64, je = std::min(jb + 64, last + 1);
+                if (jb < je) {
+                    it.jb = jb;
+                    it.je = je;
                 }
             }
-        };
-        // Synthesis order.  The kernel deals item slot (x + 8 q) group + i to the
-        // XCD x, in the order of q and i; the items of each XCD are placed in
-        // those slots longest first by their cost in the synthesis, where an
-        // item of at most 64 rings runs the one-ring-per-lane body at 1/R of
-        // the cost (longest-processing-time-first list scheduling; in the plain
-        // order these short remainders sat between the full items of their m).
-        auto order_for_synth = [&](std::vector<psht::LegItem> &items, int chunk, int R) {
-            const int group = (g.nring + chunk - 1) / chunk;
-            const int nq = (int)(items.size() / group) / 8;
-            auto cost = [&](const psht::LegItem &it) {
-                if (it.je <= it.jb) return 0.0;
-                const double steps = lmax + 1 - std::max(it.m, spin);
-                return (R > 1 && it.je - it.jb <= 64) ? steps / R : steps;
-            };
-            for (int x = 0; x < 8; ++x) {
-                std::vector<size_t> slots;
-                for (int q = 0; q < nq; ++q)
-                    for (int i = 0; i < group; ++i) slots.push_back((size_t)(x + 8 * q) * group + i);
-                std::vector<psht::LegItem> mine;
-                for (size_t sl : slots) mine.push_back(items[sl]);
-                std::stable_sort(mine.begin(), mine.end(),
-                                 [&](const psht::LegItem &u, const psht::LegItem &v) { return cost(u) > cost(v); });
-                for (size_t k = 0; k < slots.size(); ++k) items[slots[k]] = mine[k];
-            }
-        };
-        std::vector<psht::LegItem> items;
+        }
+        p.n_leg_items64 = (int)items.size();
+        if (!upload(p, p.d_leg_items64, items, st)) return fail(PSHT_ERR_NOMEM, "uploading Legendre work list");
         int dev = 0, ncu = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-        auto nonempty = [](const std::vector<psht::LegItem> &v) {
-            size_t n = 0;
-            for (const auto &it : v) n += it.je > it.jb;
-            return n;
-        };
-        // Synthesis rings per lane.  Small plans whose two-ring items fill less
-        // than 40 % of the GPU's wave slots (four per SIMD) run one ring per lane:
-        // twice the items, each step half the work, so the longest items finish
-        // sooner (lmax 2048, 10-degree disc: 0.165 -> 0.132 ms).  From about half
-        // the slots on, two rings per lane are faster (lmax 4096, 20-degree disc:
-        // 0.81 against 0.99 ms).
-        int rs = psht::leg_rings_per_lane();
-        if (rs == 0) {
-            build_items(64 * 2, items);
-            rs = (ncu > 0 && (double)nonempty(items) < 0.4 * ncu * 4 * 4) ? 1 : 2;
-        }
-        const int chunk = 64 * rs;
-        build_items(chunk, items);
-        order_for_synth(items, chunk, rs);
-        p.n_leg_items = (int)items.size();
-        p.leg_rings_per_item = chunk;
-        if (!upload(p, p.d_leg_items, items, st)) return fail(PSHT_ERR_NOMEM, "uploading Legendre work list");
-        build_items(64, items);
-        p.n_leg_items64 = (int)items.size();
-        if (!upload(p, p.d_leg_items64, items, st)) return fail(PSHT_ERR_NOMEM, "uploading Legendre work list");
-
-        // Segmented adjoint (k_leg_adj_seg): items (m, l-segment), each with every
-        // active ring of m in G waves of up to 6 rings per lane, started from
-        // recurrence states stored here for every ring and segment start.
         psht::Error e2;
-        if (!build_adjoint_segments(p, ncu, st, e2)) return fail(e2);
+        if (!build_legendre(p, ncu, st, e2)) return fail(e2);
     }
 
     // NUFFT tables

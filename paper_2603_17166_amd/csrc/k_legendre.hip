@@ -13,18 +13,21 @@
 //   A_lm = sum_j lambda+_lm(theta_j) F'_j(m),  B_lm = sum_j lambda-_lm(theta_j) conj F'_j(-m),
 //   g~_lm = -(A + (-1)^s B)/2,  c~_lm = (i/2)(A - (-1)^s B)   (Sec. I, adjoint).
 //
-// Work decomposition: one 64-lane wavefront per (m, chunk of 64*R rings); each
-// lane owns R rings (registers) and runs the recurrence in l.  The per-(l, m)
-// recurrence coefficients and coefficient combinations are wave-uniform: they
-// are staged through LDS one chunk ahead of their use.  The work items of one
-// m run on one XCD so they share its L2.
+// Work decomposition.  The active rings of an order m come in bands of 64
+// consecutive rings, one ring per lane.  Below the turning point l sin(theta) ~ m
+// the lambda of a ring fall off faster than exponentially towards l = m, so a
+// band starts at the first degree (on a grid of 32) at which any of its rings
+// reaches 2^-64 (kLegStartExp): the terms left out lie below the rounding of the
+// sums.  The recurrence of each band starts from a state stored at plan time
+// (mu_l, mu_{l-1}; in the double range, see k_leg_states), so the kernels carry
+// no exponents.  A wave holds several bands (registers) and takes them in one
+// after the other as l passes their starts.  At lmax 4096 (35 degree cap) the
+// bands start at 0.73 of the (ring, m, l) triples of l >= m, at lmax 2048 0.78.
 //
-// Values below the double range (see leg_common.h) occur only near the start
-// of the l range of the rings where m is close to the cut-off; while any lane
-// of the wave carries one, the wave runs blocks of 8 steps with masked
-// accumulation and renormalises between blocks (8 steps grow a value by far
-// less than the 2^800 of headroom above the renormalisation threshold).
+// The per-(l, m) recurrence coefficients and coefficient combinations are
+// wave-uniform: they are staged through LDS one chunk of 32 degrees ahead.
 #include <cstdlib>
+#include <type_traits>
 
 #include "lane_ops.h"
 #include "leg_common.h"
@@ -33,9 +36,12 @@
 namespace psht {
 
 struct LegArgs {
-    const LegItem *items;
+    const LegItem *items;  // 64-ring chunks (batched-maps kernel)
     int nitems;
     int group;  // items per order m
+    const LegBand *bands;  // sorted by start degree within each order
+    const double2 *st_p, *st_m;  // stored states {mu_l, mu_{l-1}} of the + and - functions
+    int seg;               // degrees between stored states
     const double4 *coef;  // {-A, A + B, A - B, P} per (l, m)
     const double *kmant;
     const int32_t *kexp;
@@ -92,39 +98,6 @@ __device__ inline void leg_init(const LegArgs &a, const LegItem &it, int lane, L
             if (!SPIN) {
                 S.um[r] = S.up[r];
                 S.km[r] = S.kp[r];
-            }
-        }
-    }
-}
-
-// The R rings of this lane for order m, rings [jb + 64 r + lane] below je,
-// from recurrence states stored at plan time: the state of ring j at index
-// soff + (j - jb), {mu+_l, mu+_{l-1}, mu-_l, mu-_{l-1}} and the scales {k+, k-}.
-template <int R, bool SPIN>
-__device__ inline void leg_init_stored(const LegArgs &a, int m, int jb, int je, int lane, const double4 *st_mu,
-                                       const int2 *st_k, int64_t soff, LegState<R, SPIN> &S) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int j = jb + r * 64 + lane;
-        S.act[r] = (j < je) && (a.ring_mmax[j] >= m);
-        S.y[r] = 0.0;
-        S.up[r] = S.upp[r] = S.um[r] = S.ump[r] = 0.0;
-        S.kp[r] = S.km[r] = 0;
-        if (S.act[r]) {
-            const int64_t q = soff + (j - jb);
-            const double4 v = st_mu[q];
-            const int2 k = st_k[q];
-            S.y[r] = a.ring_y[j];
-            S.up[r] = v.x;
-            S.upp[r] = v.y;
-            S.kp[r] = k.x;
-            if (SPIN) {
-                S.um[r] = v.z;
-                S.ump[r] = v.w;
-                S.km[r] = k.y;
-            } else {
-                S.um[r] = v.x;
-                S.km[r] = k.x;
             }
         }
     }
@@ -191,280 +164,208 @@ __device__ inline double4 synth_combo(const double2 *g, const double2 *c, const 
 }
 
 // Synthesis staging: lanes 0..31 read the recurrence table, lanes 32..63 form
-// the coefficient combinations of the same 32 degrees.
+// the coefficient combinations of the same 32 degrees; zero from lend on.
 __device__ inline double4 stage_entry_synth(const LegArgs &a, const double4 *T4, int64_t base, int m, int c,
-                                            int lmax, int lane) {
+                                            int lend, int lane) {
     const int l = c + (lane & 31);
     double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (l <= lmax) {
+    if (l < lend) {
         if (lane < 32) v = T4[l];
         else v = synth_combo(a.g, a.c, a.coef, base + l, m, a.mscale);
     }
     return v;
 }
 
-// Steps t in [t0, t1) of a staged chunk starting at l = c (t1 - t0 <= 8):
-// accumulate lambda_l into the ring sums, then advance the recurrence.
-template <int R, bool SPIN>
-__device__ inline void synth_steps(LegState<R, SPIN> &S, double *fpr, double *fpi, double *fmr, double *fmi,
-                                   const double4 *sT, const double4 *sQ, int t0, int t1, int c, int lmax) {
-#pragma unroll 2
-    for (int u = 0; u < 8; ++u) {
-        const int t = t0 + u;
-        if (t < t1) {
-            const double4 q = sQ[t];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double vp = S.up[r], vm = SPIN ? S.um[r] : S.up[r];
-                fpr[r] = fma(q.x, vp, fpr[r]);
-                fpi[r] = fma(q.y, vp, fpi[r]);
-                fmr[r] = fma(q.z, vm, fmr[r]);
-                fmi[r] = fma(q.w, vm, fmi[r]);
-            }
-            if (c + t < lmax) leg_advance<R, SPIN>(S, sT[t]);
+// Recurrence values of up to RMAX bands (one ring per lane and band).
+template <int RMAX> struct BandState {
+    double y[RMAX], up[RMAX], upp[RMAX], um[RMAX], ump[RMAX];
+};
+
+// Ring of this lane in a band; -1: none.
+__device__ inline int band_ring(const LegBand &b, int lane) { return (b.mask >> lane) & 1 ? b.jb + lane : -1; }
+
+// Degree at which a band enters an item that starts at la, and its state there:
+// its own start, or the state stored for the segment start la above it.
+__device__ inline int band_enter(const LegBand &b, int la) { return b.bs > la ? b.bs : la; }
+__device__ inline int64_t band_state(const LegBand &b, int la, int l0, int seg, int lane) {
+    const int k = b.bs >= la ? 0 : (la - l0) / seg - (b.bs - l0) / seg;
+    return ((int64_t)b.blk + k) * 64 + lane;
+}
+
+// Loads a band's state into slot r (zero until then).  The slots are filled one
+// chunk before the band enters, so that the loads are in flight meanwhile.
+template <int RMAX, bool SPIN>
+__device__ inline void band_load(const LegArgs &a, int r, int j, int64_t q, BandState<RMAX> &S) {
+    if (j >= 0) {
+        const double2 v = a.st_p[q];
+        S.y[r] = a.ring_y[j];
+        S.up[r] = v.x;
+        S.upp[r] = v.y;
+        if (SPIN) {
+            const double2 w = a.st_m[q];
+            S.um[r] = w.x;
+            S.ump[r] = w.y;
         }
     }
 }
 
-// True when some active ring of the wave holds an unscaled value; otherwise
-// every term of the current steps is exactly zero and only the recurrence
-// has to run.
-template <int R, bool SPIN> __device__ inline bool leg_live(const LegState<R, SPIN> &S) {
-    bool lv = false;
+// The first R bands over n steps (a multiple of 4) of a staged chunk:
+// accumulate lambda_l into the ring sums, then advance the recurrence.  The
+// coefficients of step t + 1 are read while step t computes; within a step the
+// independent work comes first (step coefficients (A +/- B) - A y of every
+// ring, accumulations), the dependent updates last.  Entries past the item's
+// last degree are zero: their steps add nothing.
+template <int R, int RMAX, bool SPIN>
+__device__ inline void synth_chunk(BandState<RMAX> &S, double *fpr, double *fpi, double *fmr, double *fmi,
+                                   const double4 *sT, const double4 *sQ, int n) {
+    double4 q = sQ[0];
+    double3 tc = make_double3(sT[0].x, sT[0].y, sT[0].z);
+#pragma unroll 1
+    for (int t4 = 0; t4 < n; t4 += 4)
 #pragma unroll
-    for (int r = 0; r < R; ++r) lv |= S.act[r] && (S.kp[r] == 0 || (SPIN && S.km[r] == 0));
-    return __any(lv);
-}
-
-// Recurrence alone over the steps t in [t0, t1) of a staged chunk; FULL: the
-// NS steps from t0 all advance (no guards).
-template <int R, bool SPIN, bool FULL, int NS>
-__device__ inline void advance_steps(LegState<R, SPIN> &S, const double4 *sT, int t0, int t1, int c, int lmax) {
-    if (FULL) {
-#pragma unroll 2
-        for (int u = 0; u < NS; ++u) leg_advance<R, SPIN>(S, sT[t0 + u]);
-    } else {
-        for (int t = t0; t < t1; ++t)
-            if (c + t < lmax) leg_advance<R, SPIN>(S, sT[t]);
-    }
-}
-
-// Steps b..b+7 of a staged chunk when all eight advance: fully unrolled, no guards.
-template <int R, bool SPIN>
-__device__ inline void synth_steps8(LegState<R, SPIN> &S, double *fpr, double *fpi, double *fmr, double *fmi,
-                                    const double4 *sT, const double4 *sQ, int b) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const double4 q = sQ[b + u];
+    for (int t = t4; t < t4 + 4; ++t) {
+        const double4 qn = sQ[t + 1];
+        const double3 tn = make_double3(sT[t + 1].x, sT[t + 1].y, sT[t + 1].z);
+        __builtin_amdgcn_sched_barrier(0);
+        double cpl[R], cmi[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double vp = S.up[r], vm = SPIN ? S.um[r] : S.up[r];
-            fpr[r] = fma(q.x, vp, fpr[r]);
-            fpi[r] = fma(q.y, vp, fpi[r]);
+            cpl[r] = fma(tc.x, S.y[r], tc.y);
+            if (SPIN) cmi[r] = fma(tc.x, S.y[r], tc.z);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double vm = SPIN ? S.um[r] : S.up[r];
+            fpr[r] = fma(q.x, S.up[r], fpr[r]);
+            fpi[r] = fma(q.y, S.up[r], fpi[r]);
             fmr[r] = fma(q.z, vm, fmr[r]);
             fmi[r] = fma(q.w, vm, fmi[r]);
         }
-        leg_advance<R, SPIN>(S, sT[b + u]);
-    }
-}
-
-// Scaled values in the synthesis.  The sums of a ring take its stored values
-// unmasked; while the ring's scale k is negative those terms are not its true
-// (negligible, below 2^-312) ones, so the sums restart when k reaches 0 and
-// are cleared at the end if it never does (synth_clear_scaled).
-template <int R, bool SPIN>
-__device__ inline void synth_renorm(LegState<R, SPIN> &S, double *fpr, double *fpi, double *fmr, double *fmi) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int kp0 = S.kp[r];
-        rescale_sel(S.up[r], S.upp[r], S.kp[r]);
-        const bool rp = kp0 < 0 && S.kp[r] == 0;
-        fpr[r] = rp ? 0.0 : fpr[r];
-        fpi[r] = rp ? 0.0 : fpi[r];
-        bool rm = rp;
-        if (SPIN) {
-            const int km0 = S.km[r];
-            rescale_sel(S.um[r], S.ump[r], S.km[r]);
-            rm = km0 < 0 && S.km[r] == 0;
-        }
-        fmr[r] = rm ? 0.0 : fmr[r];
-        fmi[r] = rm ? 0.0 : fmi[r];
-    }
-}
-
-template <int R, bool SPIN>
-__device__ inline void synth_clear_scaled(const LegState<R, SPIN> &S, double *fpr, double *fpi, double *fmr,
-                                          double *fmi) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (S.kp[r] < 0) fpr[r] = fpi[r] = 0.0;
-        if ((SPIN ? S.km[r] : S.kp[r]) < 0) fmr[r] = fmi[r] = 0.0;
-    }
-}
-
-// One work item of the synthesis with R rings per lane (the item holds at
-// most 64 R rings): the sums over the degrees l0 .. lend of order m, where the
-// recurrence starts from the seed at l0 = max(m, s) (soff < 0) or from the
-// states stored for l0 (soff >= 0, see leg_init_stored), written to the F
-// layout at Fout.
-template <int R, bool SPIN>
-__device__ inline void leg_synth_item(const LegArgs &a, const LegItem &it, int l0, int lend, int64_t soff,
-                                      const double4 *st_mu, const int2 *st_k, double *Fout,
-                                      double4 (*sbuf)[2][kStage + 1]) {
-    const int m = it.m, s = a.spin, lane = threadIdx.x;
-    if (l0 > lend) return;
-
-    const int64_t base = (int64_t)m * (2 * a.lmax + 1 - m) / 2;
-    const double4 *T4 = a.coef + base;
-    sbuf[0][lane >> 5][lane & 31] = stage_entry_synth(a, T4, base, m, l0, lend, lane);
-
-    LegState<R, SPIN> S;
-    if (soff < 0) leg_init<R, SPIN>(a, it, lane, S);
-    else leg_init_stored<R, SPIN>(a, m, it.jb, it.je, lane, st_mu, st_k, soff, S);
-    double fpr[R], fpi[R], fmr[R], fmi[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) fpr[r] = fpi[r] = fmr[r] = fmi[r] = 0.0;
-    bool scaled = leg_any_scaled<R, SPIN>(S);
-    __syncthreads();
-
-    int slot = 0;
-    for (int c = l0; c <= lend; c += kStage) {
-        const bool has_next = c + kStage <= lend;
-        double4 nv;
-        if (has_next) nv = stage_entry_synth(a, T4, base, m, c + kStage, lend, lane);
-        const double4 *sT = sbuf[slot][0], *sQ = sbuf[slot][1];
-        const int n = min(kStage, lend + 1 - c);
-        if (!scaled && has_next) {
-            // Full chunk, every step advances, no lane scaled: no per-step guards.
-            // The coefficients of step t + 1 are read while step t computes.
-            double4 q = sQ[0], tc = sT[0];
-#pragma unroll 4
-            for (int t = 0; t < kStage; ++t) {
-                double4 qn = sQ[t + 1], tn;
-                tn.x = sT[t + 1].x;
-                tn.y = sT[t + 1].y;
-                tn.z = sT[t + 1].z;
-                tn.w = 0.0;
-                // keep these loads ahead of the arithmetic of step t
-                __builtin_amdgcn_sched_barrier(0);
-                // Independent work first, dependent updates last, so that no
-                // FMA waits for the one just before it: the step coefficients
-                // (A +/- B) - A y of every ring, the accumulation of lambda_l,
-                // then the recurrence updates that use both.
-                double cpl[R], cmi[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    cpl[r] = fma(tc.x, S.y[r], tc.y);
-                    if (SPIN) cmi[r] = fma(tc.x, S.y[r], tc.z);
-                }
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double vm = SPIN ? S.um[r] : S.up[r];
-                    fpr[r] = fma(q.x, S.up[r], fpr[r]);
-                    fpi[r] = fma(q.y, S.up[r], fpi[r]);
-                    fmr[r] = fma(q.z, vm, fmr[r]);
-                    fmi[r] = fma(q.w, vm, fmi[r]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double np = fma(cpl[r], S.up[r], -S.upp[r]);
-                    S.upp[r] = S.up[r];
-                    S.up[r] = np;
-                    if (SPIN) {
-                        const double nm = fma(cmi[r], S.um[r], -S.ump[r]);
-                        S.ump[r] = S.um[r];
-                        S.um[r] = nm;
-                    }
-                }
-                q = qn;
-                tc = tn;
-            }
-        } else for (int b = 0; b < n; b += 8) {
-            const int e = min(b + 8, n);
-            const bool full = c + b + 8 <= lend;  // all eight steps exist and advance
-            if (scaled && !leg_live<R, SPIN>(S)) {
-                // no active ring in the double range yet: recurrence only
-                if (full) advance_steps<R, SPIN, true, 8>(S, sT, b, e, c, lend);
-                else advance_steps<R, SPIN, false, 8>(S, sT, b, e, c, lend);
-            } else if (full) {
-                synth_steps8<R, SPIN>(S, fpr, fpi, fmr, fmi, sT, sQ, b);
-            } else {
-                synth_steps<R, SPIN>(S, fpr, fpi, fmr, fmi, sT, sQ, b, e, c, lend);
-            }
-            if (scaled) {
-                synth_renorm<R, SPIN>(S, fpr, fpi, fmr, fmi);
-                scaled = leg_any_scaled<R, SPIN>(S);
+        for (int r = 0; r < R; ++r) {
+            const double np = fma(cpl[r], S.up[r], -S.upp[r]);
+            S.upp[r] = S.up[r];
+            S.up[r] = np;
+            if (SPIN) {
+                const double nm = fma(cmi[r], S.um[r], -S.ump[r]);
+                S.ump[r] = S.um[r];
+                S.um[r] = nm;
             }
         }
-        if (has_next) sbuf[slot ^ 1][lane >> 5][lane & 31] = nv;
-        __syncthreads();
-        slot ^= 1;
-    }
-
-    synth_clear_scaled<R, SPIN>(S, fpr, fpi, fmr, fmi);
-    const double sgn_neg = (s & 1) ? 1.0 : -1.0;  // -(-1)^s
-    double2 *Fp = reinterpret_cast<double2 *>(Fout) + (int64_t)(a.mmax + m) * a.nring;
-    double2 *Fm = reinterpret_cast<double2 *>(Fout) + (int64_t)(a.mmax - m) * a.nring;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (!S.act[r]) continue;
-        const int j = it.jb + r * 64 + lane;
-        Fp[j] = make_double2(-fpr[r], -fpi[r]);
-        if (m != 0) Fm[j] = make_double2(sgn_neg * fmr[r], sgn_neg * fmi[r]);
+        q = qn;
+        tc = tn;
     }
 }
 
-// An item with at most 64 rings (the remainder of an order's ring range)
-// runs the one-ring-per-lane body, at half the work of the R = 2 body.
-template <int R, bool SPIN>
-__global__ __launch_bounds__(64) void k_leg_synth(LegArgs a) {
-    __shared__ double4 sbuf[2][2][kStage + 1];  // one spare entry: the pipelined loop reads one step ahead
-    const int idx = leg_item_index(blockIdx.x, a.group);
-    if (idx >= a.nitems) return;
-    const LegItem it = a.items[idx];
-    if (it.je <= it.jb) return;
-    const int l0 = it.m > a.spin ? it.m : a.spin;
-    if (R > 1 && it.je - it.jb <= 64)
-        leg_synth_item<1, SPIN>(a, it, l0, a.lmax, -1, nullptr, nullptr, a.F, sbuf);
-    else
-        leg_synth_item<R, SPIN>(a, it, l0, a.lmax, -1, nullptr, nullptr, a.F, sbuf);
-}
-
-// Degree-segmented synthesis (plans whose items would not fill the GPU): an
-// item sums the degrees [la, lb) of its order, starting from the recurrence
-// state stored at plan time for la (every segment start is one of the
-// adjoint's), into F (segment 0) or into the partial copy of F of its segment
-// (segment k >= 1 at parts + (k - 1) part_stride doubles); k_synth_parts_sum
-// then adds the partials into F.
-struct SynSegArgs {
+// Synthesis: one wave per item, the degrees [la, lb) of order m for up to RMAX
+// bands.  Segment 0 of an order, and for each band the segment it starts in,
+// writes F; later segments write the partial copy of F of their segment
+// (segment k at parts + (k - 1) part_stride doubles), which k_synth_parts_sum
+// then adds into F.  RMAX = 4 reads each staged coefficient once for four
+// bands: 18 cycles of the CU's LDS pipe per step (four 16-byte broadcasts at
+// 4.4 cycles) against 32 FMAs (39 cycles over the four SIMDs); with two bands
+// the two are level and neither overlaps fully.
+struct SynthArgs {
     LegArgs a;
-    const SynSegItem *items;
+    const SynthItem *items;
     int nitems;
-    const double4 *st_mu;
-    const int2 *st_k;
+    int syn_seg;  // degrees per segment (0: one segment)
     double *parts;
     int64_t part_stride;
 };
 
-template <int R, bool SPIN>
-__global__ __launch_bounds__(64) void k_leg_synth_seg(SynSegArgs A) {
-    __shared__ double4 sbuf[2][2][kStage + 1];
-    if ((int)blockIdx.x >= A.nitems) return;
-    const SynSegItem q = A.items[blockIdx.x];
-    if (q.je <= q.jb) return;
-    const LegItem it{q.m, q.jb, q.je};
-    double *F = q.part == 0 ? A.a.F : A.parts + (int64_t)(q.part - 1) * A.part_stride;
-    if (R > 1 && q.je - q.jb <= 64)
-        leg_synth_item<1, SPIN>(A.a, it, q.la, q.lb - 1, q.soff, A.st_mu, A.st_k, F, sbuf);
-    else
-        leg_synth_item<R, SPIN>(A.a, it, q.la, q.lb - 1, q.soff, A.st_mu, A.st_k, F, sbuf);
+// What a wave of the synthesis works on.
+struct SynthWave {
+    const LegArgs &a;
+    const LegBand *bands;  // of the item
+    const double4 *T4;
+    double4 (*sbuf)[2][kStage + 1];
+    int64_t base;
+    int m, l0, la, lb, nb, lane;
+};
+
+// The chunks from c while R bands have entered, then those with one more (one
+// loop per R, so that the bands stay in their registers).  The next band is
+// loaded during the last chunk before it enters.
+template <int R, int RMAX, bool SPIN>
+__device__ __forceinline__ void synth_run(const SynthWave &w, BandState<RMAX> &S, double *fpr, double *fpi,
+                                          double *fmr, double *fmi, int c, int slot) {
+    const bool more = R < RMAX && R < w.nb;
+    const int cend = more ? min(band_enter(w.bands[R], w.la), w.lb) : w.lb;
+    auto load = [&] {
+        const LegBand b = w.bands[R];
+        band_load<RMAX, SPIN>(w.a, R, band_ring(b, w.lane), band_state(b, w.la, w.l0, w.a.seg, w.lane), S);
+    };
+    if constexpr (R < RMAX)
+        if (more && c >= cend) load();  // enters with the one before
+    if constexpr (R > 0) {
+#pragma unroll 1
+        for (; c < cend; c += kStage) {
+            double4 nv;
+            const bool has_next = c + kStage < w.lb;
+            if (has_next) nv = stage_entry_synth(w.a, w.T4, w.base, w.m, c + kStage, w.lb, w.lane);
+            if constexpr (R < RMAX)
+                if (more && c + kStage >= cend) load();
+            synth_chunk<R, RMAX, SPIN>(S, fpr, fpi, fmr, fmi, w.sbuf[slot][0], w.sbuf[slot][1],
+                                       min(kStage, (w.lb - c + 3) & ~3));
+            if (has_next) w.sbuf[slot ^ 1][w.lane >> 5][w.lane & 31] = nv;
+            __syncthreads();
+            slot ^= 1;
+        }
+    }
+    if constexpr (R < RMAX) {
+        if (c < w.lb) synth_run<R + 1, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, c, slot);
+    }
 }
 
-// F(m)[j] += the partials of segments 1 .. nseg_m - 1 for every written entry
-// (|m| <= ring_mmax[j] and order |m| has degrees), nseg_m = ceil((lmax + 1 -
-// max(|m|, s)) / S); one thread per entry of F, rings contiguous.
+template <int RMAX, bool SPIN>
+__global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
+    __shared__ double4 sbuf[2][2][kStage + 1];  // one spare entry: the pipelined loop reads one step ahead
+    const LegArgs &a = A.a;
+    if ((int)blockIdx.x >= A.nitems) return;
+    const SynthItem it = A.items[blockIdx.x];
+    if (it.nb <= 0) return;
+    const int m = it.m, s = a.spin, lane = threadIdx.x;
+    const LegBand *bands = a.bands + it.b0;
+    const int64_t base = (int64_t)m * (2 * a.lmax + 1 - m) / 2;
+    const double4 *T4 = a.coef + base;
+    const SynthWave w{a, bands, T4, sbuf, base, m, m > s ? m : s, it.la, it.lb, it.nb, lane};
+
+    BandState<RMAX> S;
+    double fpr[RMAX], fpi[RMAX], fmr[RMAX], fmi[RMAX];
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        S.y[r] = S.up[r] = S.upp[r] = S.um[r] = S.ump[r] = 0.0;
+        fpr[r] = fpi[r] = fmr[r] = fmi[r] = 0.0;
+    }
+    const int c = band_enter(bands[0], it.la);
+    sbuf[0][lane >> 5][lane & 31] = stage_entry_synth(a, T4, base, m, c, it.lb, lane);
+    __syncthreads();
+    synth_run<0, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, c, 0);
+
+    const double sgn_neg = (s & 1) ? 1.0 : -1.0;  // -(-1)^s
+    const int64_t op = (int64_t)(a.mmax + m) * a.nring, om = (int64_t)(a.mmax - m) * a.nring;
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        if (r >= it.nb) break;
+        const LegBand b = bands[r];
+        const int j = band_ring(b, lane);
+        const bool first = b.bs >= it.la;  // the band starts in this segment
+        double2 *F = reinterpret_cast<double2 *>(first ? a.F : A.parts + (int64_t)(it.part - 1) * A.part_stride);
+        if (j >= 0) {
+            F[op + j] = make_double2(-fpr[r], -fpi[r]);
+            if (m != 0) F[om + j] = make_double2(sgn_neg * fmr[r], sgn_neg * fmi[r]);
+        }
+    }
+}
+
+// F(m)[j] += the partials of the segments after the one the ring's band starts
+// in, for every written entry (|m| <= ring_mmax[j] and order |m| has degrees);
+// order |m| has ceil((lmax + 1 - max(|m|, s)) / S) segments.  One thread per
+// entry of F, rings contiguous.
 __global__ __launch_bounds__(256) void k_synth_parts_sum(double2 *F, const double2 *parts, int64_t part_stride,
+                                                         const LegOrder *orders, const int32_t *band_bs,
                                                          const int32_t *ring_mmax, int nring, int mmax, int lmax,
                                                          int spin, int S) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -474,10 +375,12 @@ __global__ __launch_bounds__(256) void k_synth_parts_sum(double2 *F, const doubl
     const int m = mi >= mmax ? mi - mmax : mmax - mi;
     const int l0 = m > spin ? m : spin;
     if (l0 > lmax || ring_mmax[j] < m) return;
+    const LegOrder o = orders[m];
+    const int k0 = (band_bs[o.band0 + ((o.last - j) >> 6)] - l0) / S;
     const int nseg = (lmax + 1 - l0 + S - 1) / S;
-    if (nseg < 2) return;
+    if (nseg < k0 + 2) return;
     double2 acc = F[e];
-    for (int k = 1; k < nseg; ++k) {
+    for (int k = k0 + 1; k < nseg; ++k) {
         const double2 v = parts[(int64_t)(k - 1) * part_stride + e];
         acc.x += v.x;
         acc.y += v.y;
@@ -486,141 +389,69 @@ __global__ __launch_bounds__(256) void k_synth_parts_sum(double2 *F, const doubl
 }
 
 // ---------------------------------------------------------------- adjoint
-
-
-// Fold of one l-step's four lane sums c0..c3 (Re and Im of the + and - sums)
-// into the transposed reduction, as soon as they are computed: a 32-lane swap
-// keeps component c + 2 bit5(i) in lane i, summed over lanes i and i ^ 32; the
-// two steps u and u + 1 then share a 16-lane swap that keeps step
-// u + bit4(i), summed over {i, i ^ 16, i ^ 32, i ^ 48}; the value of step
-// pair u / 2 and component parity c & 1 goes to red[row][2 (u / 2) + (c & 1)][col].
-template <int CH>
-__device__ inline void adj_fold(int u, double c0, double c1, double c2, double c3, double *w, double (*red)[CH][17],
-                                int row, int col) {
-    swap32(c0, c2);
-    c0 += c2;
-    swap32(c1, c3);
-    c1 += c3;
-    const int p = u >> 1;
-    if ((u & 1) == 0) {
-        w[0] = c0;
-        w[1] = c1;
-    } else {
-        // the pair's two values are final: to LDS at once, so that only two
-        // values per lane are live across the block
-        swap16(w[0], c0);
-        swap16(w[1], c1);
-        red[row][2 * p][col] = w[0] + c0;
-        red[row][2 * p + 1][col] = w[1] + c1;
-    }
-}
-
-// Scaled values in the adjoint.  A ring's map values enter its partial sums
-// only while its scale k is 0: they are held at zero while k < 0 and loaded
-// when k reaches 0, so the stored (scaled) values need no mask.
-template <int R, bool SPIN>
-__device__ inline void adj_load_f(const LegState<R, SPIN> &S, const double2 *Fp, const double2 *Fm, int j0,
-                                  int lane, double *fpr, double *fpi, double *fmr, double *fmi) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        fpr[r] = fpi[r] = fmr[r] = fmi[r] = 0.0;
-        if (S.act[r]) {
-            const int j = j0 + r * 64 + lane;
-            if (S.kp[r] == 0) {
-                const double2 vp = Fp[j];
-                fpr[r] = vp.x;
-                fpi[r] = vp.y;
-            }
-            if ((SPIN ? S.km[r] : S.kp[r]) == 0) {
-                const double2 vm = Fm[j];
-                fmr[r] = vm.x;
-                fmi[r] = -vm.y;  // conj F'(-m); for m = 0 the same column
-            }
-        }
-    }
-}
-
-template <int R, bool SPIN>
-__device__ inline void adj_renorm(LegState<R, SPIN> &S, const double2 *Fp, const double2 *Fm, int j0, int lane,
-                                  double *fpr, double *fpi, double *fmr, double *fmi) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int kp0 = S.kp[r], km0 = SPIN ? S.km[r] : 0;
-        rescale_sel(S.up[r], S.upp[r], S.kp[r]);
-        if (SPIN) rescale_sel(S.um[r], S.ump[r], S.km[r]);
-        const int j = j0 + r * 64 + lane;
-        if (kp0 < 0 && S.kp[r] == 0) {
-            const double2 vp = Fp[j];
-            fpr[r] = vp.x;
-            fpi[r] = vp.y;
-        }
-        if (SPIN ? (km0 < 0 && S.km[r] == 0) : (kp0 < 0 && S.kp[r] == 0)) {
-            const double2 vm = Fm[j];
-            fmr[r] = vm.x;
-            fmi[r] = -vm.y;
-        }
-    }
-}
-
-// ------------------------------------------------------- segmented adjoint
 //
-// Beyond its FMAs, the adjoint pays for reducing every l-step's four partial
-// sums over the 64 lanes (adj_fold and the LDS output stage): about 13
-// instructions per step and wave, whatever the number of rings a lane holds.
-// More rings per lane amortise that, but an order's rings then make few long
-// items (one or two per order), and the longest items set the time.  Items
-// cut in l restore the balance without repeating any recurrence: the item
-// (m, [la, lb)) starts from the recurrence state at l = la that the plan
-// stored for every ring and segment start (k_leg_adj_states).  The waves of a
-// workgroup hold disjoint rings of the order, fold their partial sums into
-// LDS, and wave 0 completes them over the waves and writes each output once
-// with a plain store (no atomics, no prior clear of the output).
+// An item sums the degrees [la, lb) of order m over every active ring of the
+// order (or one group of its bands, see AdjArgs::accumulate): G waves hold the
+// bands in turn (band i in wave i mod G), up to RMAX each, and take them in as
+// l passes their starts.  Beyond its FMAs the adjoint pays for reducing each
+// degree's four sums (Re and Im of A and B) over the 64 lanes, whatever the
+// number of bands a lane holds: hence up to eight bands per lane, and the
+// reduction goes through LDS.  Four degrees at a time, each lane writes its
+// sums as two 16-byte values per degree and reads back eight lanes' values of
+// one (degree, sum) pair: 7 complex additions per lane for 4 degrees, against
+// 13 instructions per degree (of which 6 half-rate permlane swaps) for a
+// transposed butterfly in registers.  The reads are consumed one step later,
+// so that their latency overlaps the next degree's FMAs.  Once per chunk of 32
+// degrees one wave adds the eight partial sums of every wave and writes each
+// output once, coalesced, with a plain store (no atomics, no prior clear).
+// Waves of an item meet only there.
 
-constexpr int kAdjRedDoubles = 4 * 8 * 17;  // one wave's fold area per 8-step block
+// double2 per (degree, sum) row of 64 lanes: with rows half of the banks apart,
+// lane i's read of entry (i >> 3, i & 7) has the bank of a contiguous read (at
+// 66, four tenths of the LDS cycles were conflicts)
+constexpr int kRedRow = 72;
+constexpr int kRed1 = 8 * kRedRow, kRed2 = 8 * 64;  // a wave's reduction areas (double2): 4 degrees; 32 degrees
 
 struct AdjArgs {
     LegArgs a;
     const AdjItem *items;
     int nitems;
-    const double4 *st_mu;
-    const int2 *st_k;
-    bool accumulate;  // ring groups: add into the (cleared) output instead of storing
+    bool accumulate;  // band groups: add into the (cleared) output instead of storing
 };
 
-// Rings [j0 + 64 r + lane] of order m: seeds (first segment) or the stored states.
-template <int R, bool SPIN>
-__device__ inline void adj_seg_init(const AdjArgs &A, const AdjItem &it, int j0, int lane, LegState<R, SPIN> &S) {
-    if (it.soff < 0) {
-        const LegItem li{it.m, j0, it.je};
-        leg_init<R, SPIN>(A.a, li, lane, S);
-        return;
-    }
-    leg_init_stored<R, SPIN>(A.a, it.m, j0, it.je, lane, A.st_mu, A.st_k, it.soff + (j0 - it.jb), S);
+// Recurrence coefficients of 16 degrees, degree c + i in lane i of every
+// 16-lane row: a step takes its own with three row broadcasts, which leaves the
+// LDS pipe to the reduction (as LDS broadcasts they took a quarter of it).
+struct RowCoef {
+    double x, y, z;
+};
+__device__ inline RowCoef row_coef(const double4 *T4, int c, int lmax, int lane) {
+    const int l = min(c + (lane & 15), lmax);
+    return RowCoef{T4[l].x, T4[l].y, T4[l].z};
 }
 
-// Zero outputs of order m for l in [l_from, l_to) (wave 0's lanes).
-__device__ inline void adj_zero_range(const LegArgs &a, int64_t base, int l_from, int l_to, int lane) {
-    for (int l = l_from + lane; l < l_to; l += 64) {
-        const int64_t kk = base + l;
-        reinterpret_cast<double2 *>(a.alm_out)[kk] = make_double2(0.0, 0.0);
-        reinterpret_cast<double2 *>(a.alm_out)[a.nalm + kk] = make_double2(0.0, 0.0);
-    }
-}
-
-// Eight steps from b of a staged chunk, all advancing (steps past the item's
-// last degree compute with zero-padded table entries; their folded values are
-// never written out): per ring, the step coefficients, the partial sums and
-// the recurrence update, folded step by step (adj_fold).
-template <int R, bool SPIN>
-__device__ inline void adj_seg_block(LegState<R, SPIN> &S, const double4 *sT, int b, const double *fpr,
-                                     const double *fpi, const double *fmr, const double *fmi, double (*red)[8][17],
-                                     int row, int col) {
-    double w[2];
-    double3 tn = make_double3(sT[b].x, sT[b].y, sT[b].z);
+// The first R bands over the 4 nblk <= 32 degrees from c, whose coefficients
+// are in T and then Tn (both move on by the degrees taken); block b's partial
+// sums (lane 8 (2 u + pair) + h: step u, A or B, lanes h mod 8) go to red2[b].
+// A block is read back in two groups of four values, after its last step and
+// after the next block's first one.
+template <int R, int RMAX, bool SPIN>
+__device__ inline void adj_chunk(BandState<RMAX> &S, const double *fpr, const double *fpi, const double *fmr,
+                                 const double *fmi, RowCoef &T, RowCoef &Tn, const double4 *T4, int c, int lmax,
+                                 double2 *red1, double2 *red2, int nblk, int lane) {
+    const double2 *rd = red1 + (lane >> 3) * kRedRow + (lane & 7);
+    double2 v[4], p;
+    auto sum4 = [&] {
+        return make_double2((v[0].x + v[1].x) + (v[2].x + v[3].x), (v[0].y + v[1].y) + (v[2].y + v[3].y));
+    };
+    auto read4 = [&](int i0) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const double3 tc = tn;
-        if (u + 1 < 8) tn = make_double3(sT[b + u + 1].x, sT[b + u + 1].y, sT[b + u + 1].z);
+        for (int i = 0; i < 4; ++i) v[i] = rd[8 * (i0 + i)];
+    };
+    auto step = [&](auto U, int b) {
+        constexpr int u = decltype(U)::value & 3;
+        const double tx = row_bcast<decltype(U)::value>(T.x), ty = row_bcast<decltype(U)::value>(T.y),
+                     tz = SPIN ? row_bcast<decltype(U)::value>(T.z) : 0.0;
         double pa_r = 0.0, pa_i = 0.0, pb_r = 0.0, pb_i = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -629,205 +460,337 @@ __device__ inline void adj_seg_block(LegState<R, SPIN> &S, const double4 *sT, in
             pa_i = fma(vp, fpi[r], pa_i);
             pb_r = fma(vm, fmr[r], pb_r);
             pb_i = fma(vm, fmi[r], pb_i);
-            const double np = fma(fma(tc.x, S.y[r], tc.y), vp, -S.upp[r]);
+            const double np = fma(fma(tx, S.y[r], ty), vp, -S.upp[r]);
             S.upp[r] = vp;
             S.up[r] = np;
             if (SPIN) {
-                const double nm = fma(fma(tc.x, S.y[r], tc.z), vm, -S.ump[r]);
+                const double nm = fma(fma(tx, S.y[r], tz), vm, -S.ump[r]);
                 S.ump[r] = vm;
                 S.um[r] = nm;
             }
         }
-        adj_fold<8>(u, pa_r, pa_i, pb_r, pb_i, w, red, row, col);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// Workgroup barrier for LDS data only: waits for this wave's LDS operations,
-// not for its outstanding global loads (the next table chunk stays in flight
-// across the barrier), then s_barrier.
-__device__ inline void lds_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt not waited for
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-template <int R, bool SPIN>
-__device__ void adj_seg_item(const AdjArgs &A, const AdjItem &it, int G, double4 (*sbuf)[kStage], double *redbase) {
-    const LegArgs &a = A.a;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m = it.m, s = a.spin, lmax = a.lmax;
-    const int l0 = m > s ? m : s;
-    const int la = it.la, lhi = it.lb - 1;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const double4 *T4 = a.coef + base;
-    if (threadIdx.x < 32) sbuf[0][threadIdx.x] = stage_entry(T4, la, lmax, threadIdx.x);
-    if (wave == 0 && it.soff < 0) adj_zero_range(a, base, m, l0, lane);  // l < s: no such harmonic
-
-    const int j0 = it.jb + wave * 64 * R;
-    LegState<R, SPIN> S;
-    adj_seg_init<R, SPIN>(A, it, j0, lane, S);
-    double fpr[R], fpi[R], fmr[R], fmi[R];
-    const double2 *Fp = reinterpret_cast<const double2 *>(a.F) + (int64_t)(a.mmax + m) * a.nring;
-    const double2 *Fm = reinterpret_cast<const double2 *>(a.F) + (int64_t)(a.mmax - m) * a.nring;
-    adj_load_f<R, SPIN>(S, Fp, Fm, j0, lane, fpr, fpi, fmr, fmi);
-    const double sgn_s = (s & 1) ? -1.0 : 1.0;
-    const int row = lane >> 4, col = lane & 15;
-    bool scaled = leg_any_scaled<R, SPIN>(S);
-    __syncthreads();
-
-    int slot = 0, buf = 0;
-    for (int c = la; c <= lhi; c += kStage) {
-        const bool has_next = c + kStage <= lhi;
-        double4 nv;
-        if (has_next && threadIdx.x < 32) nv = stage_entry(T4, c + kStage, lmax, threadIdx.x);
-        const double4 *sT = sbuf[slot];
-        const int n = min(kStage, lhi + 1 - c);
-        for (int b = 0; b < n; b += 8) {
-            double(*red)[8][17] = reinterpret_cast<double(*)[8][17]>(redbase + (buf * G + wave) * kAdjRedDoubles);
-            if (scaled && !leg_live<R, SPIN>(S)) {
-                // every active ring of this wave is below the double range: its
-                // partial sums are zero, only the recurrence runs
-                advance_steps<R, SPIN, true, 8>(S, sT, b, n, c, lhi);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) red[row][k][col] = 0.0;
-            } else {
-                adj_seg_block<R, SPIN>(S, sT, b, fpr, fpi, fmr, fmi, red, row, col);
-            }
-            if (scaled) {
-                adj_renorm<R, SPIN>(S, Fp, Fm, j0, lane, fpr, fpi, fmr, fmi);
-                scaled = leg_any_scaled<R, SPIN>(S);
-            }
-            // The fold areas of this block are double buffered: the next block
-            // writes the other one, so one barrier per block suffices.
-            lds_barrier();
-            if (wave == 0) {
-                // Step u, component c of wave g sits in row 2 (c >> 1) + (u & 1),
-                // value 2 (u >> 1) + (c & 1) of the wave's fold area.  Lane
-                // (u = lane >> 3, x = bit 2, h = lane & 3) adds columns 4h .. 4h + 3
-                // of A_x and B_x over the waves, the lane quad completes the sums,
-                // and lanes h = 0 and 1 write g~ and c~ of component x.
-                const int u = lane >> 3, x = (lane >> 2) & 1, h = lane & 3;
-                const int qa = u & 1, kv = 2 * (u >> 1) + x;
-                double sa = 0.0, sb = 0.0;
-                for (int g = 0; g < G; ++g) {
-                    const double(*rg)[8][17] =
-                        reinterpret_cast<const double(*)[8][17]>(redbase + (buf * G + g) * kAdjRedDoubles);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        sa += rg[qa][kv][4 * h + j];
-                        sb += rg[qa + 2][kv][4 * h + j];
-                    }
-                }
-                sa += quad_xor1(sa);
-                sb += quad_xor1(sb);
-                sa += quad_xor2(sa);
-                sb += quad_xor2(sb);
-                const int t = b + u;
-                if (h < 2 && t < n) {
-                    const int64_t kk = base + c + t;
-                    const double hP = (m == 0 ? 0.5 : 0.5 * a.mscale) * sT[t].w;
-                    // Im g~_l0 and Im c~_l0 vanish (reality condition)
-                    const bool imag = h == 0 ? x == 1 : x == 0;
-                    double val;
-                    double *dst;
-                    if (h == 0) {  // g~ = -hP (A + (-1)^s B), component x
-                        val = -hP * (sa + sgn_s * sb);
-                        dst = a.alm_out + 2 * kk + x;
-                    } else {  // c~ = (i/2) P (A - (-1)^s B): Im from the real parts, Re from the imaginary ones
-                        const double d = hP * (sa - sgn_s * sb);
-                        val = x == 0 ? d : -d;
-                        dst = a.alm_out + 2 * (a.nalm + kk) + (1 - x);
-                    }
-                    val = (m == 0 && imag) ? 0.0 : val;
-                    if (A.accumulate) atomicAdd(dst, val);
-                    else *dst = val;
-                }
-            }
-            buf ^= 1;
+        if (u == 0 && b > 0) {
+            p = sum4();
+            read4(4);  // before this step's writes to the same rows (LDS runs in program order)
         }
-        if (has_next && threadIdx.x < 32) sbuf[slot ^ 1][threadIdx.x] = nv;
-        lds_barrier();
-        slot ^= 1;
+        if (u == 1 && b > 0) {
+            const double2 q = sum4();
+            red2[(b - 1) * 64 + lane] = make_double2(p.x + q.x, p.y + q.y);
+        }
+        red1[2 * u * kRedRow + lane] = make_double2(pa_r, pa_i);
+        red1[(2 * u + 1) * kRedRow + lane] = make_double2(pb_r, pb_i);
+        __builtin_amdgcn_sched_barrier(0);
+        if (u == 3) {
+            read4(0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll 1
+    for (int b = 0; b < nblk; b += 2) {
+        step(std::integral_constant<int, 0>(), b);
+        step(std::integral_constant<int, 1>(), b);
+        step(std::integral_constant<int, 2>(), b);
+        step(std::integral_constant<int, 3>(), b);
+        if (b + 1 < nblk) {
+            step(std::integral_constant<int, 4>(), b + 1);
+            step(std::integral_constant<int, 5>(), b + 1);
+            step(std::integral_constant<int, 6>(), b + 1);
+            step(std::integral_constant<int, 7>(), b + 1);
+        }
+        if (b & 2) {
+            T = Tn;
+            Tn = row_coef(T4, c + 4 * b + 24, lmax, lane);
+        } else {
+            T.x = row_rotate8(T.x);
+            T.y = row_rotate8(T.y);
+            if (SPIN) T.z = row_rotate8(T.z);
+        }
+    }
+    p = sum4();
+    read4(4);
+    const double2 q = sum4();
+    red2[(nblk - 1) * 64 + lane] = make_double2(p.x + q.x, p.y + q.y);
+}
+
+// Barrier of an item's waves for LDS data only: waits for this wave's LDS
+// operations, not for its outstanding global loads (the next coefficients stay
+// in flight across the barrier), then s_barrier.  A wave that holds its item
+// alone needs neither: its LDS operations run in program order, and only the
+// compiler has to keep it.
+__device__ inline void lds_barrier(bool alone) {
+    asm volatile("" ::: "memory");
+    if (!alone) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt not waited for
+        __builtin_amdgcn_s_barrier();
+    }
+    asm volatile("" ::: "memory");
+}
+
+// Zero outputs of order m for l in [l_from, l_to), by thread i of n.
+__device__ inline void adj_zero_range(const LegArgs &a, int64_t base, int l_from, int l_to, int i, int n) {
+    double2 *out = reinterpret_cast<double2 *>(a.alm_out);
+    for (int l = l_from + i; l < l_to; l += n) {
+        out[base + l] = make_double2(0.0, 0.0);
+        out[a.nalm + base + l] = make_double2(0.0, 0.0);
     }
 }
 
-// One workgroup of G = blockDim.x / 64 waves per item (G = 1, 2 or 4, so that
-// whole workgroups fill a CU's wave slots); rings per lane chosen per item
-// (the waves of an item share it) up to RMAX.  About 34 VGPRs per ring: the
-// RMAX = 6 kernel takes 245 (two waves per SIMD), the RMAX = 4 kernel is
-// held to three waves per SIMD.
+// What an item's wave works on.
+struct AdjWave {
+    const LegArgs &a;
+    const LegBand *bands;  // of the item
+    const double4 *T4;
+    const double2 *Fp, *Fm;
+    double2 *red1, *red2, *red2all;
+    int64_t base;
+    int m, l0, la, lb, nb, G, wave, lane;
+    bool accumulate;
+};
+
+// The wave's band i of the item into slot r.
+template <int RMAX, bool SPIN>
+__device__ __forceinline__ void adj_load(const AdjWave &w, int r, int i, BandState<RMAX> &S, double *fpr, double *fpi,
+                                         double *fmr, double *fmi) {
+    const LegBand b = w.bands[i];
+    const int j = band_ring(b, w.lane);
+    band_load<RMAX, SPIN>(w.a, r, j, band_state(b, w.la, w.l0, w.a.seg, w.lane), S);
+    if (j >= 0) {
+        const double2 vp = w.Fp[j], vm = w.Fm[j];
+        fpr[r] = vp.x;
+        fpi[r] = vp.y;
+        fmr[r] = vm.x;
+        fmi[r] = vm.y;
+    }
+}
+
+// Adds the eight partials of every wave of the chunk from c and writes its n
+// degrees: lane 2 t + pair holds A or B of step t (rotated start: the lanes of
+// one LDS phase read distinct banks), the lane pair exchanges them and writes
+// g~ and c~.  P: that of degree c + t.
+__device__ __forceinline__ void adj_write(const AdjWave &w, int c, int n, double P) {
+    double sr = 0.0, si = 0.0;
+    for (int g = 0; g < w.G; ++g) {
+        const double2 *r2 = w.red2all + g * kRed2 + w.lane * 8;
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+            const double2 v = r2[(h + (w.lane >> 1)) & 7];
+            sr += v.x;
+            si += v.y;
+        }
+    }
+    if (w.lane & 1) si = -si;  // B sums conj F'(-m)
+    const double orr = quad_xor1(sr), oi = quad_xor1(si);
+    const int t = w.lane >> 1;
+    if (t >= n) return;
+    const double sgn_s = (w.a.spin & 1) ? -1.0 : 1.0;
+    const double hP = (w.m == 0 ? 0.5 : 0.5 * w.a.mscale) * P;
+    double2 val;
+    double *dst = w.a.alm_out + 2 * (w.base + c + t);
+    // Im g~_l0 and Im c~_l0 vanish (reality condition)
+    if ((w.lane & 1) == 0) {  // g~ = -hP (A + (-1)^s B)
+        val.x = -hP * (sr + sgn_s * orr);
+        val.y = w.m == 0 ? 0.0 : -hP * (si + sgn_s * oi);
+    } else {  // c~ = i hP (A - (-1)^s B)
+        val.x = -hP * (oi - sgn_s * si);
+        val.y = w.m == 0 ? 0.0 : hP * (orr - sgn_s * sr);
+        dst += 2 * w.a.nalm;
+    }
+    if (w.accumulate) {
+        atomicAdd(dst, val.x);
+        atomicAdd(dst + 1, val.y);
+    } else {
+        *reinterpret_cast<double2 *>(dst) = val;
+    }
+}
+
+// The chunks from c while the wave has R bands, then those with one more.  The
+// next band is loaded during the last chunk before it enters.  (One loop per R:
+// a switch over R inside a common loop shuffled the bands between registers
+// and scratch at every chunk, a fifth of all instructions.)
+template <int R, int RMAX, bool SPIN>
+__device__ __forceinline__ void adj_run(const AdjWave &w, BandState<RMAX> &S, double *fpr, double *fpi, double *fmr,
+                                        double *fmi, RowCoef &T, RowCoef &Tn, int c) {
+    const int i = R * w.G + w.wave;  // the wave's next band
+    const bool more = R < RMAX && i < w.nb;
+    const int cend = more ? min(band_enter(w.bands[i], w.la), w.lb) : w.lb;
+    const int lmax = w.a.lmax;
+    if constexpr (R < RMAX)
+        if (more && c >= cend) adj_load<RMAX, SPIN>(w, R, i, S, fpr, fpi, fmr, fmi);  // enters with the one before
+#pragma unroll 1
+    for (; c < cend; c += kStage) {
+        // P of the degree whose outputs this lane may write
+        const double P = w.T4[min(c + (w.lane >> 1), lmax)].w;
+        if constexpr (R < RMAX)
+            if (more && c + kStage >= cend) adj_load<RMAX, SPIN>(w, R, i, S, fpr, fpi, fmr, fmi);
+        const int n = min(kStage, w.lb - c), nblk = (n + 3) >> 2;
+        if constexpr (R == 0) {
+            for (int b = 0; b < nblk; ++b) w.red2[b * 64 + w.lane] = make_double2(0.0, 0.0);
+            T = row_coef(w.T4, c + kStage, lmax, w.lane);
+            Tn = row_coef(w.T4, c + kStage + 16, lmax, w.lane);
+        } else {
+            adj_chunk<R, RMAX, SPIN>(S, fpr, fpi, fmr, fmi, T, Tn, w.T4, c, lmax, w.red1, w.red2, nblk, w.lane);
+        }
+        lds_barrier(w.G == 1);
+        if (w.G == 1 || (((c - w.la) / kStage) & (w.G - 1)) == w.wave) adj_write(w, c, n, P);
+        lds_barrier(w.G == 1);
+    }
+    if constexpr (R < RMAX) {
+        if (c < w.lb) adj_run<R + 1, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, T, Tn, c);
+    }
+}
+
+// A workgroup of wg waves (1, 2 or 4) holds one item of wg waves, or wg items
+// of one wave each (orders or segments with at most RMAX started bands: more
+// bands per wave, no barriers).
 template <bool SPIN, int RMAX>
-__device__ inline void adj_seg_dispatch(const AdjArgs &A) {
-    __shared__ double4 sbuf[2][kStage];
-    extern __shared__ double redbase[];  // fold areas [2][G][4][8][17]
-    if ((int)blockIdx.x >= A.nitems) return;
-    const AdjItem it = A.items[blockIdx.x];
-    const int G = blockDim.x >> 6;
-    switch (it.R) {
-        case 0:
-            // no active ring: the order's outputs are zero
-            if (threadIdx.x < 64)
-                adj_zero_range(A.a, (int64_t)it.m * (2 * A.a.lmax + 1 - it.m) / 2, it.la, it.lb, threadIdx.x);
-            break;
-        case 1: adj_seg_item<1, SPIN>(A, it, G, sbuf, redbase); break;
-        case 2: adj_seg_item<2, SPIN>(A, it, G, sbuf, redbase); break;
-        case 3: adj_seg_item<3, SPIN>(A, it, G, sbuf, redbase); break;
-        case 4: adj_seg_item<4, SPIN>(A, it, G, sbuf, redbase); break;
-        case 5: if constexpr (RMAX >= 5) adj_seg_item<5, SPIN>(A, it, G, sbuf, redbase); break;
-        default: if constexpr (RMAX >= 6) adj_seg_item<6, SPIN>(A, it, G, sbuf, redbase); break;
-    }
-}
-
-template <bool SPIN>
-__global__ __launch_bounds__(256, 2) void k_leg_adj_seg6(AdjArgs A) { adj_seg_dispatch<SPIN, 6>(A); }
-template <bool SPIN>
-__global__ __launch_bounds__(256, 3) void k_leg_adj_seg4(AdjArgs A) { adj_seg_dispatch<SPIN, 4>(A); }
-
-// Plan time: one lane per ring runs the recurrence of order m from its seed
-// and stores (mu_l, mu_{l-1}) and the scales at every segment start
-// l = l0 + k S, k >= 1.
-template <bool SPIN>
-__global__ __launch_bounds__(64) void k_leg_adj_states(LegArgs a, const StateItem *items, int nitems, double4 *st_mu,
-                                                       int2 *st_k) {
-    if ((int)blockIdx.x >= nitems) return;
-    const StateItem it = items[blockIdx.x];
-    const int j = it.j0 + (int)threadIdx.x;
-    if (j >= it.je) return;
+__device__ inline void adj_item(const AdjArgs &A) {
+    extern __shared__ __align__(16) double2 redbase[];  // per wave: kRed1, then kRed2 of every wave
+    const LegArgs &a = A.a;
+    const int wg = blockDim.x >> 6, w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if ((int)blockIdx.x * wg + w0 >= A.nitems) return;
+    const AdjItem it = A.items[blockIdx.x * wg + w0];
+    const int G = it.waves, wave = G == 1 ? 0 : w0;
     const int m = it.m, s = a.spin, lmax = a.lmax;
     const int l0 = m > s ? m : s;
-    const double y = a.ring_y[j];
-    double up, um, upp = 0.0, ump = 0.0;
-    int kp, km;
-    leg_seed(a.kmant[m], a.kexp[m], m, s, a.ring_ch[j], a.ring_sh[j], up, kp, um, km);
-    if (!SPIN) {
-        um = up;
-        km = kp;
+    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
+    const LegBand *bands = a.bands + it.b0;
+    const int la = max(it.la, l0);
+    const int c0 = it.nb > 0 ? band_enter(bands[0], la) : it.lb;
+    // no ring has started (or l < s)
+    if (!A.accumulate) adj_zero_range(a, base, it.la, min(c0, it.lb), 64 * wave + lane, 64 * G);
+    if (it.nb <= 0) return;
+    double2 *red2 = redbase + wg * kRed1 + w0 * kRed2;
+    const double2 *F = reinterpret_cast<const double2 *>(a.F);
+    const double4 *T4 = a.coef + base;
+    const AdjWave w{a,    bands, T4, F + (int64_t)(a.mmax + m) * a.nring, F + (int64_t)(a.mmax - m) * a.nring,
+                    redbase + w0 * kRed1, red2, red2 - wave * kRed2, base, m, l0, la, it.lb, it.nb, G, wave, lane,
+                    A.accumulate};
+    BandState<RMAX> S;
+    double fpr[RMAX], fpi[RMAX], fmr[RMAX], fmi[RMAX];
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        S.y[r] = S.up[r] = S.upp[r] = S.um[r] = S.ump[r] = 0.0;
+        fpr[r] = fpi[r] = fmr[r] = fmi[r] = 0.0;
+    }
+    RowCoef T = row_coef(T4, c0, lmax, lane), Tn = row_coef(T4, c0 + 16, lmax, lane);
+    adj_run<0, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, T, Tn, c0);
+}
+
+template <bool SPIN>
+__global__ __launch_bounds__(256, 2) void k_leg_adj8(AdjArgs A) { adj_item<SPIN, 8>(A); }
+template <bool SPIN>
+__global__ __launch_bounds__(256, 2) void k_leg_adj4(AdjArgs A) { adj_item<SPIN, 4>(A); }
+
+// ------------------------------------------------------- starts and states
+
+// Plan time, one wave per band: the degree l0 + 32 i of the chunk in which a
+// ring of the band first has |lambda+-| >= 2^kLegStartExp (at most the last
+// chunk of the order).
+template <bool SPIN>
+__global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *bands, int nbands, int32_t *bs) {
+    if ((int)blockIdx.x >= nbands) return;
+    const LegBand b = bands[blockIdx.x];
+    const int lane = threadIdx.x, m = b.order, s = a.spin, lmax = a.lmax;
+    const int l0 = m > s ? m : s;
+    const int j = band_ring(b, lane);
+    const bool act = j >= 0;
+    const double thr = ldexp(1.0, kLegStartExp);
+    double y = 0.0, up = 0.0, um = 0.0, upp = 0.0, ump = 0.0;
+    int kp = 0, km = 0;
+    if (act) {
+        y = a.ring_y[j];
+        leg_seed(a.kmant[m], a.kexp[m], m, s, a.ring_ch[j], a.ring_sh[j], up, kp, um, km);
     }
     const double4 *T4 = a.coef + (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const int64_t nr = it.je - it.jb;
-    const int lend = l0 + (it.nseg - 1) * it.S;
-    int k = 1;
-    for (int l = l0; l < lend && l < lmax; ++l) {
-        const double4 t = T4[l];
-        const double np = fma(fma(t.x, y, t.y), up, -upp);
-        upp = up;
-        up = np;
-        leg_rescale(up, upp, kp);
-        if (SPIN) {
-            const double nm = fma(fma(t.x, y, t.z), um, -ump);
-            ump = um;
-            um = nm;
-            leg_rescale(um, ump, km);
+    int c = l0;
+    for (; c + kStage <= lmax; c += kStage) {
+        bool hit = false;
+#pragma unroll 8
+        for (int t = 0; t < kStage; ++t) {
+            const double4 f = T4[c + t];
+            hit |= kp == 0 && fabs(f.w * up) >= thr;
+            double n = fma(fma(f.x, y, f.y), up, -upp);
+            upp = up;
+            up = n;
+            if (SPIN) {
+                hit |= km == 0 && fabs(f.w * um) >= thr;
+                n = fma(fma(f.x, y, f.z), um, -ump);
+                ump = um;
+                um = n;
+            }
+            if ((t & 7) == 7) {  // 8 steps grow a value by far less than the headroom above 2^200
+                leg_rescale(up, upp, kp);
+                if (SPIN) leg_rescale(um, ump, km);
+            }
         }
-        if (l + 1 == l0 + k * it.S) {
-            const int64_t q = it.soff + (int64_t)(k - 1) * nr + (j - it.jb);
-            st_mu[q] = SPIN ? make_double4(up, upp, um, ump) : make_double4(up, upp, up, upp);
-            st_k[q] = make_int2(kp, SPIN ? km : kp);
-            ++k;
+        if (__any(hit)) break;
+    }
+    if (lane == 0) bs[blockIdx.x] = c;
+}
+
+// Plan time, one wave per band: stores the state (mu_l, mu_{l-1}) of both signs
+// at the band's start bs and at every segment start l0 + k seg above it (in
+// blocks of 64 from blk).  The values are stored in the double range: a value
+// below 2^-960 there (a ring far inside its band, or the weaker sign at high
+// spin) would lose digits; *lost counts the rings in which such a value grows
+// past the start threshold before the next stored state (the plan then takes
+// shorter segments).
+template <bool SPIN>
+__global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double2 *st_p, double2 *st_m,
+                                                   int32_t *lost) {
+    if ((int)blockIdx.x >= nbands) return;
+    const LegBand w = a.bands[blockIdx.x];
+    const int lane = threadIdx.x, m = w.order, s = a.spin, lmax = a.lmax;
+    const int l0 = m > s ? m : s;
+    const int j = band_ring(w, lane);
+    const bool act = j >= 0;
+    const double thr = ldexp(1.0, kLegStartExp), low = ldexp(1.0, -960);
+    double y = 0.0, up = 0.0, um = 0.0, upp = 0.0, ump = 0.0;
+    int kp = 0, km = 0;
+    if (act) {
+        y = a.ring_y[j];
+        leg_seed(a.kmant[m], a.kexp[m], m, s, a.ring_ch[j], a.ring_sh[j], up, kp, um, km);
+    }
+    const double4 *T4 = a.coef + (int64_t)m * (2 * lmax + 1 - m) / 2;
+    const int lsteps = lmax - l0;
+    bool lp = false, lm = false, bad = false;
+    // l advances in steps of 32 between the points that may store (bs and the
+    // segment starts are multiples of 32 from l0); seg is a multiple of 64
+    int64_t q = (int64_t)w.blk * 64 + lane;
+    const int klast = lsteps / a.seg;
+    for (int c = l0; c <= lmax; c += kStage) {
+        if (c == w.bs || (c > w.bs && (c - l0) % a.seg == 0)) {
+            const double vp = ldexp(up, kScaleStep * kp), vm = SPIN ? ldexp(um, kScaleStep * km) : vp;
+            st_p[q] = make_double2(vp, ldexp(upp, kScaleStep * kp));
+            lp = up != 0.0 && fabs(vp) < low;
+            if (SPIN) {
+                st_m[q] = make_double2(vm, ldexp(ump, kScaleStep * km));
+                lm = um != 0.0 && fabs(vm) < low;
+            }
+            q += 64;
+        }
+        if (c > w.bs && c - l0 >= klast * a.seg && !(lp || lm)) break;
+        const int n = min(kStage, lmax + 1 - c);
+#pragma unroll 8
+        for (int t = 0; t < n; ++t) {
+            const double4 f = T4[c + t];
+            bad |= lp && kp == 0 && fabs(f.w * up) >= thr;
+            double v = fma(fma(f.x, y, f.y), up, -upp);
+            upp = up;
+            up = v;
+            if (SPIN) {
+                bad |= lm && km == 0 && fabs(f.w * um) >= thr;
+                v = fma(fma(f.x, y, f.z), um, -ump);
+                ump = um;
+                um = v;
+            }
+            if ((t & 7) == 7) {
+                leg_rescale(up, upp, kp);
+                if (SPIN) leg_rescale(um, ump, km);
+            }
         }
     }
+    if (bad) atomicAdd(lost, 1);
 }
 
 // ------------------------------------------------------- batched maps (MFMA)
@@ -984,15 +947,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
 }
 
-// Arguments over the synthesis work list (64 R rings per item); the adjoint
-// replaces items and nitems by its own list.
-template <int R>
 static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, const void *alm_out, double *F) {
     const Geometry &g = p.g;
     LegArgs a;
-    a.items = p.d_leg_items;
-    a.nitems = p.n_leg_items;
-    a.group = (g.nring + 64 * R - 1) / (64 * R);
+    a.items = p.d_leg_items64;
+    a.nitems = p.n_leg_items64;
+    a.group = (g.nring + 63) / 64;
+    a.bands = p.d_bands;
+    a.st_p = reinterpret_cast<const double2 *>(p.d_st_p);
+    a.st_m = reinterpret_cast<const double2 *>(p.d_st_m);
+    a.seg = p.adj_seg;
     a.coef = reinterpret_cast<const double4 *>(p.leg->d_coef);
     a.kmant = p.leg->d_kmant;
     a.kexp = p.leg->d_kexp;
@@ -1013,69 +977,60 @@ static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, const void *al
     return a;
 }
 
-static int rings_knob(const char *name, int dflt) {
-    const char *e = getenv(name);
-    const int v = e ? atoi(e) : dflt;
-    return (v >= 1 && v <= 4) || v == 8 ? v : dflt;
-}
-
-// Rings per lane of the synthesis: PSHT_LEG_R (1, 2, 3, 4 or 8) fixes it for
-// tuning runs; without it 0, and the plan chooses 1 or 2 by the size of its
-// work list.
-int leg_rings_per_lane() {
-    static const int r = rings_knob("PSHT_LEG_R", 0);
+// Bands per wave of the synthesis: PSHT_LEG_R (1, 2 or 4) fixes it for tuning
+// runs; without it 0, and the plan chooses by the size of its work list.
+int leg_bands_per_wave() {
+    static const int r = [] {
+        const char *e = getenv("PSHT_LEG_R");
+        const int v = e ? atoi(e) : 0;
+        return v == 1 || v == 2 || v == 4 ? v : 0;
+    }();
     return r;
 }
 
 template <int R>
-static void leg_synth_r(const psht_plan_s &p, const void *alm, double *F, double mscale, hipStream_t st) {
-    LegArgs a = leg_args<R>(p, alm, nullptr, F);
-    a.mscale = mscale;
-    dim3 grid(p.n_leg_items), block(64);
-    if (p.g.spin) hipLaunchKernelGGL((k_leg_synth<R, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((k_leg_synth<R, false>), grid, block, 0, st, a);
+static void leg_synth_r(const SynthArgs &A, int spin, hipStream_t st) {
+    const dim3 grid(A.nitems), block(64);
+    if (spin) hipLaunchKernelGGL((k_leg_synth<R, true>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((k_leg_synth<R, false>), grid, block, 0, st, A);
+}
+
+static hipError_t leg_synth_list(const psht_plan_s &p, SynthArgs &A, const SynthItem *items, int nitems, int R,
+                                 hipStream_t st) {
+    if (nitems == 0) return hipSuccess;
+    A.items = items;
+    A.nitems = nitems;
+    if (R == 4) leg_synth_r<4>(A, p.g.spin, st);
+    else if (R == 2) leg_synth_r<2>(A, p.g.spin, st);
+    else leg_synth_r<1>(A, p.g.spin, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, double *F, double mscale, hipStream_t st) {
-    if (p.n_leg_items == 0) return hipSuccess;
-    switch (p.leg_rings_per_item / 64) {
-        case 1: leg_synth_r<1>(p, alm, F, mscale, st); break;
-        case 3: leg_synth_r<3>(p, alm, F, mscale, st); break;
-        case 2: leg_synth_r<2>(p, alm, F, mscale, st); break;
-        case 8: leg_synth_r<8>(p, alm, F, mscale, st); break;
-        default: leg_synth_r<4>(p, alm, F, mscale, st); break;
-    }
-    return hipGetLastError();
+    SynthArgs A;
+    A.a = leg_args(p, alm, nullptr, F);
+    A.a.mscale = mscale;
+    A.syn_seg = 0;
+    A.parts = nullptr;
+    A.part_stride = 0;
+    return leg_synth_list(p, A, p.d_leg_items, p.n_leg_items, p.leg_r, st);
 }
 
 hipError_t launch_leg_synth_parts(const psht_plan_s &p, const void *alm, double *F, double *parts,
                                   int64_t part_stride, double mscale, hipStream_t st) {
     if (p.syn_seg == 0) return launch_leg_synth(p, alm, F, mscale, st);
-    if (p.n_syn_items == 0) return hipSuccess;
-    SynSegArgs A;
-    A.a = leg_args<1>(p, alm, nullptr, F);
+    SynthArgs A;
+    A.a = leg_args(p, alm, nullptr, F);
     A.a.mscale = mscale;
-    A.items = p.d_syn_items;
-    A.nitems = p.n_syn_items;
-    A.st_mu = reinterpret_cast<const double4 *>(p.d_adj_mu);
-    A.st_k = reinterpret_cast<const int2 *>(p.d_adj_k);
+    A.syn_seg = p.syn_seg;
     A.parts = parts;
     A.part_stride = part_stride;
-    const dim3 grid(p.n_syn_items), block(64);
-    const bool two = p.syn_r == 2;
-    if (p.g.spin) {
-        if (two) hipLaunchKernelGGL((k_leg_synth_seg<2, true>), grid, block, 0, st, A);
-        else hipLaunchKernelGGL((k_leg_synth_seg<1, true>), grid, block, 0, st, A);
-    } else {
-        if (two) hipLaunchKernelGGL((k_leg_synth_seg<2, false>), grid, block, 0, st, A);
-        else hipLaunchKernelGGL((k_leg_synth_seg<1, false>), grid, block, 0, st, A);
-    }
-    hipError_t e = hipGetLastError();
+    hipError_t e = leg_synth_list(p, A, p.d_syn_items, p.n_syn_items, p.syn_r, st);
     if (e != hipSuccess || p.syn_parts == 0) return e;
     const int64_t n = (int64_t)(2 * p.g.mmax + 1) * p.g.nring;
     hipLaunchKernelGGL(k_synth_parts_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                        reinterpret_cast<double2 *>(F), reinterpret_cast<const double2 *>(parts), part_stride / 2,
-                       p.d_ring_mmax, p.g.nring, p.g.mmax, p.g.lmax, p.g.spin, p.syn_seg);
+                       p.d_orders, p.d_band_bs, p.d_ring_mmax, p.g.nring, p.g.mmax, p.g.lmax, p.g.spin, p.syn_seg);
     return hipGetLastError();
 }
 
@@ -1084,10 +1039,7 @@ hipError_t launch_leg_synth_batch(const psht_plan_s &p, int nb, const void *alm0
     if (nb < 1 || nb > kMaxLegBatch) return hipErrorInvalidValue;
     if (p.n_leg_items64 == 0) return hipSuccess;
     LegBatchArgs bt;
-    bt.a = leg_args<1>(p, nullptr, nullptr, nullptr);
-    bt.a.items = p.d_leg_items64;
-    bt.a.nitems = p.n_leg_items64;
-    bt.a.group = (p.g.nring + 63) / 64;
+    bt.a = leg_args(p, nullptr, nullptr, nullptr);
     bt.a.mscale = mscale;
     bt.alm0 = static_cast<const char *>(alm0);
     bt.alm_stride = alm_stride;
@@ -1099,52 +1051,52 @@ hipError_t launch_leg_synth_batch(const psht_plan_s &p, int nb, const void *alm0
     return hipGetLastError();
 }
 
-hipError_t launch_leg_adj_states(const psht_plan_s &p, const StateItem *items, int nitems, hipStream_t st) {
-    if (nitems == 0) return hipSuccess;
-    LegArgs a = leg_args<1>(p, nullptr, nullptr, nullptr);
-    double4 *mu = reinterpret_cast<double4 *>(p.d_adj_mu);
-    int2 *k = reinterpret_cast<int2 *>(p.d_adj_k);
-    if (p.g.spin) hipLaunchKernelGGL(k_leg_adj_states<true>, dim3(nitems), dim3(64), 0, st, a, items, nitems, mu, k);
-    else hipLaunchKernelGGL(k_leg_adj_states<false>, dim3(nitems), dim3(64), 0, st, a, items, nitems, mu, k);
+hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
+                             hipStream_t st) {
+    if (nbands == 0) return hipSuccess;
+    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr);
+    if (p.g.spin) hipLaunchKernelGGL(k_leg_starts<true>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
+    else hipLaunchKernelGGL(k_leg_starts<false>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
     return hipGetLastError();
 }
 
-static hipError_t leg_adjoint_seg(const psht_plan_s &p, const double *F, void *alm, double mscale, hipStream_t st) {
-    // orders above mmax have no ring: their outputs (the tail of g and of c) are zero
-    const int64_t nalm = (int64_t)(p.g.lmax + 1) * (p.g.lmax + 2) / 2;
-    if (p.adj_accumulate) {
-        hipError_t e = launch_fill_zero(alm, (size_t)nalm * 2 * 16, st);
-        if (e != hipSuccess) return e;
-    } else if (p.alm_tail < nalm) {
-        double2 *g = static_cast<double2 *>(alm);
-        hipError_t e = launch_fill_zero(g + p.alm_tail, (size_t)(nalm - p.alm_tail) * 16, st);
-        if (e == hipSuccess) e = launch_fill_zero(g + nalm + p.alm_tail, (size_t)(nalm - p.alm_tail) * 16, st);
-        if (e != hipSuccess) return e;
-    }
-    if (p.n_adj_items == 0) return hipSuccess;
-    AdjArgs A;
-    A.a = leg_args<1>(p, nullptr, alm, const_cast<double *>(F));
-    A.a.mscale = mscale;
-    A.items = p.d_adj_items;
-    A.nitems = p.n_adj_items;
-    A.st_mu = reinterpret_cast<const double4 *>(p.d_adj_mu);
-    A.st_k = reinterpret_cast<const int2 *>(p.d_adj_k);
-    A.accumulate = p.adj_accumulate;
-    const int G = p.adj_waves;
-    const size_t lds = sizeof(double) * 2 * G * kAdjRedDoubles;
-    const dim3 grid(p.n_adj_items), block(64 * G);
-    if (p.adj_rmax <= 4) {
-        if (p.g.spin) hipLaunchKernelGGL(k_leg_adj_seg4<true>, grid, block, lds, st, A);
-        else hipLaunchKernelGGL(k_leg_adj_seg4<false>, grid, block, lds, st, A);
-    } else {
-        if (p.g.spin) hipLaunchKernelGGL(k_leg_adj_seg6<true>, grid, block, lds, st, A);
-        else hipLaunchKernelGGL(k_leg_adj_seg6<false>, grid, block, lds, st, A);
-    }
+hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st) {
+    if (nbands == 0) return hipSuccess;
+    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr);
+    double2 *sp = reinterpret_cast<double2 *>(p.d_st_p), *sm = reinterpret_cast<double2 *>(p.d_st_m);
+    if (p.g.spin)
+        hipLaunchKernelGGL(k_leg_states<true>, dim3(nbands), dim3(64), 0, st, a, nbands, sp, sm, lost);
+    else
+        hipLaunchKernelGGL(k_leg_states<false>, dim3(nbands), dim3(64), 0, st, a, nbands, sp, sm, lost);
+    return hipGetLastError();
+}
+
+template <typename K>
+static hipError_t leg_adjoint_run(K kern, const psht_plan_s &p, const AdjArgs &A, hipStream_t st) {
+    const size_t lds = sizeof(double2) * (size_t)p.adj_waves * (kRed1 + kRed2);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(p.n_adj_items / p.adj_waves), dim3(64 * p.adj_waves), lds, st, A);
     return hipGetLastError();
 }
 
 hipError_t launch_leg_adjoint(const psht_plan_s &p, const double *F, void *alm, double mscale, hipStream_t st) {
-    return leg_adjoint_seg(p, F, alm, mscale, st);
+    const int64_t nalm = (int64_t)(p.g.lmax + 1) * (p.g.lmax + 2) / 2;
+    if (p.adj_accumulate) {
+        const hipError_t e = launch_fill_zero(alm, (size_t)nalm * 2 * 16, st);
+        if (e != hipSuccess) return e;
+    }
+    if (p.n_adj_items == 0) return hipSuccess;
+    AdjArgs A;
+    A.a = leg_args(p, nullptr, alm, const_cast<double *>(F));
+    A.a.mscale = mscale;
+    A.items = p.d_adj_items;
+    A.nitems = p.n_adj_items;
+    A.accumulate = p.adj_accumulate;
+    if (p.adj_rmax <= 4)
+        return p.g.spin ? leg_adjoint_run(k_leg_adj4<true>, p, A, st) : leg_adjoint_run(k_leg_adj4<false>, p, A, st);
+    return p.g.spin ? leg_adjoint_run(k_leg_adj8<true>, p, A, st) : leg_adjoint_run(k_leg_adj8<false>, p, A, st);
 }
 
 }  // namespace psht

@@ -52,4 +52,12 @@ __device__ inline double lane_xor8(double x) {
     return __hiloint2double(hi, lo);
 }
 
+// Lane N of each 16-lane row of x, in every lane of the row (the one DPP
+// permutation that moves 64-bit values, at full rate).
+template <int N> __device__ inline double row_bcast(double x) {
+    return __builtin_amdgcn_mov_dpp(x, 0x150 + N, 0xF, 0xF, false);
+}
+// Each 16-lane row of x rotated by 8 lanes: lane i gets lane i ^ 8.
+__device__ inline double row_rotate8(double x) { return lane_xor8(x); }
+
 }  // namespace psht

@@ -104,39 +104,32 @@ struct LegItem {
     int32_t m, jb, je;  // rings [jb, je) for this m
 };
 
-// Work item of the segmented Legendre adjoint: one workgroup of `waves`
-// wavefronts computes the outputs l in [la, lb) of order m from the active
-// rings [jb, je) of m (every ring of m, or one ring group of an order with
-// more rings than an item holds).  Wave w holds the 64 R consecutive rings
-// from jb + 64 R w, R per lane.  An item that does not start at the seed l0 = max(m, s) starts from the
-// recurrence state stored at plan time for l = la (index soff of the item's
-// first ring; -1 for the first segment).  R = 0: the order has no active ring
-// and its outputs are zero.
+// Bands of the Legendre stages (see k_legendre.hip): the rings [jb, jb + 64) of
+// an order, one per lane, counted from the order's last ring downwards, so that
+// the partial band is the innermost one.  The band starts at degree bs; its
+// stored states (bs, then every segment start above bs) are blocks of 64 from
+// blk.
+struct LegBand {
+    int32_t jb, bs, blk, order;  // order: m
+    uint64_t mask;               // lanes whose ring holds order m
+};
+struct LegOrder {
+    int32_t last, band0;  // last active ring of the order, index of its first band counted downwards from there
+};
+// log2 of |lambda| below which the terms of a ring are left out before the band's start
+constexpr int kLegStartExp = -64;
+
+// Work item of the synthesis: degrees [la, lb) of order m for the bands b0 ..
+// b0 + nb - 1 (sorted by start degree); segment number `part` of the order.
+struct SynthItem {
+    int32_t m, la, lb, b0, nb, part;
+};
+// Work item of the adjoint: the outputs l in [la, lb) of order m from the bands
+// b0 .. b0 + nb - 1 (all that start below lb, or one group of them), held by
+// `waves` waves.  nb = 0: the outputs are zero.  One entry per wave of the
+// launch: an item of several waves is repeated.
 struct AdjItem {
-    int32_t m, jb, je;
-    int32_t la, lb;
-    int32_t R;
-    int64_t soff;
-};
-
-// Plan-time recurrence states of the segmented adjoint: one lane per ring of
-// the 64 rings from j0 of order m (rings [jb, je) of the order), storing the
-// state at the nseg - 1 segment starts l0 + k S, k = 1..nseg-1, at
-// soff + (k - 1) (je - jb) + (j - jb).
-struct StateItem {
-    int32_t m, j0, jb, je, nseg, S;
-    int64_t soff;
-};
-
-// Work item of the degree-segmented synthesis: rings [jb, je) of order m
-// (at most 64 R), degrees [la, lb), starting from the seed (soff = -1, la =
-// max(m, s)) or from the adjoint's stored state of the item's first ring at
-// index soff; written to F (part 0) or to the partial copy `part` of F.
-struct SynSegItem {
-    int32_t m, jb, je;
-    int32_t la, lb;
-    int32_t part;
-    int64_t soff;
+    int32_t m, la, lb, b0, nb, waves;
 };
 
 // ------------------------------------------------------------------- plan
@@ -155,28 +148,28 @@ struct psht_plan_s {
     // rings
     double *d_ring_y = nullptr, *d_ring_ch = nullptr, *d_ring_sh = nullptr, *d_ring_w = nullptr;
     int32_t *d_ring_mmax = nullptr;
-    // Legendre work lists: synthesis (blocks of ring chunks per m)
-    psht::LegItem *d_leg_items = nullptr;
-    int n_leg_items = 0;
-    int leg_rings_per_item = 0;
-    // segmented adjoint: items, waves per workgroup, segment length, stored states
+    // Legendre bands and the states their recurrences start from
+    psht::LegBand *d_bands = nullptr;   // by order, sorted by start degree
+    psht::LegOrder *d_orders = nullptr; // by order
+    int32_t *d_band_bs = nullptr;       // start degrees, bands of an order from its last ring downwards
+    double *d_st_p = nullptr, *d_st_m = nullptr;  // [block][64] {mu_l, mu_{l-1}} of the + and - functions
+    // synthesis: items and bands per wave of the plain work list
+    psht::SynthItem *d_leg_items = nullptr;
+    int n_leg_items = 0, leg_r = 2;
+    // adjoint: items, waves per workgroup, segment length (degrees between stored states)
     psht::AdjItem *d_adj_items = nullptr;
     int n_adj_items = 0;
-    int adj_waves = 1;
-    int adj_rmax = 6;  // largest rings per lane of any item (selects the kernel instantiation)
-    bool adj_accumulate = false;  // ring groups: items add into a cleared output instead of storing
+    int adj_waves = 1;  // waves per workgroup: one item of so many waves, or as many items of one wave
+    int adj_rmax = 8;  // largest number of bands per wave of any item (selects the kernel instantiation)
+    bool adj_accumulate = false;  // band groups: items add into a cleared output instead of storing
     int adj_seg = 0;
-    double *d_adj_mu = nullptr;    // [state] {mu+_l, mu+_{l-1}, mu-_l, mu-_{l-1}}
-    int32_t *d_adj_k = nullptr;    // [state] {k+, k-}
     int64_t n_adj_states = 0;
-    int64_t alm_tail = 0;          // first coefficient index of order mmax + 1 (outputs zero from there)
     // degree-segmented synthesis (plans whose synthesis items would not fill
     // the GPU): items, segment length and number of partial copies of F
-    psht::SynSegItem *d_syn_items = nullptr;
-    int n_syn_items = 0;
+    psht::SynthItem *d_syn_items = nullptr;
+    int n_syn_items = 0, syn_r = 2;
     int syn_seg = 0;    // 0: not segmented
     int syn_parts = 0;  // partial copies of F (segments beyond the first of the longest order)
-    int syn_r = 2;      // rings per lane of the segmented items (1 or 2)
     psht::LegItem *d_leg_items64 = nullptr;  // 64-ring chunks (batched-maps kernel)
     int n_leg_items64 = 0;
     std::shared_ptr<psht::LegTable> leg;
@@ -218,10 +211,14 @@ hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, double *F, do
 hipError_t launch_leg_synth_parts(const psht_plan_s &p, const void *alm, double *F, double *parts,
                                   int64_t part_stride, double mscale, hipStream_t st);
 hipError_t launch_leg_adjoint(const psht_plan_s &p, const double *F, void *alm, double mscale, hipStream_t st);
-constexpr int kAdjMaxWavesHost = 4;  // waves per workgroup of the segmented adjoint
-constexpr int kAdjMaxRings = 6;      // rings per lane of the segmented adjoint
-// Plan time: the recurrence states of the segmented adjoint.
-hipError_t launch_leg_adj_states(const psht_plan_s &p, const StateItem *items, int nitems, hipStream_t st);
+constexpr int kAdjMaxWaves = 4;  // waves per workgroup of the adjoint
+constexpr int kAdjMaxBands = 8;  // bands per wave of the adjoint
+// Plan time: start degrees of the bands, then the states p.d_bands start from
+// (*lost counts states that do not fit the
+// double range although they matter later, see k_leg_states).
+hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
+                             hipStream_t st);
+hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st);
 
 // Legendre synthesis of nb <= kMaxLegBatch maps in one pass (MFMA): map b reads
 // its coefficients at alm0 + b alm_stride and writes F at F0 + b ws_stride
@@ -277,9 +274,9 @@ hipError_t launch_point_sort_order(psht_plan_s &p, int32_t *d_keys, const int32_
 struct TileGeom;
 TileGeom tile_geom(const psht_plan_s &p);
 
-// Rings per lane of the Legendre synthesis kernel (a work item covers 64 x
-// this many rings); 0 leaves the choice to the plan.
-int leg_rings_per_lane();
+// Bands per wave of the Legendre synthesis set for tuning runs; 0 leaves the
+// choice to the plan.
+int leg_bands_per_wave();
 
 // Largest FFT length one workgroup transforms in LDS (160 KB on gfx950).
 constexpr int kFftMaxLds64 = 10240;

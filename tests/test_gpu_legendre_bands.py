@@ -1,0 +1,82 @@
+"""Legendre stages that start each band of 64 rings at its first degree above
+2^-64: ring coefficients and the adjoint against the oracle and as each other's
+transpose, at the sizes where the bands, the stored states and the work lists
+change: a few rings, one ring past a band, more rings than one wave holds,
+high spins (states of the weaker sign far below the stronger one), the full
+sky, segments of every list."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from paper_2603_17166_amd import synthetic as syn
+from paper_2603_17166_amd.plan import Plan, plan_geometry
+
+pytestmark = pytest.mark.gpu
+DEG = math.pi / 180
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+# lmax, spin, cap radius (deg), full sky
+CASES = [
+    (3, 2, 5.0, False),
+    (40, 0, 30.0, False),
+    (130, 1, 60.0, False),
+    (256, 255, 20.0, False),   # spin next to lmax
+    (300, 150, 40.0, False),   # the two signs start hundreds of degrees apart
+    (200, 2, 100.0, True),     # rings past the equator: starts are not ordered by ring
+    (900, 0, 3.0, False),
+    (1500, 2, 65.0, False),    # more than 512 rings: two waves per item
+    (2500, 3, 1.5, False),     # deep polar orders
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "l%d-s%d-r%g-full%d" % c)
+def test_bands(case):
+    lmax, spin, rad, full = case
+    th, ph = syn.uniform_cap(400, rad * DEG, 14000 + lmax)
+    p = Plan(th, ph, lmax, spin, 1e-10, "fp64", full_sky=full)
+    i = p.info
+    L, mmax = i["Lmax"], i["mmax"]
+    a = syn.gaussian_alm(lmax, spin, 14100 + spin)
+    ad = torch.as_tensor(a).cuda()
+    F = p.legendre_synth(ad, workspace=True)
+    Fp = p.legendre_synth(ad)
+    thj = 2 * math.pi * np.arange(L + 1) / i["n2"] * i["theta_max"] / math.pi
+    rows = np.unique(np.linspace(0, L, 40).astype(int))
+    ref = oracle.ring_coeffs(a, thj[rows], lmax, spin, mmax)
+    # the entries a plan keeps (orders up to the ring's cut-off); a few units of
+    # roundoff per degree of the recurrence, as for the other work lists
+    cut = plan_geometry(lmax, spin, i["theta_star"], 1e-10, "fp64", full_sky=full)[3][rows]
+    ref[np.abs(np.arange(-mmax, mmax + 1))[:, None] > cut[None, :]] = 0.0
+    scale = np.max(np.abs(ref))
+    tol = max(1e-12, 1e-15 * lmax)
+    for name, G in (("workspace", F), ("plain", Fp)):
+        err = np.max(np.abs(G.cpu().numpy()[:, rows] - ref)) / scale
+        say("l%d s%d r%g: rings %d waves %d segments %d/%d, %s list vs oracle %.2e" % (
+            lmax, spin, rad, L + 1, i["adj_waves"], i["adj_segment"], i["syn_segment"], name, err))
+        assert err < tol
+    assert (lmax != 1500) or i["adj_waves"] == 2
+    # <legendre a, F'> = <a, legendre^T F'> for a random F' (the ring sums and their transpose over the same terms)
+    r = syn.rng(14200)
+    W = r.standard_normal(F.shape) + 1j * r.standard_normal(F.shape)
+    at = p.legendre_adjoint(torch.as_tensor(W).cuda()).cpu().numpy()
+    f = F.cpu().numpy()
+    lhs = float(np.sum((np.conj(f) * W).real))
+    rhs = oracle.alm_dot(a, at, lmax)
+    bound = np.linalg.norm(f) * np.linalg.norm(W)
+    say("  dot |lhs - rhs| / scale %.2e" % (abs(lhs - rhs) / bound))
+    assert abs(lhs - rhs) <= 1e-12 * bound
+    # the adjoint writes every coefficient
+    out = torch.full((2, syn.nalm(lmax)), complex(float("nan"), 1.0), dtype=torch.complex128, device="cuda")
+    p.stage(2, torch.as_tensor(W).cuda(), out)
+    assert bool(torch.isfinite(torch.view_as_real(out)).all())
+    p.close()
