@@ -504,7 +504,7 @@ def plan_rules(w, steps: int, log) -> dict:
 
 def batched_maps(w, nmaps: int, steps: int, check_points: int, log) -> dict:
     """nmaps coefficient sets / maps per call on one plan (the Legendre
-    synthesis runs as one MFMA pass per group of up to 8 maps)."""
+    synthesis shares its recurrence between maps)."""
     import torch
 
     import oracle

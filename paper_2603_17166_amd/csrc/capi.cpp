@@ -401,7 +401,6 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
 
     // synthesis items: seg degrees per segment (0: one segment), R bands per wave
     auto synth_items = [&](int seg, int R, int x, std::vector<psht::SynthItem> &list, std::vector<double> &c) {
-        int parts = 0;
         for (int m = x < 0 ? 0 : x; m <= M; m += x < 0 ? 1 : 8) {
             const int l0 = std::max(m, s), b0 = orders[m].band0, nb = orders[m + 1].band0 - b0;
             const int len = seg > 0 ? seg : lmax + 1;
@@ -415,25 +414,31 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
                     if (n == 0) continue;
                     list.push_back(psht::SynthItem{m, la, lb, b0 + q, n, k});
                     c.push_back(w + 0.3 * (lb - std::max(la, bands[b0 + q].bs)));
-                    parts = std::max(parts, k);
                 }
         }
-        return parts;
     };
     const int fixed = psht::leg_bands_per_wave();
-    {
-        std::vector<psht::SynthItem> syn;
-        std::vector<double> c;
+    // segmented lists: syn_seg degrees; and for calls of several maps, which fill
+    // the GPU with fewer items, four times as many (fewer copies of F to add; 8
+    // maps at lmax 2048 on a 5-degree disc: 146 -> 115 us) with two bands per wave
+    p.syn_parts = 0;
+    if (p.syn_seg > 0) {
         p.syn_r = fixed ? fixed : 4;
-        p.syn_parts = 0;
-        if (p.syn_seg > 0) {
-            (void)synth_items(p.syn_seg, p.syn_r, -1, syn, c);
+        // copies for every segment of the longest order
+        p.syn_parts = (lmax + 1 - s + p.syn_seg - 1) / p.syn_seg - 1;
+        p.multi_seg = 4 * p.syn_seg < lmax + 1 - s ? 4 * p.syn_seg : 0;
+        p.multi_r = fixed ? fixed : 2;
+        auto list = [&](int seg, int R, psht::SynthItem *&d, int &n) {
+            std::vector<psht::SynthItem> syn;
+            std::vector<double> c;
+            synth_items(seg, R, -1, syn, c);
             longest_first(syn, c);
-            // copies for every segment of the longest order
-            p.syn_parts = (lmax + 1 - s + p.syn_seg - 1) / p.syn_seg - 1;
-            if (!upload(p, p.d_syn_items, syn, st)) return nomem("uploading the synthesis work list");
-        }
-        p.n_syn_items = (int)syn.size();
+            n = (int)syn.size();
+            return upload(p, d, syn, st);
+        };
+        if (!list(p.syn_seg, p.syn_r, p.d_syn_items, p.n_syn_items) ||
+            (p.multi_seg > 0 && !list(p.multi_seg, p.multi_r, p.d_multi_items, p.n_multi_items)))
+            return nomem("uploading the synthesis work list");
     }
     // plain list: the items of an order on one XCD (blocks are dealt round-robin
     // to the eight), so that they share its L2, each XCD's longest first
@@ -442,7 +447,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     size_t most = 0;
     for (int x = 0; x < 8; ++x) {
         std::vector<double> c;
-        (void)synth_items(0, p.leg_r, x, per[x], c);
+        synth_items(0, p.leg_r, x, per[x], c);
         longest_first(per[x], c);
         most = std::max(most, per[x].size());
     }
@@ -529,31 +534,8 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
         !upload(p, p.d_ring_w, g.ring_w, st) || !upload(p, p.d_ring_mmax, g.ring_mmax, st))
         return fail(PSHT_ERR_NOMEM, "uploading ring tables");
 
-    // Legendre bands, states and work lists; and the list of 64-ring chunks of
-    // the batched-maps kernel (groups padded to a multiple of 8)
+    // Legendre bands, states and work lists
     {
-        const int group = (g.nring + 63) / 64;
-        std::vector<psht::LegItem> items((size_t)(((g.mmax + 1) + 7) / 8 * 8) * group, psht::LegItem{0, 0, 0});
-        for (int m = 0; m <= g.mmax; ++m) {
-            int first = -1, last = -1;
-            for (int j = 0; j < g.nring; ++j)
-                if (g.ring_mmax[j] >= m) {
-                    if (first < 0) first = j;
-                    last = j;
-                }
-            for (int c = 0; c < group; ++c) {
-                psht::LegItem &it = items[(size_t)m * group + c];
-                it.m = m;
-                if (first < 0) continue;
-                const int jb = first + c * 64, je = std::min(jb + 64, last + 1);
-                if (jb < je) {
-                    it.jb = jb;
-                    it.je = je;
-                }
-            }
-        }
-        p.n_leg_items64 = (int)items.size();
-        if (!upload(p, p.d_leg_items64, items, st)) return fail(PSHT_ERR_NOMEM, "uploading Legendre work list");
         int dev = 0, ncu = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -637,17 +619,12 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
     return PSHT_OK;
 }
 
-// Smallest number of maps that takes the batched Legendre pass: its cost does
-// not depend on the number of maps (the MFMA tiles always hold 8), and it
-// beats the one-map pass from about 4.6 maps on (PSHT_MM_MIN overrides it
-// for tuning runs; a value above 8 disables the batched pass).
-int leg_batch_min() {
-    static int v = [] {
-        const char *e = getenv("PSHT_MM_MIN");
-        const int x = e ? atoi(e) : 5;
-        return x >= 2 ? x : 5;
-    }();
-    return v;
+// Maps per launch of the stages after the Legendre step (before it, in the
+// adjoint): as many as keep their V and U, which one stage writes and the next
+// reads, within half of the 256 MB last-level cache.
+int maps_per_launch(const psht_plan_s &p, int nmaps) {
+    const size_t room = size_t(128) << 20, one = std::max<size_t>(p.ws_V + p.ws_U, 1);
+    return (int)std::min<size_t>((size_t)nmaps, std::max<size_t>(1, std::min<size_t>(room / one, 1024)));
 }
 
 bool check_ws(const psht_plan_s &p, int nmaps, void *ws, size_t ws_bytes) {
@@ -707,36 +684,28 @@ psht_status psht::synth_run(psht_plan plan, int nmaps, const void *alm, void *ma
     const size_t alm_bytes = (size_t)(g.lmax + 1) * (g.lmax + 2) / 2 * 2 * 16;
     const size_t map_bytes = (size_t)plan->npts * (g.fp32 ? 8 : 16);
     psht_plan_s &P = *plan;
-    const int batch_min = leg_batch_min();
+    const int64_t wss = (int64_t)P.ws_per_map;
+    char *ws = static_cast<char *>(workspace);
+    constexpr int kMost = 1024;  // maps per Legendre launch
     for (int i = 0; i < nmaps;) {
-        // groups of batch_min..8 maps share one batched (MFMA) Legendre pass
-        const int nb = nmaps - i >= batch_min ? std::min(nmaps - i, psht::kMaxLegBatch) : 1;
-        char *ws0 = static_cast<char *>(workspace) + (size_t)i * plan->ws_per_map;
-        const char *a0 = static_cast<const char *>(alm) + i * alm_bytes;
-        hipError_t e;
-        if (nb > 1)
-            e = timed(P, PSHT_T_LEG_SYNTH, st, [&] {
-                return psht::launch_leg_synth_batch(P, nb, a0, (int64_t)alm_bytes, ws0, (int64_t)plan->ws_per_map,
-                                                    mscale, st);
-            });
-        else
-            e = timed(P, PSHT_T_LEG_SYNTH, st, [&] {
-                return psht::launch_leg_synth_parts(P, a0, reinterpret_cast<double *>(ws0),
-                                                    reinterpret_cast<double *>(ws0 + plan->ws_F),
-                                                    (int64_t)(plan->ws_F / 8), mscale, st);
-            });
-        for (int b = 0; b < nb && e == hipSuccess; ++b) {
-            char *ws = ws0 + (size_t)b * plan->ws_per_map;
-            double *F = reinterpret_cast<double *>(ws);
-            void *V = ws + plan->ws_F;
-            void *U = ws + plan->ws_F + plan->ws_V;
-            void *m = static_cast<char *>(map) + (size_t)(i + b) * map_bytes;
-            e = timed(P, PSHT_T_THETA_SYNTH, st, [&] { return psht::launch_theta_synth(P, F, V, st); });
-            if (e == hipSuccess) e = timed(P, PSHT_T_PHI_SYNTH, st, [&] { return psht::launch_phi_synth(P, V, U, st); });
-            if (e == hipSuccess) e = timed(P, PSHT_T_INTERP, st, [&] { return psht::launch_interp(P, U, m, st); });
+        const int nl = std::min(nmaps - i, kMost), group = maps_per_launch(P, nl);
+        hipError_t e = timed(P, PSHT_T_LEG_SYNTH, st, [&] {
+            return psht::launch_leg_synth(P, static_cast<const char *>(alm) + i * alm_bytes, ws + i * wss, true,
+                                          psht::MapBatch{nl, wss}, mscale, st);
+        });
+        for (int k = i; k < i + nl && e == hipSuccess; k += group) {
+            const psht::MapBatch mb{std::min(group, i + nl - k), wss};
+            char *F = ws + k * wss, *V = F + P.ws_F, *U = V + P.ws_V;
+            e = timed(P, PSHT_T_THETA_SYNTH, st, [&] { return psht::launch_theta_synth(P, F, V, mb, st); });
+            if (e == hipSuccess)
+                e = timed(P, PSHT_T_PHI_SYNTH, st, [&] { return psht::launch_phi_synth(P, V, U, mb, st); });
+            if (e == hipSuccess)
+                e = timed(P, PSHT_T_INTERP, st, [&] {
+                    return psht::launch_interp(P, U, static_cast<char *>(map) + k * map_bytes, mb, st);
+                });
         }
         if (e != hipSuccess) return device_fail(e, "synthesis launch");
-        i += nb;
+        i += nl;
     }
     return PSHT_OK;
 }
@@ -754,20 +723,21 @@ psht_status adjoint_impl(psht_plan plan, int nmaps, const void *map, void *alm, 
     const psht::Geometry &g = plan->g;
     const size_t alm_bytes = (size_t)(g.lmax + 1) * (g.lmax + 2) / 2 * 2 * 16;
     const size_t map_bytes = (size_t)plan->npts * (g.fp32 ? 8 : 16);
-    for (int i = 0; i < nmaps; ++i) {
-        char *ws = static_cast<char *>(workspace) + (size_t)i * plan->ws_per_map;
-        double *F = reinterpret_cast<double *>(ws);
-        void *V = ws + plan->ws_F;
-        void *U = ws + plan->ws_F + plan->ws_V;
-        void *a = static_cast<char *>(alm) + i * alm_bytes;
+    psht_plan_s &P = *plan;
+    const int64_t wss = (int64_t)P.ws_per_map;
+    const int group = maps_per_launch(P, std::max(nmaps, 1));
+    for (int i = 0; i < nmaps; i += group) {
+        const psht::MapBatch mb{std::min(group, nmaps - i), wss};
+        char *F = static_cast<char *>(workspace) + i * wss, *V = F + P.ws_F, *U = V + P.ws_V;
         const void *m = static_cast<const char *>(map) + i * map_bytes;
-        psht_plan_s &P = *plan;
-        hipError_t e = timed(P, PSHT_T_GRID_ZERO, st, [&] { return psht::launch_fill_zero(U, P.ws_U, st); });
-        if (e == hipSuccess) e = timed(P, PSHT_T_SPREAD, st, [&] { return psht::launch_spread(P, m, U, st); });
-        if (e == hipSuccess) e = timed(P, PSHT_T_PHI_ADJ, st, [&] { return psht::launch_phi_adjoint(P, U, V, st); });
-        if (e == hipSuccess) e = timed(P, PSHT_T_THETA_ADJ, st, [&] { return psht::launch_theta_adjoint(P, V, F, st); });
-
-        if (e == hipSuccess) e = timed(P, PSHT_T_LEG_ADJ, st, [&] { return psht::launch_leg_adjoint(P, F, a, mscale, st); });
+        void *a = static_cast<char *>(alm) + i * alm_bytes;
+        hipError_t e = timed(P, PSHT_T_GRID_ZERO, st, [&] { return psht::launch_grid_zero(P, U, mb, st); });
+        if (e == hipSuccess) e = timed(P, PSHT_T_SPREAD, st, [&] { return psht::launch_spread(P, m, U, mb, st); });
+        if (e == hipSuccess) e = timed(P, PSHT_T_PHI_ADJ, st, [&] { return psht::launch_phi_adjoint(P, U, V, mb, st); });
+        if (e == hipSuccess)
+            e = timed(P, PSHT_T_THETA_ADJ, st, [&] { return psht::launch_theta_adjoint(P, V, F, mb, st); });
+        if (e == hipSuccess)
+            e = timed(P, PSHT_T_LEG_ADJ, st, [&] { return psht::launch_leg_adjoint(P, F, a, mb, mscale, st); });
         if (e != hipSuccess) return device_fail(e, "adjoint launch");
     }
     return PSHT_OK;
@@ -1004,10 +974,13 @@ psht_status psht_stage_ex(psht_plan plan, int stage, const void *in, void *out, 
             return fail(PSHT_ERR_WORKSPACE, "workspace smaller than workspace_bytes_per_map");
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const psht::Geometry &g = plan->g;
-        hipError_t e = psht::launch_fill_zero(out, (size_t)(2 * g.mmax + 1) * g.nring * 16, st);
+        hipError_t e = hipSuccess;
+        // F and its partial copies lie in the workspace; F then goes to the output
+        char *F = static_cast<char *>(workspace);
+        if (e == hipSuccess) e = psht::launch_fill_zero(F, plan->ws_F, st);
+        if (e == hipSuccess) e = psht::launch_leg_synth(*plan, in, F, true, psht::MapBatch(), 1.0, st);
         if (e == hipSuccess)
-            e = psht::launch_leg_synth_parts(*plan, in, static_cast<double *>(out), static_cast<double *>(workspace),
-                                             (int64_t)(plan->ws_F / 8), 1.0, st);
+            e = hipMemcpyAsync(out, F, (size_t)(2 * g.mmax + 1) * g.nring * 16, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return device_fail(e, "stage launch");
         return PSHT_OK;
     }
@@ -1025,14 +998,14 @@ psht_status psht_stage_ex(psht_plan plan, int stage, const void *in, void *out, 
     void *U = ws + P.ws_F + P.ws_V;
     hipError_t e;
     if (stage == PSHT_STAGE_FOURIER_SYNTH) {
-        e = psht::launch_theta_synth(P, static_cast<const double *>(in), V, st);
-        if (e == hipSuccess) e = psht::launch_phi_synth(P, V, U, st);
-        if (e == hipSuccess) e = psht::launch_interp(P, U, out, st);
+        e = psht::launch_theta_synth(P, in, V, psht::MapBatch(), st);
+        if (e == hipSuccess) e = psht::launch_phi_synth(P, V, U, psht::MapBatch(), st);
+        if (e == hipSuccess) e = psht::launch_interp(P, U, out, psht::MapBatch(), st);
     } else {
-        e = psht::launch_fill_zero(U, P.ws_U, st);
-        if (e == hipSuccess) e = psht::launch_spread(P, in, U, st);
-        if (e == hipSuccess) e = psht::launch_phi_adjoint(P, U, V, st);
-        if (e == hipSuccess) e = psht::launch_theta_adjoint(P, V, static_cast<double *>(out), st);
+        e = psht::launch_grid_zero(P, U, psht::MapBatch(), st);
+        if (e == hipSuccess) e = psht::launch_spread(P, in, U, psht::MapBatch(), st);
+        if (e == hipSuccess) e = psht::launch_phi_adjoint(P, U, V, psht::MapBatch(), st);
+        if (e == hipSuccess) e = psht::launch_theta_adjoint(P, V, out, psht::MapBatch(), st);
     }
     if (e != hipSuccess) return device_fail(e, "stage launch");
     return PSHT_OK;
@@ -1045,10 +1018,10 @@ psht_status psht_stage(psht_plan plan, int stage, const void *in, void *out, voi
     hipError_t e;
     if (stage == PSHT_STAGE_LEGENDRE_SYNTH) {
         e = psht::launch_fill_zero(out, (size_t)(2 * g.mmax + 1) * g.nring * 16, st);
-        if (e == hipSuccess) e = psht::launch_leg_synth(*plan, in, static_cast<double *>(out), 1.0, st);
+        if (e == hipSuccess) e = psht::launch_leg_synth(*plan, in, out, false, psht::MapBatch(), 1.0, st);
     } else if (stage == PSHT_STAGE_LEGENDRE_ADJOINT) {
         e = psht::launch_fill_zero(out, (size_t)(g.lmax + 1) * (g.lmax + 2) / 2 * 2 * 16, st);
-        if (e == hipSuccess) e = psht::launch_leg_adjoint(*plan, static_cast<const double *>(in), out, 1.0, st);
+        if (e == hipSuccess) e = psht::launch_leg_adjoint(*plan, in, out, psht::MapBatch(), 1.0, st);
     } else {
         return fail(PSHT_ERR_ARG, "unknown stage");
     }

@@ -247,7 +247,13 @@ struct StageArgs {
     const double *ring_w;
     const int32_t *ring_mmax;
     const double *psihat_t, *psihat_p;
+    int64_t ws_stride;  // bytes between the workspaces of the maps (blockIdx.y)
 };
+
+// The pointer p of the batch's first map moved to this block's map.
+template <typename T> __device__ inline T *map_ptr(T *p, const StageArgs &a) {
+    return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + blockIdx.y * a.ws_stride);
+}
 
 // Column of the Theta stage handled by block b.  Blocks are dealt to the 8
 // XCDs round-robin; this map gives each XCD one contiguous range of columns,
@@ -277,6 +283,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth(StageArgs a, const double2 *F,
                                                              typename CT<T>::type *V) {
     typedef typename CT<T>::type C;
+    F = map_ptr(F, a);
+    V = map_ptr(V, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     const int mi = xcd_column(blockIdx.x, 2 * a.mmax + 1);
@@ -324,6 +332,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth_split(StageArgs a, const double2 *F,
                                                              typename CT<T>::type *V) {
     typedef typename CT<T>::type C;
+    F = map_ptr(F, a);
+    V = map_ptr(V, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     const int mi = xcd_column(blockIdx.x, 2 * a.mmax + 1);
@@ -382,6 +392,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_adjoint(StageArgs a, const typename CT<T>::type *V,
                                                                double2 *F) {
     typedef typename CT<T>::type C;
+    V = map_ptr(V, a);
+    F = map_ptr(F, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     const int mi = xcd_column(blockIdx.x, 2 * a.mmax + 1);
@@ -428,6 +440,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_adjoint_split(StageArgs a, const typename CT<T>::type *V,
                                                                double2 *F) {
     typedef typename CT<T>::type C;
+    V = map_ptr(V, a);
+    F = map_ptr(F, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     const int mi = xcd_column(blockIdx.x, 2 * a.mmax + 1);
@@ -522,6 +536,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_phi_synth(StageArgs a, const typename CT<T>::type *V,
                                                            typename CT<T>::type *U) {
     typedef typename CT<T>::type C;
+    V = map_ptr(V, a);
+    U = map_ptr(U, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     int r, h;
@@ -567,6 +583,8 @@ template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_phi_adjoint(StageArgs a, const typename CT<T>::type *U,
                                                              typename CT<T>::type *V) {
     typedef typename CT<T>::type C;
+    U = map_ptr(U, a);
+    V = map_ptr(V, a);
     extern __shared__ __align__(16) unsigned char smem[];
     C *buf = reinterpret_cast<C *>(smem);
     int r, h;
@@ -606,7 +624,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_phi_adjoint(StageArgs 
 
 // ---------------------------------------------------------------- launch
 
-static StageArgs stage_args(const psht_plan_s &p) {
+static StageArgs stage_args(const psht_plan_s &p, const MapBatch &mb) {
     const Geometry &g = p.g;
     StageArgs a;
     a.fn2 = to_dev(p.fft_n2.f);
@@ -631,6 +649,7 @@ static StageArgs stage_args(const psht_plan_s &p) {
     a.ring_mmax = p.d_ring_mmax;
     a.psihat_t = p.d_psihat_t;
     a.psihat_p = p.d_psihat_p;
+    a.ws_stride = mb.ws_stride;
     return a;
 }
 
@@ -651,7 +670,7 @@ template <typename Fn> static void tier_dispatch(int n, Fn fn) {
 }
 
 template <typename T>
-static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, const double2 *F, void *V, hipStream_t st) {
+static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const double2 *F, void *V, hipStream_t st) {
     typedef typename CT<T>::type C;
     const int n = p.theta_split ? p.g.N2 : p.g.Ntheta;
     const size_t lds = (size_t)n * sizeof(C);
@@ -660,11 +679,11 @@ static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, const 
         constexpr int MX = decltype(M)::value;
         if (p.theta_split) {
             if ((err = set_lds(k_theta_synth_split<T, MX>, lds)) != hipSuccess) return;
-            hipLaunchKernelGGL((k_theta_synth_split<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1)), dim3(fft_threads<T>(MX)),
+            hipLaunchKernelGGL((k_theta_synth_split<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1), nmaps), dim3(fft_threads<T>(MX)),
                                lds, st, a, F, static_cast<C *>(V));
         } else {
             if ((err = set_lds(k_theta_synth<T, MX>, lds)) != hipSuccess) return;
-            hipLaunchKernelGGL((k_theta_synth<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1)), dim3(fft_threads<T>(MX)), lds,
+            hipLaunchKernelGGL((k_theta_synth<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1), nmaps), dim3(fft_threads<T>(MX)), lds,
                                st, a, F, static_cast<C *>(V));
         }
     });
@@ -672,7 +691,7 @@ static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, const 
 }
 
 template <typename T>
-static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, const void *V, double2 *F, hipStream_t st) {
+static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, double2 *F, hipStream_t st) {
     typedef typename CT<T>::type C;
     const int n = p.theta_split ? p.g.N2 : p.g.Ntheta;
     const size_t lds = (size_t)n * sizeof(C);
@@ -681,11 +700,11 @@ static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, cons
         constexpr int MX = decltype(M)::value;
         if (p.theta_split) {
             if ((err = set_lds(k_theta_adjoint_split<T, MX>, lds)) != hipSuccess) return;
-            hipLaunchKernelGGL((k_theta_adjoint_split<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1)),
+            hipLaunchKernelGGL((k_theta_adjoint_split<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1), nmaps),
                                dim3(fft_threads<T>(MX)), lds, st, a, static_cast<const C *>(V), F);
         } else {
             if ((err = set_lds(k_theta_adjoint<T, MX>, lds)) != hipSuccess) return;
-            hipLaunchKernelGGL((k_theta_adjoint<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1)), dim3(fft_threads<T>(MX)),
+            hipLaunchKernelGGL((k_theta_adjoint<T, MX>), dim3(xcd_grid(2 * p.g.mmax + 1), nmaps), dim3(fft_threads<T>(MX)),
                                lds, st, a, static_cast<const C *>(V), F);
         }
     });
@@ -693,7 +712,7 @@ static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, cons
 }
 
 template <typename T>
-static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, const void *V, void *U, hipStream_t st) {
+static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, void *U, hipStream_t st) {
     typedef typename CT<T>::type C;
     const int nh = p.g.Nphi / p.g.phi_parts;
     const size_t lds = (size_t)nh * sizeof(C);
@@ -701,7 +720,7 @@ static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, const vo
     tier_dispatch(nh, [&](auto M) {
         constexpr int MX = decltype(M)::value;
         if ((err = set_lds(k_phi_synth<T, MX>, lds)) != hipSuccess) return;
-        hipLaunchKernelGGL((k_phi_synth<T, MX>), dim3(phi_grid(p.g.rows_used, p.g.phi_parts)), dim3(fft_threads<T>(MX)), lds,
+        hipLaunchKernelGGL((k_phi_synth<T, MX>), dim3(phi_grid(p.g.rows_used, p.g.phi_parts), nmaps), dim3(fft_threads<T>(MX)), lds,
                            st, a,
                            static_cast<const C *>(V), static_cast<C *>(U));
     });
@@ -709,7 +728,7 @@ static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, const vo
 }
 
 template <typename T>
-static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, const void *U, void *V, hipStream_t st) {
+static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *U, void *V, hipStream_t st) {
     typedef typename CT<T>::type C;
     const int nh = p.g.Nphi / p.g.phi_parts;
     const size_t lds = (size_t)nh * sizeof(C);
@@ -717,39 +736,39 @@ static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, const 
     tier_dispatch(nh, [&](auto M) {
         constexpr int MX = decltype(M)::value;
         if ((err = set_lds(k_phi_adjoint<T, MX>, lds)) != hipSuccess) return;
-        hipLaunchKernelGGL((k_phi_adjoint<T, MX>), dim3(phi_grid(p.g.rows_used, p.g.phi_parts)), dim3(fft_threads<T>(MX)),
+        hipLaunchKernelGGL((k_phi_adjoint<T, MX>), dim3(phi_grid(p.g.rows_used, p.g.phi_parts), nmaps), dim3(fft_threads<T>(MX)),
                            lds, st, a,
                            static_cast<const C *>(U), static_cast<C *>(V));
     });
     return err;
 }
 
-hipError_t launch_theta_synth(const psht_plan_s &p, const double *F, void *V, hipStream_t st) {
-    const StageArgs a = stage_args(p);
-    const double2 *F2 = reinterpret_cast<const double2 *>(F);
-    const hipError_t e = p.g.fp32 ? theta_synth_t<float>(p, a, F2, V, st) : theta_synth_t<double>(p, a, F2, V, st);
+hipError_t launch_theta_synth(const psht_plan_s &p, const void *F, void *V, const MapBatch &mb, hipStream_t st) {
+    const StageArgs a = stage_args(p, mb);
+    const double2 *F2 = static_cast<const double2 *>(F);
+    const hipError_t e = p.g.fp32 ? theta_synth_t<float>(p, a, mb.n, F2, V, st) : theta_synth_t<double>(p, a, mb.n, F2, V, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
-hipError_t launch_theta_adjoint(const psht_plan_s &p, const void *V, double *F, hipStream_t st) {
-    const StageArgs a = stage_args(p);
-    double2 *F2 = reinterpret_cast<double2 *>(F);
-    const hipError_t e = p.g.fp32 ? theta_adjoint_t<float>(p, a, V, F2, st) : theta_adjoint_t<double>(p, a, V, F2, st);
+hipError_t launch_theta_adjoint(const psht_plan_s &p, const void *V, void *F, const MapBatch &mb, hipStream_t st) {
+    const StageArgs a = stage_args(p, mb);
+    double2 *F2 = static_cast<double2 *>(F);
+    const hipError_t e = p.g.fp32 ? theta_adjoint_t<float>(p, a, mb.n, V, F2, st) : theta_adjoint_t<double>(p, a, mb.n, V, F2, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
-hipError_t launch_phi_synth(const psht_plan_s &p, const void *V, void *U, hipStream_t st) {
-    const StageArgs a = stage_args(p);
-    const hipError_t e = p.g.fp32 ? phi_synth_t<float>(p, a, V, U, st) : phi_synth_t<double>(p, a, V, U, st);
+hipError_t launch_phi_synth(const psht_plan_s &p, const void *V, void *U, const MapBatch &mb, hipStream_t st) {
+    const StageArgs a = stage_args(p, mb);
+    const hipError_t e = p.g.fp32 ? phi_synth_t<float>(p, a, mb.n, V, U, st) : phi_synth_t<double>(p, a, mb.n, V, U, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
-hipError_t launch_phi_adjoint(const psht_plan_s &p, const void *U, void *V, hipStream_t st) {
-    const StageArgs a = stage_args(p);
-    const hipError_t e = p.g.fp32 ? phi_adjoint_t<float>(p, a, U, V, st) : phi_adjoint_t<double>(p, a, U, V, st);
+hipError_t launch_phi_adjoint(const psht_plan_s &p, const void *U, void *V, const MapBatch &mb, hipStream_t st) {
+    const StageArgs a = stage_args(p, mb);
+    const hipError_t e = p.g.fp32 ? phi_adjoint_t<float>(p, a, mb.n, U, V, st) : phi_adjoint_t<double>(p, a, mb.n, U, V, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }

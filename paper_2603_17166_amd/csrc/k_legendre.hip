@@ -26,6 +26,7 @@
 //
 // The per-(l, m) recurrence coefficients and coefficient combinations are
 // wave-uniform: they are staged through LDS one chunk of 32 degrees ahead.
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -36,9 +37,6 @@
 namespace psht {
 
 struct LegArgs {
-    const LegItem *items;  // 64-ring chunks (batched-maps kernel)
-    int nitems;
-    int group;  // items per order m
     const LegBand *bands;  // sorted by start degree within each order
     const double2 *st_p, *st_m;  // stored states {mu_l, mu_{l-1}} of the + and - functions
     int seg;               // degrees between stored states
@@ -46,114 +44,31 @@ struct LegArgs {
     const double *kmant;
     const int32_t *kexp;
     const double *ring_y, *ring_ch, *ring_sh;
-    const int32_t *ring_mmax;
     int nring, lmax, spin, mmax;
     int64_t nalm;
-    const double2 *g, *c;  // synthesis input: g_lm and c_lm, complex [nalm] each
-    double *alm_out;   // adjoint output, complex [2][nalm]
-    double *F;         // complex [2 mmax + 1][nring]: synthesis output / adjoint input
+    const char *alm_in;  // synthesis input of map 0: g_lm then c_lm, complex [nalm] each
+    char *alm_out;       // adjoint output of map 0, complex [2][nalm]
+    char *F;             // complex [2 mmax + 1][nring] of map 0: synthesis output / adjoint input
+    int64_t alm_stride, F_stride;  // bytes between the coefficients / the F (workspaces) of consecutive maps
+    int nmaps;
     double mscale;     // extra factor on the inputs (synthesis) or outputs (adjoint) of order m >= 1
 };
 
-// Block -> item map: the `group` items of one order m run on the same XCD
-// (blocks are dealt round-robin to the 8 XCDs), and every XCD starts with the
-// low orders, which carry the most work.
-__device__ inline int leg_item_index(int bid, int group) {
-    int xcd = bid & 7, k = bid >> 3;
-    int q = k / group, i = k - q * group;
-    return (xcd + 8 * q) * group + i;
-}
-
-// Branch-free renormalisation of a scaled pair (see leg_common.h).
-__device__ inline void rescale_sel(double &cur, double &prev, int &k) {
-    const bool big = (k < 0) && (fabs(cur) > PSHT_RESCALE_HI);
-    const double f = big ? PSHT_RESCALE_FACTOR : 1.0;
-    cur *= f;
-    prev *= f;
-    k += big ? 1 : 0;
-}
-
-template <int R, bool SPIN> struct LegState {
-    double y[R], up[R], upp[R], um[R], ump[R];
-    int kp[R], km[R];
-    bool act[R];
-};
-
-// Seeds of the R rings of this lane for order m.
-template <int R, bool SPIN>
-__device__ inline void leg_init(const LegArgs &a, const LegItem &it, int lane, LegState<R, SPIN> &S) {
-    const int m = it.m, s = a.spin;
-    const double kmant = a.kmant[m];
-    const int kexp = a.kexp[m];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int j = it.jb + r * 64 + lane;
-        S.act[r] = (j < it.je) && (a.ring_mmax[j] >= m);
-        S.y[r] = 0.0;
-        S.up[r] = S.um[r] = S.upp[r] = S.ump[r] = 0.0;
-        S.kp[r] = S.km[r] = 0;
-        if (S.act[r]) {
-            S.y[r] = a.ring_y[j];
-            leg_seed(kmant, kexp, m, s, a.ring_ch[j], a.ring_sh[j], S.up[r], S.kp[r], S.um[r], S.km[r]);
-            if (!SPIN) {
-                S.um[r] = S.up[r];
-                S.km[r] = S.kp[r];
-            }
-        }
-    }
-}
-
-template <int R, bool SPIN> __device__ inline bool leg_any_scaled(const LegState<R, SPIN> &S) {
-    bool sc = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) sc |= S.act[r] && (S.kp[r] < 0 || (SPIN && S.km[r] < 0));
-    return __any(sc);
-}
-
-// mu_{l+1} = ((A +/- B) - A y) mu_l - mu_{l-1}
-template <int R, bool SPIN> __device__ inline void leg_advance(LegState<R, SPIN> &S, const double4 t) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double np = fma(fma(t.x, S.y[r], t.y), S.up[r], -S.upp[r]);
-        S.upp[r] = S.up[r];
-        S.up[r] = np;
-        if (SPIN) {
-            const double nm = fma(fma(t.x, S.y[r], t.z), S.um[r], -S.ump[r]);
-            S.ump[r] = S.um[r];
-            S.um[r] = nm;
-        }
-    }
-}
-
-template <int R, bool SPIN> __device__ inline void leg_renorm(LegState<R, SPIN> &S) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        rescale_sel(S.up[r], S.upp[r], S.kp[r]);
-        if (SPIN) rescale_sel(S.um[r], S.ump[r], S.km[r]);
-    }
-}
-
 // The coefficient stream of one order m ({-A, A+B, A-B, P} and, for the
-// synthesis, the combinations Q) is staged through LDS in chunks of kStage
-// steps: every lane loads one 32-byte entry of the next chunk (coalesced)
-// while the current chunk is computed from wave-uniform (broadcast) LDS reads.
+// synthesis, the combinations Q) is staged in chunks of kStage degrees: by the
+// synthesis through LDS, every lane loading 32-byte entries of the next chunk
+// (coalesced) while the current chunk is computed from wave-uniform (broadcast)
+// LDS reads.
 constexpr int kStage = 32;
-
-// Entry `lane` of the chunk starting at c: the recurrence table, zero past lmax.
-__device__ inline double4 stage_entry(const double4 *T4, int c, int lmax, int lane) {
-    const int l = c + (lane & 31);
-    return l <= lmax ? T4[l] : make_double4(0.0, 0.0, 0.0, 0.0);
-}
 
 // The synthesis multiplies lambda+ by P (g + i c) and lambda- by P (conj g +
 // i conj c) (Sec. I, with lambda_l = P_l mu_l): the four real combinations
 // P {g_r - c_i, g_i + c_r, g_r + c_i, c_r - g_i} of order m at degree l
 // (coefficient index k), with the imaginary parts of the m = 0 coefficients
 // dropped and the inputs of order m >= 1 scaled by mscale.
-__device__ inline double4 synth_combo(const double2 *g, const double2 *c, const double4 *coef, int64_t k, int m,
+__device__ inline double4 synth_combo(const double2 *g, const double2 *c, double P, int64_t k, int m,
                                       double mscale) {
     double2 a = g[k], b = c[k];
-    double P = coef[k].w;
     if (m == 0) {
         a.y = 0.0;
         b.y = 0.0;
@@ -163,18 +78,11 @@ __device__ inline double4 synth_combo(const double2 *g, const double2 *c, const 
     return make_double4((a.x - b.y) * P, (a.y + b.x) * P, (a.x + b.y) * P, (b.x - a.y) * P);
 }
 
-// Synthesis staging: lanes 0..31 read the recurrence table, lanes 32..63 form
-// the coefficient combinations of the same 32 degrees; zero from lend on.
-__device__ inline double4 stage_entry_synth(const LegArgs &a, const double4 *T4, int64_t base, int m, int c,
-                                            int lend, int lane) {
-    const int l = c + (lane & 31);
-    double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (l < lend) {
-        if (lane < 32) v = T4[l];
-        else v = synth_combo(a.g, a.c, a.coef, base + l, m, a.mscale);
-    }
-    return v;
-}
+// Staged chunk of the synthesis: the recurrence table and the coefficient
+// combinations of NM maps (one spare entry: the loop reads one step ahead).
+template <int NM> struct SynthChunk {
+    double4 T[kStage + 1], Q[NM][kStage + 1];
+};
 
 // Recurrence values of up to RMAX bands (one ring per lane and band).
 template <int RMAX> struct BandState {
@@ -209,23 +117,26 @@ __device__ inline void band_load(const LegArgs &a, int r, int j, int64_t q, Band
     }
 }
 
-// The first R bands over n steps (a multiple of 4) of a staged chunk:
-// accumulate lambda_l into the ring sums, then advance the recurrence.  The
-// coefficients of step t + 1 are read while step t computes; within a step the
-// independent work comes first (step coefficients (A +/- B) - A y of every
+// The first R bands and NM maps over n steps (a multiple of 4) of a staged
+// chunk: accumulate lambda_l into the ring sums, then advance the recurrence.
+// The coefficients of step t + 1 are read while step t computes; within a step
+// the independent work comes first (step coefficients (A +/- B) - A y of every
 // ring, accumulations), the dependent updates last.  Entries past the item's
 // last degree are zero: their steps add nothing.
-template <int R, int RMAX, bool SPIN>
-__device__ inline void synth_chunk(BandState<RMAX> &S, double *fpr, double *fpi, double *fmr, double *fmi,
-                                   const double4 *sT, const double4 *sQ, int n) {
-    double4 q = sQ[0];
-    double3 tc = make_double3(sT[0].x, sT[0].y, sT[0].z);
+template <int R, int RMAX, int NM, bool SPIN>
+__device__ inline void synth_chunk(BandState<RMAX> &S, double4 (*f)[RMAX], const SynthChunk<NM> &b, int n) {
+    double4 q[NM];
+#pragma unroll
+    for (int k = 0; k < NM; ++k) q[k] = b.Q[k][0];
+    double3 tc = make_double3(b.T[0].x, b.T[0].y, b.T[0].z);
 #pragma unroll 1
     for (int t4 = 0; t4 < n; t4 += 4)
 #pragma unroll
     for (int t = t4; t < t4 + 4; ++t) {
-        const double4 qn = sQ[t + 1];
-        const double3 tn = make_double3(sT[t + 1].x, sT[t + 1].y, sT[t + 1].z);
+        double4 qn[NM];
+#pragma unroll
+        for (int k = 0; k < NM; ++k) qn[k] = b.Q[k][t + 1];
+        const double3 tn = make_double3(b.T[t + 1].x, b.T[t + 1].y, b.T[t + 1].z);
         __builtin_amdgcn_sched_barrier(0);
         double cpl[R], cmi[R];
 #pragma unroll
@@ -234,13 +145,15 @@ __device__ inline void synth_chunk(BandState<RMAX> &S, double *fpr, double *fpi,
             if (SPIN) cmi[r] = fma(tc.x, S.y[r], tc.z);
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double vm = SPIN ? S.um[r] : S.up[r];
-            fpr[r] = fma(q.x, S.up[r], fpr[r]);
-            fpi[r] = fma(q.y, S.up[r], fpi[r]);
-            fmr[r] = fma(q.z, vm, fmr[r]);
-            fmi[r] = fma(q.w, vm, fmi[r]);
-        }
+        for (int k = 0; k < NM; ++k)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double vm = SPIN ? S.um[r] : S.up[r];
+                f[k][r].x = fma(q[k].x, S.up[r], f[k][r].x);
+                f[k][r].y = fma(q[k].y, S.up[r], f[k][r].y);
+                f[k][r].z = fma(q[k].z, vm, f[k][r].z);
+                f[k][r].w = fma(q[k].w, vm, f[k][r].w);
+            }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -253,7 +166,8 @@ __device__ inline void synth_chunk(BandState<RMAX> &S, double *fpr, double *fpi,
                 S.um[r] = nm;
             }
         }
-        q = qn;
+#pragma unroll
+        for (int k = 0; k < NM; ++k) q[k] = qn[k];
         tc = tn;
     }
 }
@@ -261,8 +175,7 @@ __device__ inline void synth_chunk(BandState<RMAX> &S, double *fpr, double *fpi,
 // Synthesis: one wave per item, the degrees [la, lb) of order m for up to RMAX
 // bands.  Segment 0 of an order, and for each band the segment it starts in,
 // writes F; later segments write the partial copy of F of their segment
-// (segment k at parts + (k - 1) part_stride doubles), which k_synth_parts_sum
-// then adds into F.  RMAX = 4 reads each staged coefficient once for four
+// (k part_stride bytes after F), which k_synth_parts_sum then adds into F.  RMAX = 4 reads each staged coefficient once for four
 // bands: 18 cycles of the CU's LDS pipe per step (four 16-byte broadcasts at
 // 4.4 cycles) against 32 FMAs (39 cycles over the four SIMDs); with two bands
 // the two are level and neither overlaps fully.
@@ -270,27 +183,58 @@ struct SynthArgs {
     LegArgs a;
     const SynthItem *items;
     int nitems;
-    int syn_seg;  // degrees per segment (0: one segment)
-    double *parts;
-    int64_t part_stride;
+    int64_t part_stride;  // bytes from F to the copy of segment 1, and on to the next ones
 };
 
 // What a wave of the synthesis works on.
-struct SynthWave {
+template <int NM> struct SynthWave {
     const LegArgs &a;
     const LegBand *bands;  // of the item
     const double4 *T4;
-    double4 (*sbuf)[2][kStage + 1];
+    SynthChunk<NM> *buf;   // two chunks
     int64_t base;
-    int m, l0, la, lb, nb, lane;
+    int m, l0, la, lb, nb, lane, map0;
+};
+
+// Loads one chunk's entries from degree c (zero from the item's end on): lanes
+// 0..31 and 32..63 take an entry array each per round, the table first (round
+// 0, lower half), then the maps' combinations.
+template <int NM> struct SynthStage {
+    static constexpr int N = (NM + 2) / 2;
+    double4 v[N];
+    __device__ inline void load(const SynthWave<NM> &w, int c) {
+        const int l = c + (w.lane & 31), half = w.lane >> 5;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = 2 * i + half - 1;  // map; -1: the table
+            v[i] = make_double4(0.0, 0.0, 0.0, 0.0);
+            if (l < w.lb && k < NM && w.map0 + k < w.a.nmaps) {
+                const double4 T = w.T4[l];
+                if (k < 0) {
+                    v[i] = T;
+                } else {
+                    const double2 *g = reinterpret_cast<const double2 *>(w.a.alm_in + (w.map0 + k) * w.a.alm_stride);
+                    v[i] = synth_combo(g, g + w.a.nalm, T.w, w.base + l, w.m, w.a.mscale);
+                }
+            }
+        }
+    }
+    __device__ inline void store(SynthChunk<NM> &b, int lane) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = 2 * i + (lane >> 5) - 1;
+            if (k < 0) b.T[lane & 31] = v[i];
+            else if (k < NM) b.Q[k][lane & 31] = v[i];
+        }
+    }
 };
 
 // The chunks from c while R bands have entered, then those with one more (one
 // loop per R, so that the bands stay in their registers).  The next band is
 // loaded during the last chunk before it enters.
-template <int R, int RMAX, bool SPIN>
-__device__ __forceinline__ void synth_run(const SynthWave &w, BandState<RMAX> &S, double *fpr, double *fpi,
-                                          double *fmr, double *fmi, int c, int slot) {
+template <int R, int RMAX, int NM, bool SPIN>
+__device__ __forceinline__ void synth_run(const SynthWave<NM> &w, BandState<RMAX> &S, double4 (*f)[RMAX], int c,
+                                          int slot) {
     const bool more = R < RMAX && R < w.nb;
     const int cend = more ? min(band_enter(w.bands[R], w.la), w.lb) : w.lb;
     auto load = [&] {
@@ -302,26 +246,26 @@ __device__ __forceinline__ void synth_run(const SynthWave &w, BandState<RMAX> &S
     if constexpr (R > 0) {
 #pragma unroll 1
         for (; c < cend; c += kStage) {
-            double4 nv;
+            SynthStage<NM> next;
             const bool has_next = c + kStage < w.lb;
-            if (has_next) nv = stage_entry_synth(w.a, w.T4, w.base, w.m, c + kStage, w.lb, w.lane);
+            if (has_next) next.load(w, c + kStage);
             if constexpr (R < RMAX)
                 if (more && c + kStage >= cend) load();
-            synth_chunk<R, RMAX, SPIN>(S, fpr, fpi, fmr, fmi, w.sbuf[slot][0], w.sbuf[slot][1],
-                                       min(kStage, (w.lb - c + 3) & ~3));
-            if (has_next) w.sbuf[slot ^ 1][w.lane >> 5][w.lane & 31] = nv;
+            synth_chunk<R, RMAX, NM, SPIN>(S, f, w.buf[slot], min(kStage, (w.lb - c + 3) & ~3));
+            if (has_next) next.store(w.buf[slot ^ 1], w.lane);
             __syncthreads();
             slot ^= 1;
         }
     }
     if constexpr (R < RMAX) {
-        if (c < w.lb) synth_run<R + 1, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, c, slot);
+        if (c < w.lb) synth_run<R + 1, RMAX, NM, SPIN>(w, S, f, c, slot);
     }
 }
 
-template <int RMAX, bool SPIN>
+// Maps NM blockIdx.y .. + NM - 1 share the recurrence.
+template <int RMAX, int NM, bool SPIN>
 __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
-    __shared__ double4 sbuf[2][2][kStage + 1];  // one spare entry: the pipelined loop reads one step ahead
+    __shared__ SynthChunk<NM> buf[2];
     const LegArgs &a = A.a;
     if ((int)blockIdx.x >= A.nitems) return;
     const SynthItem it = A.items[blockIdx.x];
@@ -329,33 +273,43 @@ __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
     const int m = it.m, s = a.spin, lane = threadIdx.x;
     const LegBand *bands = a.bands + it.b0;
     const int64_t base = (int64_t)m * (2 * a.lmax + 1 - m) / 2;
-    const double4 *T4 = a.coef + base;
-    const SynthWave w{a, bands, T4, sbuf, base, m, m > s ? m : s, it.la, it.lb, it.nb, lane};
+    const SynthWave<NM> w{a, bands, a.coef + base, buf, base, m, m > s ? m : s, it.la, it.lb, it.nb, lane,
+                          (int)blockIdx.y * NM};
 
     BandState<RMAX> S;
-    double fpr[RMAX], fpi[RMAX], fmr[RMAX], fmi[RMAX];
+    double4 f[NM][RMAX];  // sums of the +m and -m coefficients {Re, Im, Re, Im}
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         S.y[r] = S.up[r] = S.upp[r] = S.um[r] = S.ump[r] = 0.0;
-        fpr[r] = fpi[r] = fmr[r] = fmi[r] = 0.0;
+#pragma unroll
+        for (int k = 0; k < NM; ++k) f[k][r] = make_double4(0.0, 0.0, 0.0, 0.0);
     }
     const int c = band_enter(bands[0], it.la);
-    sbuf[0][lane >> 5][lane & 31] = stage_entry_synth(a, T4, base, m, c, it.lb, lane);
+    {
+        SynthStage<NM> first;
+        first.load(w, c);
+        first.store(buf[0], lane);
+    }
     __syncthreads();
-    synth_run<0, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, c, 0);
+    synth_run<0, RMAX, NM, SPIN>(w, S, f, c, 0);
 
     const double sgn_neg = (s & 1) ? 1.0 : -1.0;  // -(-1)^s
     const int64_t op = (int64_t)(a.mmax + m) * a.nring, om = (int64_t)(a.mmax - m) * a.nring;
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-        if (r >= it.nb) break;
-        const LegBand b = bands[r];
-        const int j = band_ring(b, lane);
-        const bool first = b.bs >= it.la;  // the band starts in this segment
-        double2 *F = reinterpret_cast<double2 *>(first ? a.F : A.parts + (int64_t)(it.part - 1) * A.part_stride);
-        if (j >= 0) {
-            F[op + j] = make_double2(-fpr[r], -fpi[r]);
-            if (m != 0) F[om + j] = make_double2(sgn_neg * fmr[r], sgn_neg * fmi[r]);
+    for (int k = 0; k < NM; ++k) {
+        if (w.map0 + k >= a.nmaps) break;
+#pragma unroll
+        for (int r = 0; r < RMAX; ++r) {
+            if (r >= it.nb) break;
+            const LegBand b = bands[r];
+            const int j = band_ring(b, lane);
+            const bool first = b.bs >= it.la;  // the band starts in this segment
+            double2 *F = reinterpret_cast<double2 *>(a.F + (w.map0 + k) * a.F_stride +
+                                                     (first ? 0 : (int64_t)it.part * A.part_stride));
+            if (j >= 0) {
+                F[op + j] = make_double2(-f[k][r].x, -f[k][r].y);
+                if (m != 0) F[om + j] = make_double2(sgn_neg * f[k][r].z, sgn_neg * f[k][r].w);
+            }
         }
     }
 }
@@ -364,7 +318,7 @@ __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
 // in, for every written entry (|m| <= ring_mmax[j] and order |m| has degrees);
 // order |m| has ceil((lmax + 1 - max(|m|, s)) / S) segments.  One thread per
 // entry of F, rings contiguous.
-__global__ __launch_bounds__(256) void k_synth_parts_sum(double2 *F, const double2 *parts, int64_t part_stride,
+__global__ __launch_bounds__(256) void k_synth_parts_sum(char *F0, int64_t F_stride, int64_t part_stride,
                                                          const LegOrder *orders, const int32_t *band_bs,
                                                          const int32_t *ring_mmax, int nring, int mmax, int lmax,
                                                          int spin, int S) {
@@ -379,9 +333,11 @@ __global__ __launch_bounds__(256) void k_synth_parts_sum(double2 *F, const doubl
     const int k0 = (band_bs[o.band0 + ((o.last - j) >> 6)] - l0) / S;
     const int nseg = (lmax + 1 - l0 + S - 1) / S;
     if (nseg < k0 + 2) return;
+    char *Fc = F0 + blockIdx.y * F_stride;
+    double2 *F = reinterpret_cast<double2 *>(Fc);
     double2 acc = F[e];
     for (int k = k0 + 1; k < nseg; ++k) {
-        const double2 v = parts[(int64_t)(k - 1) * part_stride + e];
+        const double2 v = reinterpret_cast<const double2 *>(Fc + k * part_stride)[e];
         acc.x += v.x;
         acc.y += v.y;
     }
@@ -527,8 +483,8 @@ __device__ inline void lds_barrier(bool alone) {
 }
 
 // Zero outputs of order m for l in [l_from, l_to), by thread i of n.
-__device__ inline void adj_zero_range(const LegArgs &a, int64_t base, int l_from, int l_to, int i, int n) {
-    double2 *out = reinterpret_cast<double2 *>(a.alm_out);
+__device__ inline void adj_zero_range(const LegArgs &a, double *dst, int64_t base, int l_from, int l_to, int i, int n) {
+    double2 *out = reinterpret_cast<double2 *>(dst);
     for (int l = l_from + i; l < l_to; l += n) {
         out[base + l] = make_double2(0.0, 0.0);
         out[a.nalm + base + l] = make_double2(0.0, 0.0);
@@ -541,6 +497,7 @@ struct AdjWave {
     const LegBand *bands;  // of the item
     const double4 *T4;
     const double2 *Fp, *Fm;
+    double *out;  // complex [2][nalm]
     double2 *red1, *red2, *red2all;
     int64_t base;
     int m, l0, la, lb, nb, G, wave, lane;
@@ -585,7 +542,7 @@ __device__ __forceinline__ void adj_write(const AdjWave &w, int c, int n, double
     const double sgn_s = (w.a.spin & 1) ? -1.0 : 1.0;
     const double hP = (w.m == 0 ? 0.5 : 0.5 * w.a.mscale) * P;
     double2 val;
-    double *dst = w.a.alm_out + 2 * (w.base + c + t);
+    double *dst = w.out + 2 * (w.base + c + t);
     // Im g~_l0 and Im c~_l0 vanish (reality condition)
     if ((w.lane & 1) == 0) {  // g~ = -hP (A + (-1)^s B)
         val.x = -hP * (sr + sgn_s * orr);
@@ -656,14 +613,15 @@ __device__ inline void adj_item(const AdjArgs &A) {
     const LegBand *bands = a.bands + it.b0;
     const int la = max(it.la, l0);
     const int c0 = it.nb > 0 ? band_enter(bands[0], la) : it.lb;
+    double *out = reinterpret_cast<double *>(a.alm_out + blockIdx.y * a.alm_stride);
     // no ring has started (or l < s)
-    if (!A.accumulate) adj_zero_range(a, base, it.la, min(c0, it.lb), 64 * wave + lane, 64 * G);
+    if (!A.accumulate) adj_zero_range(a, out, base, it.la, min(c0, it.lb), 64 * wave + lane, 64 * G);
     if (it.nb <= 0) return;
     double2 *red2 = redbase + wg * kRed1 + w0 * kRed2;
-    const double2 *F = reinterpret_cast<const double2 *>(a.F);
+    const double2 *F = reinterpret_cast<const double2 *>(a.F + blockIdx.y * a.F_stride);
     const double4 *T4 = a.coef + base;
     const AdjWave w{a,    bands, T4, F + (int64_t)(a.mmax + m) * a.nring, F + (int64_t)(a.mmax - m) * a.nring,
-                    redbase + w0 * kRed1, red2, red2 - wave * kRed2, base, m, l0, la, it.lb, it.nb, G, wave, lane,
+                    out,  redbase + w0 * kRed1, red2, red2 - wave * kRed2, base, m, l0, la, it.lb, it.nb, G, wave, lane,
                     A.accumulate};
     BandState<RMAX> S;
     double fpr[RMAX], fpi[RMAX], fmr[RMAX], fmi[RMAX];
@@ -793,166 +751,9 @@ __global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double
     if (bad) atomicAdd(lost, 1);
 }
 
-// ------------------------------------------------------- batched maps (MFMA)
-//
-// nb <= 8 coefficient sets on one plan.  For one order m and a chunk of 64
-// rings, the sums over l are the dense contraction
-//   F_b(+m)[j] = -sum_l lambda+_l(theta_j) Z+_b[l],  Z+_b = P (g_b + i c_b),
-//   F_b(-m)[j] = -(-1)^s sum_l lambda-_l(theta_j) Z-_b[l],
-// i.e. (64 rings x L) times (L x 16 real columns: 8 maps x {Re, Im}) for each
-// sign.  The recurrence runs once for all maps (one ring per lane); blocks of
-// 4 consecutive l go through LDS to the A operand of v_mfma_f64_16x16x4f64
-// (A[i][k] in lane i + 16 k: ring 16 q + i, l + k), the staged columns are the
-// B operand (B[k][j] in lane j + 16 k) and D accumulates in registers (D[i][j]
-// in lane j + 16 (i mod 4), register i / 4).
-
-typedef double d4v __attribute__((ext_vector_type(4)));
-
-struct LegBatchArgs {
-    LegArgs a;           // work list of 64-ring chunks, tables, rings
-    const char *alm0;    // coefficients (g, c) of map 0, complex [2][nalm]; map b at alm0 + b * alm_stride
-    int64_t alm_stride;  // bytes
-    char *F0;            // F of map 0; map b at F0 + b * stride
-    int64_t stride;      // bytes between consecutive maps' F (their workspaces)
-    int nb;              // maps in this launch, 1..8
-};
-
-// Register budget of two waves per SIMD: the accumulators then stay in VGPRs
-// (a three-wave budget split them into AGPRs and copied them around every
-// block); the compiler needs 162 VGPRs, the LDS (14 KB) allows 11 waves per CU.
-template <bool SPIN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_leg_synth_mm(LegBatchArgs bt) {
-    const LegArgs &a = bt.a;
-    __shared__ double4 sT[2][kStage];
-    // one buffer of coefficient columns: the next chunk waits in registers
-    // (nz) until the current one is done, which keeps the LDS at 18 KB
-    __shared__ double sZ[kStage][2][16];  // [l][sign][column]
-    __shared__ double sL[2][4][64];          // [sign][k][ring]
-    const int idx = leg_item_index(blockIdx.x, a.group);
-    if (idx >= a.nitems) return;
-    const LegItem it = a.items[idx];
-    if (it.je <= it.jb) return;
-    const int m = it.m, s = a.spin, lane = threadIdx.x;
-    const int l0 = m > s ? m : s, lmax = a.lmax;
-    if (l0 > lmax) return;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const double4 *T4 = a.coef + base;
-
-    // Staging of a chunk of kStage steps from l = c: lanes 0..31 load the
-    // recurrence table, every lane forms 4 (l, map) entries of the columns
-    // (l = c + e / 8, map = e % 8) from the coefficients, zero past lmax and
-    // past nb.  The loads of
-    // the next chunk are issued before the current chunk is computed and
-    // written to the other LDS slot after it.
-    auto load_z = [&](int c, int e) {
-        const int lo = e >> 3, b = e & 7, l = c + lo;
-        double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
-        if (b < bt.nb && l <= lmax) {
-            const double2 *gb = reinterpret_cast<const double2 *>(bt.alm0 + (int64_t)b * bt.alm_stride);
-            v = synth_combo(gb, gb + a.nalm, a.coef, base + l, m, a.mscale);
-        }
-        return v;
-    };
-    auto store_z = [&](int e, double4 v) {
-        const int lo = e >> 3, b = e & 7;
-        sZ[lo][0][2 * b] = v.x;
-        sZ[lo][0][2 * b + 1] = v.y;
-        sZ[lo][1][2 * b] = v.z;
-        sZ[lo][1][2 * b + 1] = v.w;
-    };
-    if (lane < 32) sT[0][lane] = stage_entry(T4, l0, lmax, lane);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) store_z(lane + 64 * i, load_z(l0, lane + 64 * i));
-
-    LegState<1, SPIN> S;
-    leg_init<1, SPIN>(a, it, lane, S);
-    bool scaled = leg_any_scaled<1, SPIN>(S);
-    d4v Dp[4], Dm[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) Dp[q] = Dm[q] = d4v{0.0, 0.0, 0.0, 0.0};
-    const int kk = lane >> 4, jj = lane & 15;
-    __syncthreads();
-
-    int slot = 0;
-    for (int c = l0; c <= lmax; c += kStage) {
-        const bool has_next = c + kStage <= lmax;
-        double4 nt, nz[4];
-        if (has_next) {
-            if (lane < 32) nt = stage_entry(T4, c + kStage, lmax, lane);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) nz[i] = load_z(c + kStage, lane + 64 * i);
-        }
-        const int n = min(kStage, lmax + 1 - c);
-        for (int b4 = 0; b4 < n; b4 += 4) {
-            double cp = 1.0, cm = 1.0;
-            if (scaled) {
-                cp = S.kp[0] == 0 ? 1.0 : 0.0;
-                cm = (SPIN ? S.km[0] : S.kp[0]) == 0 ? 1.0 : 0.0;
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int t = b4 + k;
-                double vp = 0.0, vm = 0.0;
-                if (t < n) {
-                    vp = S.up[0] * cp;
-                    vm = (SPIN ? S.um[0] : S.up[0]) * cm;
-                    if (c + t < lmax) leg_advance<1, SPIN>(S, sT[slot][t]);
-                }
-                sL[0][k][lane] = vp;
-                sL[1][k][lane] = vm;
-            }
-            if (scaled) {
-                leg_renorm<1, SPIN>(S);
-                scaled = leg_any_scaled<1, SPIN>(S);
-            }
-            // One wave per workgroup, whose LDS operations run in program order:
-            // the barrier only keeps the compiler from moving this block's
-            // writes past its reads (and the next block's writes past them).
-            __syncthreads();
-            // columns of l = c + b4 + kk (zero past lmax)
-            const double bp = sZ[b4 + kk][0][jj], bm = sZ[b4 + kk][1][jj];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                Dp[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(sL[0][kk][16 * q + jj], bp, Dp[q], 0, 0, 0);
-                Dm[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(sL[1][kk][16 * q + jj], bm, Dm[q], 0, 0, 0);
-            }
-            __syncthreads();
-        }
-        if (has_next) {
-            if (lane < 32) sT[slot ^ 1][lane] = nt;
-            __syncthreads();  // the last block's column reads come first
-#pragma unroll
-            for (int i = 0; i < 4; ++i) store_z(lane + 64 * i, nz[i]);
-        }
-        __syncthreads();
-        slot ^= 1;
-    }
-
-    // D[i][j] of block q: ring jb + 16 q + i, column j = 2 map + {Re, Im}
-    const double sgn_neg = (s & 1) ? 1.0 : -1.0;  // -(-1)^s
-    const int b = jj >> 1, comp = jj & 1;
-    if (b >= bt.nb) return;
-    double *F = reinterpret_cast<double *>(bt.F0 + (int64_t)b * bt.stride);
-    const int64_t op = 2 * ((int64_t)(a.mmax + m) * a.nring) + comp;
-    const int64_t om = 2 * ((int64_t)(a.mmax - m) * a.nring) + comp;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = it.jb + 16 * q + kk + 4 * r;
-            if (j >= it.je || a.ring_mmax[j] < m) continue;
-            F[op + 2 * j] = -Dp[q][r];
-            if (m != 0) F[om + 2 * j] = sgn_neg * Dm[q][r];
-        }
-    }
-}
-
-static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, const void *alm_out, double *F) {
+static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, void *alm_out, void *F, const MapBatch &mb) {
     const Geometry &g = p.g;
     LegArgs a;
-    a.items = p.d_leg_items64;
-    a.nitems = p.n_leg_items64;
-    a.group = (g.nring + 63) / 64;
     a.bands = p.d_bands;
     a.st_p = reinterpret_cast<const double2 *>(p.d_st_p);
     a.st_m = reinterpret_cast<const double2 *>(p.d_st_m);
@@ -963,16 +764,17 @@ static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, const void *al
     a.ring_y = p.d_ring_y;
     a.ring_ch = p.d_ring_ch;
     a.ring_sh = p.d_ring_sh;
-    a.ring_mmax = p.d_ring_mmax;
     a.nring = g.nring;
     a.lmax = g.lmax;
     a.spin = g.spin;
     a.mmax = g.mmax;
     a.nalm = (int64_t)(g.lmax + 1) * (g.lmax + 2) / 2;
-    a.g = static_cast<const double2 *>(alm_in);
-    a.c = a.g ? a.g + a.nalm : nullptr;
-    a.alm_out = static_cast<double *>(const_cast<void *>(alm_out));
-    a.F = F;
+    a.alm_in = static_cast<const char *>(alm_in);
+    a.alm_out = static_cast<char *>(alm_out);
+    a.F = static_cast<char *>(F);
+    a.alm_stride = 2 * 16 * a.nalm;
+    a.F_stride = mb.ws_stride;
+    a.nmaps = mb.n;
     a.mscale = 1.0;
     return a;
 }
@@ -988,11 +790,42 @@ int leg_bands_per_wave() {
     return r;
 }
 
+template <int R, int NM>
+static void leg_synth_run(const SynthArgs &A, int spin, hipStream_t st) {
+    const dim3 grid(A.nitems, (A.a.nmaps + NM - 1) / NM), block(64);
+    if (spin) {
+        hipLaunchKernelGGL((k_leg_synth<R, NM, true>), grid, block, 0, st, A);
+    } else {
+        if constexpr (NM <= 2) hipLaunchKernelGGL((k_leg_synth<R, NM, false>), grid, block, 0, st, A);
+    }
+}
+
+// NM maps per wave share the recurrence (4 of the 8 FMAs per ring, degree and
+// map with a spin; 2 of 6 without): 6 FMAs per map with two maps, 5 with four.
+// Four fit the registers beside two bands (210 VGPRs) and pay with a spin only
+// (lmax 2048, 8 maps, us per map: spin 2 on a 34-degree cap 128 against 145 with
+// two; spin 0 on 20 degrees 58 against 60, on fewer maps slower); with four
+// bands they leave one wave per SIMD (lmax 4096: 915 against 822 with two).
 template <int R>
-static void leg_synth_r(const SynthArgs &A, int spin, hipStream_t st) {
-    const dim3 grid(A.nitems), block(64);
-    if (spin) hipLaunchKernelGGL((k_leg_synth<R, true>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((k_leg_synth<R, false>), grid, block, 0, st, A);
+static hipError_t leg_synth_maps(SynthArgs A, int spin, hipStream_t st) {
+    LegArgs &a = A.a;
+    const int total = a.nmaps;
+    for (int done = 0; done < total; done += a.nmaps) {
+        const int left = total - done;
+        if constexpr (R <= 2) {
+            if (spin && left >= 3) {  // whole groups of four; three left over fill a group but for one
+                a.nmaps = left % 4 == 3 ? left : left / 4 * 4;
+                leg_synth_run<R, 4>(A, spin, st);
+                a.alm_in += a.nmaps * a.alm_stride;
+                a.F += a.nmaps * a.F_stride;
+                continue;
+            }
+        }
+        a.nmaps = left;
+        if (left >= 2) leg_synth_run<R, 2>(A, spin, st);
+        else leg_synth_run<R, 1>(A, spin, st);
+    }
+    return hipGetLastError();
 }
 
 static hipError_t leg_synth_list(const psht_plan_s &p, SynthArgs &A, const SynthItem *items, int nitems, int R,
@@ -1000,61 +833,34 @@ static hipError_t leg_synth_list(const psht_plan_s &p, SynthArgs &A, const Synth
     if (nitems == 0) return hipSuccess;
     A.items = items;
     A.nitems = nitems;
-    if (R == 4) leg_synth_r<4>(A, p.g.spin, st);
-    else if (R == 2) leg_synth_r<2>(A, p.g.spin, st);
-    else leg_synth_r<1>(A, p.g.spin, st);
-    return hipGetLastError();
+    if (R == 4) return leg_synth_maps<4>(A, p.g.spin, st);
+    if (R == 2) return leg_synth_maps<2>(A, p.g.spin, st);
+    return leg_synth_maps<1>(A, p.g.spin, st);
 }
 
-hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, double *F, double mscale, hipStream_t st) {
+hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, void *F, bool segments, const MapBatch &mb,
+                            double mscale, hipStream_t st) {
     SynthArgs A;
-    A.a = leg_args(p, alm, nullptr, F);
+    A.a = leg_args(p, alm, nullptr, F, mb);
     A.a.mscale = mscale;
-    A.syn_seg = 0;
-    A.parts = nullptr;
-    A.part_stride = 0;
-    return leg_synth_list(p, A, p.d_leg_items, p.n_leg_items, p.leg_r, st);
-}
-
-hipError_t launch_leg_synth_parts(const psht_plan_s &p, const void *alm, double *F, double *parts,
-                                  int64_t part_stride, double mscale, hipStream_t st) {
-    if (p.syn_seg == 0) return launch_leg_synth(p, alm, F, mscale, st);
-    SynthArgs A;
-    A.a = leg_args(p, alm, nullptr, F);
-    A.a.mscale = mscale;
-    A.syn_seg = p.syn_seg;
-    A.parts = parts;
-    A.part_stride = part_stride;
-    hipError_t e = leg_synth_list(p, A, p.d_syn_items, p.n_syn_items, p.syn_r, st);
+    A.part_stride = (int64_t)p.ws_F;
+    const bool multi = mb.n >= 3;
+    const int seg = !segments ? 0 : multi && p.syn_seg > 0 ? p.multi_seg : p.syn_seg;
+    if (seg == 0) return leg_synth_list(p, A, p.d_leg_items, p.n_leg_items, p.leg_r, st);
+    const hipError_t e = multi ? leg_synth_list(p, A, p.d_multi_items, p.n_multi_items, p.multi_r, st)
+                               : leg_synth_list(p, A, p.d_syn_items, p.n_syn_items, p.syn_r, st);
     if (e != hipSuccess || p.syn_parts == 0) return e;
     const int64_t n = (int64_t)(2 * p.g.mmax + 1) * p.g.nring;
-    hipLaunchKernelGGL(k_synth_parts_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<double2 *>(F), reinterpret_cast<const double2 *>(parts), part_stride / 2,
-                       p.d_orders, p.d_band_bs, p.d_ring_mmax, p.g.nring, p.g.mmax, p.g.lmax, p.g.spin, p.syn_seg);
-    return hipGetLastError();
-}
-
-hipError_t launch_leg_synth_batch(const psht_plan_s &p, int nb, const void *alm0, int64_t alm_stride, char *F0,
-                                  int64_t ws_stride, double mscale, hipStream_t st) {
-    if (nb < 1 || nb > kMaxLegBatch) return hipErrorInvalidValue;
-    if (p.n_leg_items64 == 0) return hipSuccess;
-    LegBatchArgs bt;
-    bt.a = leg_args(p, nullptr, nullptr, nullptr);
-    bt.a.mscale = mscale;
-    bt.alm0 = static_cast<const char *>(alm0);
-    bt.alm_stride = alm_stride;
-    bt.F0 = F0;
-    bt.stride = ws_stride;
-    bt.nb = nb;
-    if (p.g.spin) hipLaunchKernelGGL((k_leg_synth_mm<true>), dim3(p.n_leg_items64), dim3(64), 0, st, bt);
-    else hipLaunchKernelGGL((k_leg_synth_mm<false>), dim3(p.n_leg_items64), dim3(64), 0, st, bt);
+    hipLaunchKernelGGL(k_synth_parts_sum, dim3((unsigned)((n + 255) / 256), mb.n), dim3(256), 0, st,
+                       static_cast<char *>(F), mb.ws_stride, (int64_t)p.ws_F, p.d_orders, p.d_band_bs, p.d_ring_mmax,
+                       p.g.nring, p.g.mmax, p.g.lmax, p.g.spin, seg);
     return hipGetLastError();
 }
 
 hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
                              hipStream_t st) {
     if (nbands == 0) return hipSuccess;
-    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr);
+    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr, MapBatch());
     if (p.g.spin) hipLaunchKernelGGL(k_leg_starts<true>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
     else hipLaunchKernelGGL(k_leg_starts<false>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
     return hipGetLastError();
@@ -1062,7 +868,7 @@ hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nba
 
 hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st) {
     if (nbands == 0) return hipSuccess;
-    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr);
+    const LegArgs a = leg_args(p, nullptr, nullptr, nullptr, MapBatch());
     double2 *sp = reinterpret_cast<double2 *>(p.d_st_p), *sm = reinterpret_cast<double2 *>(p.d_st_m);
     if (p.g.spin)
         hipLaunchKernelGGL(k_leg_states<true>, dim3(nbands), dim3(64), 0, st, a, nbands, sp, sm, lost);
@@ -1077,19 +883,20 @@ static hipError_t leg_adjoint_run(K kern, const psht_plan_s &p, const AdjArgs &A
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(p.n_adj_items / p.adj_waves), dim3(64 * p.adj_waves), lds, st, A);
+    hipLaunchKernelGGL(kern, dim3(p.n_adj_items / p.adj_waves, A.a.nmaps), dim3(64 * p.adj_waves), lds, st, A);
     return hipGetLastError();
 }
 
-hipError_t launch_leg_adjoint(const psht_plan_s &p, const double *F, void *alm, double mscale, hipStream_t st) {
+hipError_t launch_leg_adjoint(const psht_plan_s &p, const void *F, void *alm, const MapBatch &mb, double mscale,
+                              hipStream_t st) {
     const int64_t nalm = (int64_t)(p.g.lmax + 1) * (p.g.lmax + 2) / 2;
     if (p.adj_accumulate) {
-        const hipError_t e = launch_fill_zero(alm, (size_t)nalm * 2 * 16, st);
+        const hipError_t e = launch_fill_zero(alm, (size_t)nalm * 2 * 16 * mb.n, st);
         if (e != hipSuccess) return e;
     }
     if (p.n_adj_items == 0) return hipSuccess;
     AdjArgs A;
-    A.a = leg_args(p, nullptr, alm, const_cast<double *>(F));
+    A.a = leg_args(p, nullptr, alm, const_cast<void *>(F), mb);
     A.a.mscale = mscale;
     A.items = p.d_adj_items;
     A.nitems = p.n_adj_items;

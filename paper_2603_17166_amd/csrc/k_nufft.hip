@@ -42,7 +42,13 @@ struct NufftArgs {
     // the sort; counted, not silently skipped)
     unsigned long long *dropped;
     int xcd_group;  // tiles per XCD group (xcd_tile)
+    int64_t npts, ws_stride;  // points of a map; bytes between the grids U of the maps (blockIdx.y)
 };
+
+// The grid U of the batch's first map moved to this block's map.
+template <typename T> __device__ inline T *map_grid(T *U, const NufftArgs &a) {
+    return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(U) + blockIdx.y * a.ws_stride);
+}
 
 // Row stride (in elements) of a tile's subgrid in LDS: odd, so that the
 // stencil origins (li, lj) of the slots a wave handles in one instruction
@@ -232,6 +238,8 @@ __global__ __launch_bounds__(kTileThreads) void k_interp(NufftArgs a, const type
     typedef typename CplxT<T>::type C;
     extern __shared__ __align__(16) unsigned char smem[];
     C *S = reinterpret_cast<C *>(smem);
+    U = map_grid(U, a);
+    map += blockIdx.y * a.npts;
     const UniformPtr<T> sC = uniform_ptr(table<T>(a));
     const int t = xcd_tile(blockIdx.x, a.ntx * a.nty, a.xcd_group);
     if (t < 0) return;
@@ -300,6 +308,8 @@ __global__ __launch_bounds__(kTileThreads) void k_spread(NufftArgs a, const type
                                                          T *U) {
     typedef typename CplxT<T>::type C;
     extern __shared__ __align__(16) unsigned char smem[];
+    U = map_grid(U, a);
+    map += blockIdx.y * a.npts;
     const int t = xcd_tile(blockIdx.x, a.ntx * a.nty, a.xcd_group);
     if (t < 0) return;
     const int p0 = a.tile_start[t], p1 = a.tile_start[t + 1];
@@ -368,7 +378,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spread(NufftArgs a, const type
     }
 }
 
-static NufftArgs nufft_args(const psht_plan_s &p) {
+static NufftArgs nufft_args(const psht_plan_s &p, const MapBatch &mb) {
     NufftArgs a;
     a.W = p.g.W;
     a.beta = p.g.beta;
@@ -388,33 +398,35 @@ static NufftArgs nufft_args(const psht_plan_s &p) {
     a.geo = tile_geom(p);
     a.dropped = p.d_dropped;
     a.xcd_group = xcd_group(p.ntiles);
+    a.npts = p.npts;
+    a.ws_stride = mb.ws_stride;
     return a;
 }
 
 template <typename T, int W>
-static hipError_t launch_interp_w(const psht_plan_s &p, const void *U, void *map, hipStream_t st) {
+static hipError_t launch_interp_w(const psht_plan_s &p, const void *U, void *map, const MapBatch &mb, hipStream_t st) {
     typedef typename CplxT<T>::type C;
-    NufftArgs a = nufft_args(p);
+    NufftArgs a = nufft_args(p, mb);
     size_t lds = (size_t)(p.tile_x + W - 1) * tile_row_stride(p.tile_y, W) * sizeof(C);
-    hipLaunchKernelGGL((k_interp<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group)), dim3(kTileThreads), lds, st, a,
+    hipLaunchKernelGGL((k_interp<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds, st, a,
                        static_cast<const C *>(U), static_cast<C *>(map));
     return hipGetLastError();
 }
 
 template <typename T, int W>
-static hipError_t launch_spread_w(const psht_plan_s &p, const void *map, void *U, hipStream_t st) {
+static hipError_t launch_spread_w(const psht_plan_s &p, const void *map, void *U, const MapBatch &mb, hipStream_t st) {
     typedef typename CplxT<T>::type C;
-    NufftArgs a = nufft_args(p);
+    NufftArgs a = nufft_args(p, mb);
     size_t lds = (size_t)(p.tile_x + W - 1) * tile_row_stride(p.tile_y, W) * 2 * sizeof(double);
-    hipLaunchKernelGGL((k_spread<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group)), dim3(kTileThreads), lds, st, a,
+    hipLaunchKernelGGL((k_spread<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds, st, a,
                        static_cast<const C *>(map), static_cast<T *>(U));
     return hipGetLastError();
 }
 
 template <typename T>
-static hipError_t dispatch_interp(const psht_plan_s &p, const void *U, void *map, hipStream_t st) {
+static hipError_t dispatch_interp(const psht_plan_s &p, const void *U, void *map, const MapBatch &mb, hipStream_t st) {
     switch (p.g.W) {
-#define PSHT_W(w) case w: return launch_interp_w<T, w>(p, U, map, st);
+#define PSHT_W(w) case w: return launch_interp_w<T, w>(p, U, map, mb, st);
         PSHT_W(2) PSHT_W(3) PSHT_W(4) PSHT_W(5) PSHT_W(6) PSHT_W(7) PSHT_W(8) PSHT_W(9)
         PSHT_W(10) PSHT_W(11) PSHT_W(12) PSHT_W(13) PSHT_W(14) PSHT_W(15) PSHT_W(16)
 #undef PSHT_W
@@ -423,9 +435,9 @@ static hipError_t dispatch_interp(const psht_plan_s &p, const void *U, void *map
 }
 
 template <typename T>
-static hipError_t dispatch_spread(const psht_plan_s &p, const void *map, void *U, hipStream_t st) {
+static hipError_t dispatch_spread(const psht_plan_s &p, const void *map, void *U, const MapBatch &mb, hipStream_t st) {
     switch (p.g.W) {
-#define PSHT_W(w) case w: return launch_spread_w<T, w>(p, map, U, st);
+#define PSHT_W(w) case w: return launch_spread_w<T, w>(p, map, U, mb, st);
         PSHT_W(2) PSHT_W(3) PSHT_W(4) PSHT_W(5) PSHT_W(6) PSHT_W(7) PSHT_W(8) PSHT_W(9)
         PSHT_W(10) PSHT_W(11) PSHT_W(12) PSHT_W(13) PSHT_W(14) PSHT_W(15) PSHT_W(16)
 #undef PSHT_W
@@ -433,14 +445,14 @@ static hipError_t dispatch_spread(const psht_plan_s &p, const void *map, void *U
     }
 }
 
-hipError_t launch_interp(const psht_plan_s &p, const void *U, void *map, hipStream_t st) {
+hipError_t launch_interp(const psht_plan_s &p, const void *U, void *map, const MapBatch &mb, hipStream_t st) {
     if (p.npts == 0 || p.ntiles == 0) return hipSuccess;
-    return p.g.fp32 ? dispatch_interp<float>(p, U, map, st) : dispatch_interp<double>(p, U, map, st);
+    return p.g.fp32 ? dispatch_interp<float>(p, U, map, mb, st) : dispatch_interp<double>(p, U, map, mb, st);
 }
 
-hipError_t launch_spread(const psht_plan_s &p, const void *map, void *U, hipStream_t st) {
+hipError_t launch_spread(const psht_plan_s &p, const void *map, void *U, const MapBatch &mb, hipStream_t st) {
     if (p.npts == 0 || p.ntiles == 0) return hipSuccess;
-    return p.g.fp32 ? dispatch_spread<float>(p, map, U, st) : dispatch_spread<double>(p, map, U, st);
+    return p.g.fp32 ? dispatch_spread<float>(p, map, U, mb, st) : dispatch_spread<double>(p, map, U, mb, st);
 }
 
 // --------------------------------------------------------------- fill
@@ -467,6 +479,20 @@ hipError_t launch_fill_zero(void *ptr, size_t bytes, hipStream_t st) {
     if (rem)
         hipLaunchKernelGGL(k_fill_zero_bytes, dim3(1), dim3(256), 0, st, static_cast<unsigned char *>(ptr) + n16 * 16,
                            rem);
+    return hipGetLastError();
+}
+
+__global__ void k_grid_zero(uint4 *p, size_t n16, int64_t ws_stride) {
+    uint4 *q = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(p) + blockIdx.y * ws_stride);
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride) q[i] = make_uint4(0, 0, 0, 0);
+}
+
+hipError_t launch_grid_zero(const psht_plan_s &p, void *U, const MapBatch &mb, hipStream_t st) {
+    const size_t n16 = p.ws_U / 16;  // ws_U is a multiple of 256
+    if (n16 == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_grid_zero, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 8192), mb.n), dim3(256), 0, st,
+                       static_cast<uint4 *>(U), n16, mb.ws_stride);
     return hipGetLastError();
 }
 

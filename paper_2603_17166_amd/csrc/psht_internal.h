@@ -100,10 +100,6 @@ struct LegTable {
 void leg_table_host(LegTable &t, int lmax, int spin);
 std::shared_ptr<LegTable> leg_table_get(int lmax, int spin, Error &err);
 
-struct LegItem {
-    int32_t m, jb, je;  // rings [jb, je) for this m
-};
-
 // Bands of the Legendre stages (see k_legendre.hip): the rings [jb, jb + 64) of
 // an order, one per lane, counted from the order's last ring downwards, so that
 // the partial band is the innermost one.  The band starts at degree bs; its
@@ -170,8 +166,9 @@ struct psht_plan_s {
     int n_syn_items = 0, syn_r = 2;
     int syn_seg = 0;    // 0: not segmented
     int syn_parts = 0;  // partial copies of F (segments beyond the first of the longest order)
-    psht::LegItem *d_leg_items64 = nullptr;  // 64-ring chunks (batched-maps kernel)
-    int n_leg_items64 = 0;
+    // the list of calls with three or more maps (multi_seg = 0: the plain one)
+    psht::SynthItem *d_multi_items = nullptr;
+    int n_multi_items = 0, multi_r = 2, multi_seg = 0;
     std::shared_ptr<psht::LegTable> leg;
     // NUFFT tables
     double *d_psihat_t = nullptr, *d_psihat_p = nullptr;
@@ -200,17 +197,25 @@ struct psht_plan_s {
 
 namespace psht {
 
-// Stage launchers (defined in the .hip files).  All asynchronous on `st`.
-// `mscale` multiplies the coefficients (synthesis) or the outputs (adjoint) of
-// every order m >= 1; 1 for the plain transforms.
-hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, double *F, double mscale, hipStream_t st);
-// The same through the degree-segmented work list when the plan has one
-// (syn_seg > 0), with the partial copies of F at `parts` (syn_parts copies of
-// 2 mmax + 1 by nring complex values, `part_stride` doubles apart); otherwise
-// launch_leg_synth.
-hipError_t launch_leg_synth_parts(const psht_plan_s &p, const void *alm, double *F, double *parts,
-                                  int64_t part_stride, double mscale, hipStream_t st);
-hipError_t launch_leg_adjoint(const psht_plan_s &p, const double *F, void *alm, double mscale, hipStream_t st);
+// Maps that share a launch (the second grid dimension): n maps, whose
+// workspaces (F, V and U) lie ws_stride bytes apart; maps and coefficients are
+// contiguous.
+struct MapBatch {
+    int n = 1;
+    int64_t ws_stride = 0;
+};
+
+// Stage launchers (defined in the .hip files).  All asynchronous on `st`; the
+// pointers are those of the batch's first map.  `mscale` multiplies the
+// coefficients (synthesis) or the outputs (adjoint) of every order m >= 1; 1 for
+// the plain transforms.  With `segments` the synthesis takes the
+// degree-segmented work list where the plan has one (syn_seg > 0); the partial
+// copies of F (syn_parts copies of 2 mmax + 1 by nring complex values) then
+// follow F, ws_F bytes apart.
+hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, void *F, bool segments, const MapBatch &mb,
+                            double mscale, hipStream_t st);
+hipError_t launch_leg_adjoint(const psht_plan_s &p, const void *F, void *alm, const MapBatch &mb, double mscale,
+                              hipStream_t st);
 constexpr int kAdjMaxWaves = 4;  // waves per workgroup of the adjoint
 constexpr int kAdjMaxBands = 8;  // bands per wave of the adjoint
 // Plan time: start degrees of the bands, then the states p.d_bands start from
@@ -220,18 +225,14 @@ hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nba
                              hipStream_t st);
 hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st);
 
-// Legendre synthesis of nb <= kMaxLegBatch maps in one pass (MFMA): map b reads
-// its coefficients at alm0 + b alm_stride and writes F at F0 + b ws_stride
-// (its own workspace).
-constexpr int kMaxLegBatch = 8;
-hipError_t launch_leg_synth_batch(const psht_plan_s &p, int nb, const void *alm0, int64_t alm_stride, char *F0,
-                                  int64_t ws_stride, double mscale, hipStream_t st);
-hipError_t launch_theta_synth(const psht_plan_s &p, const double *F, void *V, hipStream_t st);
-hipError_t launch_theta_adjoint(const psht_plan_s &p, const void *V, double *F, hipStream_t st);
-hipError_t launch_phi_synth(const psht_plan_s &p, const void *V, void *U, hipStream_t st);
-hipError_t launch_phi_adjoint(const psht_plan_s &p, const void *U, void *V, hipStream_t st);
-hipError_t launch_interp(const psht_plan_s &p, const void *U, void *map, hipStream_t st);
-hipError_t launch_spread(const psht_plan_s &p, const void *map, void *U, hipStream_t st);
+hipError_t launch_theta_synth(const psht_plan_s &p, const void *F, void *V, const MapBatch &mb, hipStream_t st);
+hipError_t launch_theta_adjoint(const psht_plan_s &p, const void *V, void *F, const MapBatch &mb, hipStream_t st);
+hipError_t launch_phi_synth(const psht_plan_s &p, const void *V, void *U, const MapBatch &mb, hipStream_t st);
+hipError_t launch_phi_adjoint(const psht_plan_s &p, const void *U, void *V, const MapBatch &mb, hipStream_t st);
+hipError_t launch_interp(const psht_plan_s &p, const void *U, void *map, const MapBatch &mb, hipStream_t st);
+hipError_t launch_spread(const psht_plan_s &p, const void *map, void *U, const MapBatch &mb, hipStream_t st);
+// Clears the grid rows U of a batch.
+hipError_t launch_grid_zero(const psht_plan_s &p, void *U, const MapBatch &mb, hipStream_t st);
 hipError_t launch_fill_zero(void *ptr, size_t bytes, hipStream_t st);
 
 // Patch-frame rotation (k_rotate.hip): R = Rz(alpha) Ry(beta) Rz(gamma).

@@ -80,3 +80,26 @@ def test_bands(case):
     p.stage(2, torch.as_tensor(W).cuda(), out)
     assert bool(torch.isfinite(torch.view_as_real(out)).all())
     p.close()
+
+
+@pytest.mark.parametrize("lmax,spin,rad,nm", [(96, 2, 12.0, 3), (96, 0, 12.0, 3), (1024, 2, 3.0, 7), (700, 1, 40.0, 6),
+                                              (64, 0, 20.0, 1100)])
+def test_maps_share_a_launch(lmax, spin, rad, nm):
+    """Several maps per launch (groups that share the recurrence, their
+    remainders, the segment list of such calls, more maps than one launch
+    takes): every map of both directions equals the one-map call up to the
+    order of the sums (FP64 rounding)."""
+    n = 300
+    th, ph = syn.uniform_cap(n, rad * DEG, 14300 + lmax)
+    p = Plan(th, ph, lmax, spin, 1e-10, "fp64")
+    kinds = [torch.as_tensor(syn.gaussian_alm(lmax, spin, 14400 + k)).cuda() for k in range(min(nm, 9))]
+    a = torch.stack([kinds[k % 9] for k in range(nm)])
+    f = p.synth(a)
+    g = torch.stack([f[k] * (1 + 0.5j * (k % 5)) for k in range(nm)])
+    at = p.adjoint(g)
+    for k in sorted({0, 1, nm // 2, nm - 2, nm - 1}):
+        one = p.synth(a[k])
+        assert float(torch.linalg.norm(f[k] - one) / torch.linalg.norm(one)) <= 1e-12
+        back = p.adjoint(g[k])
+        assert float(torch.linalg.norm(at[k] - back) / torch.linalg.norm(back)) <= 1e-12
+    p.close()
