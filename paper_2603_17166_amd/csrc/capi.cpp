@@ -554,7 +554,18 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
     if (g.phi_parts > 1 && !make_fft_table(p, p.fft_np_part, g.Nphi / g.phi_parts, st))
         return fail(PSHT_ERR_NOMEM, "FFT tables");
 
-    // points: bucket sort into tiles (PSHT_TILE="<rows>x<cols>" overrides the tile shape for tuning runs)
+    // points: bucket sort into tiles of 16 x 32 stencil origins.  Plans that would
+    // make fewer than 1024 such tiles (four workgroups per CU) halve them, down to
+    // 8 x 8, so that the points of a few tiles are shared by more workgroups (us at
+    // 16x32 / 8x8: 10-degree cap at lmax 128, interpolation 19.8 / 8.2; 2-degree disc
+    // at lmax 512, spreading 20.8 / 9.6; 5-degree disc at lmax 1024, interpolation
+    // 23.5 / 10.1).  Larger plans lose to the smaller tiles' halos (7-degree disc at
+    // lmax 4000, spreading 70 / 125).  PSHT_TILE="<rows>x<cols>" overrides the shape
+    // for tuning runs.
+    auto tiles = [&] {
+        return (int64_t)((g.rows_used + p.tile_x - 1) / p.tile_x) * ((g.Nphi + p.tile_y - 1) / p.tile_y);
+    };
+    while (p.tile_x * p.tile_y > 64 && tiles() < 1024) (p.tile_y > p.tile_x ? p.tile_y : p.tile_x) /= 2;
     if (const char *ts = getenv("PSHT_TILE")) {
         int tx = 0, ty = 0;
         if (sscanf(ts, "%dx%d", &tx, &ty) == 2 && tx >= 4 && ty >= 8 && tx <= 64 && ty <= 128 &&
