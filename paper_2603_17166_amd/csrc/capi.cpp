@@ -543,8 +543,11 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
         if (!build_legendre(p, ncu, st, e2)) return fail(e2);
     }
 
-    // NUFFT tables
-    if (!upload(p, p.d_psihat_t, g.psihat_theta, st) || !upload(p, p.d_psihat_p, g.psihat_phi, st) ||
+    // NUFFT tables (the kernel transforms as the factors the stages multiply by)
+    std::vector<double> scale_t(g.psihat_theta), scale_p(g.psihat_phi);
+    for (double &x : scale_t) x = 1.0 / (g.N2 * x);
+    for (double &x : scale_p) x = 1.0 / x;
+    if (!upload(p, p.d_scale_t, scale_t, st) || !upload(p, p.d_scale_p, scale_p, st) ||
         (!g.es_poly.empty() && !upload(p, p.d_es_poly, g.es_poly, st)) ||
         (!g.es_poly32.empty() && !upload(p, p.d_es_poly32, g.es_poly32, st)))
         return fail(PSHT_ERR_NOMEM, "uploading kernel tables");

@@ -14,9 +14,17 @@
 //   transform, zero-pad to the oversampled length, inverse FFT.
 // The adjoint stages are the exact transposes.
 //
-// The FFT is a mixed-radix (4, 2, 3, 5, 7, 11, 13) Stockham transform held in
-// LDS: each pass stages its butterfly inputs in registers, synchronises, and
-// writes the outputs in place, so one buffer of n complex values suffices.
+// The FFT is a mixed-radix (2 .. 11, 13) Stockham transform held in LDS: each
+// pass stages its butterfly inputs in registers, synchronises, and writes the
+// outputs in place, so one buffer of n complex values suffices.
+//
+// What bounds the stages: the passes' instructions and LDS round trips, beside
+// the memory traffic (FP64 plan of 21.6 M points at lmax 4096, us per stage with
+// all passes skipped / with radices 4, 2, 3, 5, 7, 11, 13 / as it is now: Theta
+// synthesis 86 / 287 / 212, phi synthesis 123 / 254 / 234, phi adjoint 102 / 233 /
+// 213, Theta adjoint 101 / 303 / 212).  Index arithmetic was half of all vector
+// instructions: no integer remainder or division is left in a pass, and the
+// composite radices halve the number of passes.
 #include <type_traits>
 
 #include "psht_internal.h"
@@ -87,6 +95,17 @@ template <> struct Rot<13> {
     static constexpr double s[13] = {0, 0.46472317204376851, 0.82298386589365635, 0.99270887409805397, 0.93501624268541483, 0.66312265824079519, 0.23931566428755768, -0.23931566428755743, -0.66312265824079497, -0.93501624268541472, -0.99270887409805397, -0.82298386589365702, -0.4647231720437684};
 };
 
+// e^{2 pi i p q / R}, p, q < the factors, of the composite radices 8 and 9
+template <int R> struct Inner;
+template <> struct Inner<8> {
+    static constexpr double c[4] = {1, 0.7071067811865476, 0, -0.7071067811865476};
+    static constexpr double s[4] = {0, 0.7071067811865476, 1, 0.7071067811865476};
+};
+template <> struct Inner<9> {
+    static constexpr double c[5] = {1, 0.766044443118978, 0.17364817766693036, 0, -0.9396926207859084};
+    static constexpr double s[5] = {0, 0.6427876096865394, 0.984807753012208, 0, 0.3420201433256687};
+};
+
 // Radix-R DFT in registers: y_q = sum_r v_r e^{sign 2 pi i r q / R}.  Odd R
 // uses the symmetric form: with t_r = v_r + v_{R-r} and u_r = v_r - v_{R-r},
 // y_q = a_q + sign i b_q and y_{R-q} = a_q - sign i b_q, where
@@ -139,7 +158,58 @@ template <typename C, int R> __device__ inline void dft(C *v, int sign) {
     }
 }
 
-// Threads of a workgroup transforming up to MAXN points.  The passes are
+// Composite radix A B as A-point and B-point transforms in registers.  Coprime
+// factors (6, 10): input B p + A q, output by the residues mod A and B, no
+// twiddles between.  8 = 2 4 and 9 = 3 3: input B p + q, output p + A q, with
+// e^{sign 2 pi i p q / R} between.  A pass of a composite radix costs the index
+// arithmetic, the LDS traffic and the two barriers of one pass instead of two.
+template <typename C, int A, int B> __device__ inline void dft_ab(C *v, int sign) {
+    typedef decltype(v[0].x) S;
+    constexpr int R = A * B;
+    constexpr bool coprime = A == 2 && B % 2 == 1;
+    C y[A][B];
+#pragma unroll
+    for (int q = 0; q < B; ++q) {
+        C x[A];
+#pragma unroll
+        for (int p = 0; p < A; ++p) x[p] = v[coprime ? (B * p + A * q) % R : B * p + q];
+        dft<C, A>(x, sign);
+#pragma unroll
+        for (int p = 0; p < A; ++p) y[p][q] = x[p];
+    }
+#pragma unroll
+    for (int p = 0; p < A; ++p) {
+        if constexpr (!coprime) {
+#pragma unroll
+            for (int q = 1; q < B; ++q) {
+                if (p == 0) continue;
+                const S c = (S)Inner<R>::c[p * q], s = sign * (S)Inner<R>::s[p * q];
+                const C a = y[p][q];
+                y[p][q].x = a.x * c - a.y * s;
+                y[p][q].y = a.x * s + a.y * c;
+            }
+        }
+        dft<C, B>(y[p], sign);
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            // coprime: the output with residues p mod 2 and q mod B
+            v[coprime ? ((q - p) % 2 == 0 ? q : q + B) : p + A * q] = y[p][q];
+        }
+    }
+}
+
+template <typename C, int R> __device__ inline void butterfly(C *v, int sign) {
+    if constexpr (R == 6) dft_ab<C, 2, 3>(v, sign);
+    else if constexpr (R == 8) dft_ab<C, 2, 4>(v, sign);
+    else if constexpr (R == 9) dft_ab<C, 3, 3>(v, sign);
+    else if constexpr (R == 10) dft_ab<C, 2, 5>(v, sign);
+    else dft<C, R>(v, sign);
+}
+
+// Threads of a workgroup transforming up to MAXN points: about 8 points per
+// thread up to 1024 (256 threads left half of the lanes without a butterfly of
+// radix 8 to 10; Theta adjoint at N2 = 507, NT = 1014: 31 -> 25 us; 64 threads up
+// to 512 points were slower, 7.3 -> 8.2 us at 350 points).  The passes are
 // bound by latency (LDS round trips and barriers), so what counts is the
 // number of transforms in flight per CU: up to 2560 points (40 KB of FP64
 // data) four workgroups of 256 threads fit a CU, where two of 512 did.  The
@@ -147,6 +217,7 @@ template <typename C, int R> __device__ inline void dft(C *v, int sign) {
 // give each SIMD four waves.
 template <typename T> __host__ __device__ constexpr int fft_threads(int maxn) {
     // (the 10240-point tier fills the 160 KB of LDS a gfx950 workgroup may use)
+    if (maxn <= 1024) return 128;
     if constexpr (sizeof(T) == 8) return maxn <= 2560 ? 256 : (maxn <= 4096 ? 512 : (maxn <= 8192 ? 1024 : 512));
     // FP32 data takes half the LDS per transform: the longest tier (64 KB) fits
     // two workgroups of 512 threads per CU (FP32 phi halves at lmax 4096:
@@ -160,17 +231,32 @@ template <typename T> __host__ __device__ constexpr int fft_threads(int maxn) {
 // length MAXN the kernel is built for, so short transforms do not pay the
 // registers of long ones.
 template <typename T, int R, int MAXN>
-__device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, int sign, const double2 *tw) {
+__device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns, int tws, int sign, const double2 *tw) {
     typedef typename CT<T>::type C;
     constexpr int NT = fft_threads<T>(MAXN);
     constexpr int NB = (MAXN / R + NT - 1) / NT;
+    // opaque, so that the butterfly addresses of every radix are not hoisted out
+    // of the loop over the passes and held in registers
+    int tid = threadIdx.x;
+    asm volatile("" : "+s"(n));
+    asm volatile("" : "+v"(tid));
     const int nb = n / R;
-    const int tws = n / (Ns * R);
-    C v[NB][R];
+    C v[NB][R], w[NB];
+    int k[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        int b = threadIdx.x + i * NT;
+        const int b = tid + i * NT;
+        k[i] = 0;
         if (b < nb) {
+            if (Ns > 1) {
+                // k = b mod Ns: the quotient of (b + 1/2) and Ns is at least
+                // 1 / (2 Ns) away from a whole number, far more than the
+                // rounding of the float product for b < 2^14
+                k[i] = b - __mul24((int)(((float)b + 0.5f) * inv_ns), Ns);
+                // twiddles w^r (r = 1..R-1) as powers of the one table entry w:
+                // one load per butterfly instead of R - 1 scattered ones
+                w[i] = twiddle<C>(tw, __mul24(k[i], tws), sign);
+            }
 #pragma unroll
             for (int r = 0; r < R; ++r) v[i][r] = buf[b + r * nb];
         }
@@ -178,21 +264,21 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, int sign, con
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        int b = threadIdx.x + i * NT;
+        const int b = tid + i * NT;
         if (b < nb) {
-            int k = b % Ns;
-            // twiddles w^r (r = 1..R-1) as powers of the one table entry w:
-            // one load per butterfly instead of R - 1 scattered ones
-            const C w1 = twiddle<C>(tw, k * tws, sign);
-            C wr = w1;
-            v[i][1] = cmul(v[i][1], w1);
+            if (Ns > 1) {
+                // by halving the exponent: r - 1 roundings in a row become log2 r
+                C wr[R];
+                wr[1] = w[i];
+                v[i][1] = cmul(v[i][1], wr[1]);
 #pragma unroll
-            for (int r = 2; r < R; ++r) {
-                wr = cmul(wr, w1);
-                v[i][r] = cmul(v[i][r], wr);
+                for (int r = 2; r < R; ++r) {
+                    wr[r] = cmul(wr[r / 2], wr[r - r / 2]);
+                    v[i][r] = cmul(v[i][r], wr[r]);
+                }
             }
-            dft<C, R>(v[i], sign);
-            int d = (b - k) * R + k;
+            butterfly<C, R>(v[i], sign);
+            const int d = __mul24(b - k[i], R) + k[i];
 #pragma unroll
             for (int r = 0; r < R; ++r) buf[d + r * Ns] = v[i][r];
         }
@@ -203,17 +289,20 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, int sign, con
 // In-place FFT of buf[0..n) in LDS, n <= MAXN; the caller synchronises before the call.
 template <typename T, int MAXN>
 __device__ void lds_fft(typename CT<T>::type *buf, const FftDev &f, int sign, const double2 *tw) {
-    int Ns = 1;
+    int Ns = 1, tws = f.n;
+    float inv_ns = 1.0f;
     for (int p = 0; p < f.npass; ++p) {
         const int R = (int)((f.code >> (4 * p)) & 15);
         switch (R) {
-            case 4: fft_pass<T, 4, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 2: fft_pass<T, 2, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 3: fft_pass<T, 3, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 5: fft_pass<T, 5, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 7: fft_pass<T, 7, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 11: fft_pass<T, 11, MAXN>(buf, f.n, Ns, sign, tw); break;
-            case 13: fft_pass<T, 13, MAXN>(buf, f.n, Ns, sign, tw); break;
+#define PSHT_PASS(r) \
+    case r: \
+        tws /= r; \
+        fft_pass<T, r, MAXN>(buf, f.n, Ns, inv_ns, tws, sign, tw); \
+        inv_ns *= 1.0f / r; \
+        break;
+            PSHT_PASS(2) PSHT_PASS(3) PSHT_PASS(4) PSHT_PASS(5) PSHT_PASS(6) PSHT_PASS(7)
+            PSHT_PASS(8) PSHT_PASS(9) PSHT_PASS(10) PSHT_PASS(11) PSHT_PASS(13)
+#undef PSHT_PASS
             default: break;
         }
         Ns *= R;
@@ -246,7 +335,7 @@ struct StageArgs {
     bool tsplit;  // Theta grid transform (NT = 2 N2 points) as two N2-point transforms (even / odd rows)
     const double *ring_w;
     const int32_t *ring_mmax;
-    const double *psihat_t, *psihat_p;
+    const double *scale_t, *scale_p;  // 1 / (N2 psihat(n)), 1 / psihat(m)
     int64_t ws_stride;  // bytes between the workspaces of the maps (blockIdx.y)
 };
 
@@ -279,6 +368,46 @@ template <typename T, int MAXN> struct ThetaHalves {
     static constexpr int NQ = (MAXN + NTHR - 1) / NTHR;
 };
 
+// Column m of F completed to the doubled circle and windowed, into buf[0 .. N2).
+// All of a thread's loads are issued before the first is used (in a plain loop
+// each trip waited for memory); positions past the end reread the last one.
+template <typename T, int MAXN>
+__device__ inline void load_column(typename CT<T>::type *buf, const StageArgs &a, const double2 *Fm, int am, double sig) {
+    constexpr int NTHR = fft_threads<T>(MAXN), NQ = (MAXN + NTHR - 1) / NTHR, G = NQ < 4 ? NQ : 4;
+    const int L = a.L, N2 = a.N2;
+#pragma unroll 1
+    for (int q0 = 0; q0 * NTHR < N2; q0 += G) {
+        double2 v[G];
+        double w[G];
+        int mx[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int k = min((int)threadIdx.x + (q0 + q) * NTHR, N2 - 1);
+            const int j = k <= L ? k : N2 - k;
+            v[q] = Fm[j];
+            w[q] = a.ring_w[j];
+            mx[q] = a.ring_mmax[j];
+        }
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int k = threadIdx.x + (q0 + q) * NTHR;
+            if (k < N2) {
+                const double wj = k <= L ? w[q] : sig * w[q];
+                typename CT<T>::type c;
+                c.x = mx[q] >= am ? (T)(v[q].x * wj) : (T)0;
+                c.y = mx[q] >= am ? (T)(v[q].y * wj) : (T)0;
+                buf[k] = c;
+            }
+        }
+    }
+}
+
+// Grid row of stored row r, in [0, NT).
+__device__ inline int theta_row(const StageArgs &a, int r) {
+    const int row = a.row_lo + r;  // row_lo > -NT and rows_used <= NT
+    return row < 0 ? row + a.NT : (row >= a.NT ? row - a.NT : row);
+}
+
 template <typename T, int MAXN>
 __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth(StageArgs a, const double2 *F,
                                                              typename CT<T>::type *V) {
@@ -293,26 +422,17 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth(StageArgs 
     const double sig = ((a.spin + am) & 1) ? -1.0 : 1.0;  // mirror sign (-1)^(s+m)
     const int L = a.L, N2 = a.N2, NT = a.NT;
     const double2 *Fm = F + (int64_t)mi * a.nring;
-    for (int k = threadIdx.x; k < N2; k += fft_threads<T>(MAXN)) {
-        const int j = k <= L ? k : N2 - k;
-        const double wj = (k <= L ? 1.0 : sig) * a.ring_w[j];
-        double2 v = make_double2(0.0, 0.0);
-        if (a.ring_mmax[j] >= am) v = Fm[j];
-        C c;
-        c.x = (T)(v.x * wj);
-        c.y = (T)(v.y * wj);
-        buf[k] = c;
-    }
+    load_column<T, MAXN>(buf, a, Fm, am, sig);
     __syncthreads();
     lds_fft<T, MAXN>(buf, a.fn2, -1, a.tw_n2);  // N2 * Fourier coefficient
     const int64_t ldv = 2 * a.mmax + 1;
     // divide by N2 psihat(|n|) and pad to NT: n < 0 moves from N2 - |n| to NT - |n|
     for (int n = 1 + threadIdx.x; n <= L; n += fft_threads<T>(MAXN))
-        buf[NT - n] = cscale(buf[N2 - n], (T)(1.0 / (N2 * a.psihat_t[n])));
+        buf[NT - n] = cscale(buf[N2 - n], (T)a.scale_t[n]);
     __syncthreads();
     for (int k = threadIdx.x; k < NT - L; k += fft_threads<T>(MAXN)) {
         if (k <= L) {
-            buf[k] = cscale(buf[k], (T)(1.0 / (N2 * a.psihat_t[k])));
+            buf[k] = cscale(buf[k], (T)a.scale_t[k]);
         } else {
             C z;
             z.x = z.y = (T)0;
@@ -322,8 +442,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth(StageArgs 
     __syncthreads();
     lds_fft<T, MAXN>(buf, a.fnt, +1, a.tw_nt);
     for (int r = threadIdx.x; r < a.rows_used; r += fft_threads<T>(MAXN)) {
-        int row = (a.row_lo + r) % NT;
-        if (row < 0) row += NT;
+        const int row = theta_row(a, r);
         V[(int64_t)r * ldv + mi] = buf[row];
     }
 }
@@ -342,16 +461,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth_split(Stag
     const double sig = ((a.spin + am) & 1) ? -1.0 : 1.0;  // mirror sign (-1)^(s+m)
     const int L = a.L, N2 = a.N2, NT = a.NT;
     const double2 *Fm = F + (int64_t)mi * a.nring;
-    for (int k = threadIdx.x; k < N2; k += fft_threads<T>(MAXN)) {
-        const int j = k <= L ? k : N2 - k;
-        const double wj = (k <= L ? 1.0 : sig) * a.ring_w[j];
-        double2 v = make_double2(0.0, 0.0);
-        if (a.ring_mmax[j] >= am) v = Fm[j];
-        C c;
-        c.x = (T)(v.x * wj);
-        c.y = (T)(v.y * wj);
-        buf[k] = c;
-    }
+    load_column<T, MAXN>(buf, a, Fm, am, sig);
     __syncthreads();
     lds_fft<T, MAXN>(buf, a.fn2, -1, a.tw_n2);  // N2 * Fourier coefficient
     const int64_t ldv = 2 * a.mmax + 1;
@@ -363,7 +473,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth_split(Stag
             const int i = threadIdx.x + q * H::NTHR;
             if (i < N2) {
                 const int n = i <= L ? i : N2 - i;  // |n|
-                spec[q] = cscale(buf[i], (T)(1.0 / (N2 * a.psihat_t[n])));
+                spec[q] = cscale(buf[i], (T)a.scale_t[n]);
             }
         }
         for (int h = 0; h < 2; ++h) {
@@ -380,8 +490,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_synth_split(Stag
             __syncthreads();
             lds_fft<T, MAXN>(buf, a.fn2, +1, a.tw_n2);
             for (int r = threadIdx.x; r < a.rows_used; r += H::NTHR) {
-                int row = (a.row_lo + r) % NT;
-                if (row < 0) row += NT;
+                const int row = theta_row(a, r);
                 if ((row & 1) == h) V[(int64_t)r * ldv + mi] = buf[row >> 1];
             }
         }
@@ -407,15 +516,14 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_adjoint(StageArg
     for (int k = threadIdx.x; k < NT; k += fft_threads<T>(MAXN)) buf[k] = z;
     __syncthreads();
     for (int r = threadIdx.x; r < a.rows_used; r += fft_threads<T>(MAXN)) {
-        int row = (a.row_lo + r) % NT;
-        if (row < 0) row += NT;
+        const int row = theta_row(a, r);
         buf[row] = V[(int64_t)r * ldv + mi];
     }
     __syncthreads();
     lds_fft<T, MAXN>(buf, a.fnt, -1, a.tw_nt);
     // keep |n| <= L, divide by N2 psihat, move n < 0 from NT - |n| to N2 - |n|
     for (int k = threadIdx.x; k <= L; k += fft_threads<T>(MAXN)) {
-        const T sc = (T)(1.0 / (N2 * a.psihat_t[k]));
+        const T sc = (T)a.scale_t[k];
         buf[k] = cscale(buf[k], sc);
         if (k >= 1) buf[N2 - k] = cscale(buf[NT - k], sc);
     }
@@ -459,8 +567,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_adjoint_split(St
             for (int k = threadIdx.x; k < N2; k += H::NTHR) buf[k] = z;
             __syncthreads();
             for (int r = threadIdx.x; r < a.rows_used; r += H::NTHR) {
-                int row = (a.row_lo + r) % NT;
-                if (row < 0) row += NT;
+                const int row = theta_row(a, r);
                 if ((row & 1) == h) buf[row >> 1] = V[(int64_t)r * ldv + mi];
             }
             __syncthreads();
@@ -480,7 +587,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_theta_adjoint_split(St
 #pragma unroll
         for (int q = 0; q < H::NQ; ++q) {
             const int i = threadIdx.x + q * H::NTHR;
-            if (i < N2) buf[i] = cscale(spec[q], (T)(1.0 / (N2 * a.psihat_t[i <= L ? i : N2 - i])));
+            if (i < N2) buf[i] = cscale(spec[q], (T)a.scale_t[i <= L ? i : N2 - i]);
         }
         __syncthreads();
     }
@@ -549,21 +656,38 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_phi_synth(StageArgs a,
     C z;
     z.x = z.y = (T)0;
     if (S <= 2) {
-        for (int k = threadIdx.x; k < nh; k += fft_threads<T>(MAXN)) buf[k] = z;
-        __syncthreads();
-        // |m| <= mmax < nh / 2: the m taken mod nh land on distinct entries
-        for (int mi = threadIdx.x; mi <= 2 * mm; mi += fft_threads<T>(MAXN)) {
-            const int m = mi - mm;
-            C v = cscale(Vr[mi], (T)(1.0 / a.psihat_p[abs(m)]));
-            if (h) v = cmul(v, twiddle<C>(a.tw_np_full, m < 0 ? m + Np : m, +1));
-            buf[m < 0 ? m + nh : m] = v;
+        // |m| <= mmax < nh / 2: entry k holds m = k or k - nh, or none
+        constexpr int NTHR = fft_threads<T>(MAXN), NQ = (MAXN + NTHR - 1) / NTHR, G = NQ < 4 ? NQ : 4;
+#pragma unroll 1
+        for (int q0 = 0; q0 * NTHR < nh; q0 += G) {
+            C v[G], w[G];
+            T sc[G];
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const int k = threadIdx.x + (q0 + q) * NTHR;
+                int m = k <= mm ? k : k - nh;
+                const bool in = k < nh && m >= -mm;
+                if (!in) m = 0;
+                v[q] = Vr[m + mm];
+                sc[q] = in ? (T)a.scale_p[abs(m)] : (T)0;
+                if (h) w[q] = twiddle<C>(a.tw_np_full, m < 0 ? m + Np : m, +1);
+            }
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const int k = threadIdx.x + (q0 + q) * NTHR;
+                if (k < nh) {
+                    C c = cscale(v[q], sc[q]);
+                    if (h) c = cmul(c, w[q]);
+                    buf[k] = c;
+                }
+            }
         }
     } else {
         // entry t sums the orders m = t (mod nh) in [-mmax, mmax]
         for (int t = threadIdx.x; t < nh; t += fft_threads<T>(MAXN)) {
             C acc = z;
             for (int m = t - nh * ((t + mm) / nh); m <= mm; m += nh) {
-                C v = cscale(Vr[m + mm], (T)(1.0 / a.psihat_p[abs(m)]));
+                C v = cscale(Vr[m + mm], (T)a.scale_p[abs(m)]);
                 if (h) {
                     int e = (int)(((int64_t)m * h) % Np);
                     if (e < 0) e += Np;
@@ -618,7 +742,7 @@ __global__ __launch_bounds__(fft_threads<T>(MAXN)) void k_phi_adjoint(StageArgs 
         const int m = mi - mm;
         const int f = m < 0 ? m + Np : m;
         const C v = buf[(f - h) / S];
-        Vr[mi] = cscale(v, (T)(1.0 / a.psihat_p[abs(m)]));
+        Vr[mi] = cscale(v, (T)a.scale_p[abs(m)]);
     }
 }
 
@@ -647,8 +771,8 @@ static StageArgs stage_args(const psht_plan_s &p, const MapBatch &mb) {
     a.tsplit = p.theta_split;
     a.ring_w = p.d_ring_w;
     a.ring_mmax = p.d_ring_mmax;
-    a.psihat_t = p.d_psihat_t;
-    a.psihat_p = p.d_psihat_p;
+    a.scale_t = p.d_scale_t;
+    a.scale_p = p.d_scale_p;
     a.ws_stride = mb.ws_stride;
     return a;
 }
@@ -661,7 +785,8 @@ template <typename F> static hipError_t set_lds(F kern, size_t bytes) {
 // Calls fn(std::integral_constant<int, MAXN>) for the smallest build size
 // MAXN >= n (n <= 10240).
 template <typename Fn> static void tier_dispatch(int n, Fn fn) {
-    if (n <= 1024) fn(std::integral_constant<int, 1024>());
+    if (n <= 512) fn(std::integral_constant<int, 512>());
+    else if (n <= 1024) fn(std::integral_constant<int, 1024>());
     else if (n <= 2048) fn(std::integral_constant<int, 2048>());
     else if (n <= 2560) fn(std::integral_constant<int, 2560>());
     else if (n <= 4096) fn(std::integral_constant<int, 4096>());

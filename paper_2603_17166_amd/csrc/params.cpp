@@ -27,19 +27,39 @@ bool is_smooth(int n, const int *primes, int np) {
     return n == 1;
 }
 
+// Fewest passes first (each costs a round trip through LDS and two barriers),
+// then the smallest largest radix.
+static int fewest_passes(int n, int largest) {
+    if (n == 1) return 0;
+    static const int radices[] = {13, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2};
+    int best = 1 << 20;
+    for (int q : radices)
+        if (q <= largest && n % q == 0) best = std::min(best, 1 + fewest_passes(n / q, q));
+    return best;
+}
+
 bool fft_factor(int n, FftFactors &f) {
-    static const int order[] = {4, 2, 3, 5, 7, 11, 13};
     f.n = n;
     f.npass = 0;
-    int r = n;
-    for (int q : order) {
-        while (r % q == 0) {
-            if (f.npass >= 16) return false;  // the device code holds at most 16 passes (4 bits each)
-            f.radix[f.npass++] = q;
-            r /= q;
-        }
+    if (n < 1) return false;
+    static const int primes[] = {2, 3, 5, 7, 11, 13};
+    if (!is_smooth(n, primes, 6)) return false;
+    int largest = 2;
+    const int passes = fewest_passes(n, 13);
+    while (fewest_passes(n, largest) > passes) ++largest;
+    if (passes > 16) return false;  // the device code holds at most 16 passes (4 bits each)
+    for (int r = n; r > 1;) {
+        int q = largest;
+        while (r % q != 0 || fewest_passes(r / q, q) >= fewest_passes(r, q)) --q;
+        f.radix[f.npass++] = q;
+        r /= q;
+        largest = q;
     }
-    return r == 1 && n >= 1;
+    // The first pass writes LDS at a stride of its radix: odd radices, then 2, 6
+    // and 10, have no or few bank conflicts there; 8 comes last.
+    auto key = [](int q) { return q % 2 ? 0 : q % 4 ? 1 : q == 4 ? 2 : 3; };
+    std::stable_sort(f.radix, f.radix + f.npass, [&](int a, int b) { return key(a) < key(b); });
+    return true;
 }
 
 // ------------------------------------------------------------ quadrature

@@ -171,7 +171,7 @@ struct psht_plan_s {
     int n_multi_items = 0, multi_r = 2, multi_seg = 0;
     std::shared_ptr<psht::LegTable> leg;
     // NUFFT tables
-    double *d_psihat_t = nullptr, *d_psihat_p = nullptr;
+    double *d_scale_t = nullptr, *d_scale_p = nullptr;  // 1 / (N2 psihat_theta), 1 / psihat_phi
     double *d_es_poly = nullptr;
     float *d_es_poly32 = nullptr;
     psht::FftTable fft_n2, fft_nt, fft_np, fft_np_part;
