@@ -10,23 +10,42 @@
 // c of a spin field each obey it) and d^l the Wigner small-d matrix of
 // Appendix A.  The cost is O(lmax^3); the kernels below:
 //
-// k_rot_prep  b_{l m'} = exp(-i m' gamma) a_lm' for every m' = -l..l, stored
-//             l-major with the columns in |m'|-major order 0, 1, -1, 2, -2, ...
-//             (zero where |m'| > l), so that a wavefront reads one row of
-//             consecutive columns per degree.
-// k_rot_main  one wavefront per (8 consecutive orders m, 128 consecutive
-//             columns): each lane runs the three-term recurrence in l of
-//             d^l_{m m'}(beta) for 8 orders x 2 columns, forms the partial sums
-//             sum_{m'} d b of the 8 outputs (l, m) per degree, reduces them
-//             over the 64 lanes with a transposed butterfly (each exchange
-//             round halves the values held per lane), turns them by
-//             exp(-i m alpha) and adds them into a'_lm with atomics (the
-//             columns of one order are spread over several wavefronts).
+// k_rot_prep  tables over (l, k), k = |m'|: the recurrence factor G_l(k) below and
+//             b_lk = exp(-i k gamma) a_lk scaled by it; the other sign of m' needs
+//             no entry of its own, b_{l,-k} = (-1)^k conj(b_lk).  Zeroes the output.
+// k_rot_main  one workgroup per (64 orders m, 16 values of k), lanes along m: each
+//             wavefront runs the recurrence in l of d^l_{m,k} and d^l_{m,-k} for 4
+//             values of k and adds d b in registers (no reduction over lanes; the
+//             b are uniform, scalar loads).  The four wavefronts add up in LDS over
+//             8 degrees, which then go to a'_lm with atomics.
+//
+// Normalised recurrence.  With d^l_{m m'} = h_l c_l(m) c_l(m') y_l and factors
+// that obey c_{l+1} c_l A_{l+1} = 1 (A_l(x)^2 = l^2 - x^2, c_x(x) = 1) and
+// h_{l+1} h_l = l + 1 (h_0 = 1), the three-term recurrence becomes
+//   y_{l+1} = G_l(m) G_l(m') (cos beta - m m' / (l (l + 1))) y_l - y_{l-1},
+//   G_l(x) = sqrt(2 l + 1) h_l c_l(x)^2,
+// three multiply-adds a step where the plain form takes six and a square root
+// and a division per column.  c^2 and h are ratios of double factorials,
+// (2n-1)!! / (2n)!! = W(n):
+//   l - x = 2 n:  c_l(x)^2 = W(n) W(x + n) / W(x);  otherwise the reciprocal of
+//   that at l - 1, over l^2 - x^2;   h_{2n} = 1 / W(n),  h_{2n+1} = (2 n + 1) W(n),
+// taken from log2(n!) in double-double, so no product over l is accumulated.
+//
+// Bound by the vector instructions (12 FP64 ones per degree, order and pair of
+// signs, as many again for broadcasts, sums and the flush: 62 % of the busy
+// cycles) and by the atomics (without them 0.74 ms of the 1.6 ms that separate
+// atomics for Re and Im took at lmax 1024; 128 consecutive bytes per order and
+// flush: 0.97 ms).  us per call, before (8 orders x 128 columns per wavefront,
+// summed over lanes at every degree) / now: lmax 64, two components 137 / 60;
+// lmax 256, one component 355 / 138; lmax 1024, two components 2031 / 891; lmax
+// 2048, two components 9218 / 5630.  Eight wavefronts per workgroup: 800 at lmax
+// 1024, but 76, 172 and 6220 at the other sizes.
 // k_rot_points, k_spin_phase  points and the spin basis angle.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "lane_ops.h"
 #include "leg_common.h"
@@ -34,11 +53,10 @@
 
 namespace psht {
 
-constexpr int kRotK = 8;                // orders per wavefront
-constexpr int kRotP = 2;                // columns per lane
-constexpr int kRotCols = 64 * kRotP;    // columns per wavefront
-
-__host__ __device__ inline int rot_mp(int col) { return (col & 1) ? (col + 1) / 2 : -(col / 2); }
+constexpr int kRotPairs = 4;                  // values of k = |m'| per wavefront
+constexpr int kRotWaves = 4;                  // wavefronts per workgroup
+constexpr int kRotCols = kRotPairs * kRotWaves;  // values of k per workgroup
+constexpr int kRotSteps = 8;                  // degrees between two flushes of the sums
 
 __device__ inline int64_t rot_alm_index(int lmax, int l, int m) { return (int64_t)m * (2 * lmax + 1 - m) / 2 + l; }
 
@@ -64,40 +82,73 @@ __device__ inline double2 dd_sub(double2 a, double2 b) {
 
 struct RotArgs {
     const double2 *alm;   // input [nc][nalm]
-    double2 *B;           // [nc][lmax + 1][ncol]
+    double *B;            // [lmax + 1][lmax + 1][2 nc]: (l, k, Re and Im of each component)
+    double *G;            // [lmax + 1][lmax + 1]: G_l(x), zero for x > l
     double *out;          // output [nc][nalm] complex, accumulated
     const double2 *lf;    // log2(n!) as double-double, n = 0..2 lmax
-    int lmax, ncol;
+    int lmax;
     int64_t nalm;
     double alpha, gamma, cb, hc, hs;  // cos beta, cos(beta/2), sin(beta/2)
 };
 
-__global__ __launch_bounds__(256) void k_rot_prep(RotArgs A, int nc) {
-    const int col = blockIdx.x * 256 + threadIdx.x;
-    const int l = blockIdx.y;
-    const int c = blockIdx.z;
-    if (col >= A.ncol || c >= nc) return;
-    const int mp = rot_mp(col), k = mp < 0 ? -mp : mp;
-    double2 v = make_double2(0.0, 0.0);
-    if (k <= l) {
-        double2 a = A.alm[(int64_t)c * A.nalm + rot_alm_index(A.lmax, l, k)];
-        if (k == 0) a.y = 0.0;
-        if (mp < 0) {
-            a.y = -a.y;
-            if (k & 1) {
-                a.x = -a.x;
-                a.y = -a.y;
-            }
-        }
-        const double2 e = phase_neg(mp, A.gamma);
-        v = make_double2(e.x * a.x - e.y * a.y, e.x * a.y + e.y * a.x);
-    }
-    A.B[((int64_t)c * (A.lmax + 1) + l) * A.ncol + col] = v;
+// log2 W(n), W(n) = (2n)! / (4^n n!^2)
+__device__ inline double2 rot_log_w(const double2 *lf, int n) {
+    const double2 f = lf[n], d = dd_sub(dd_sub(lf[2 * n], f), f);
+    return dd_sub(d, make_double2(2.0 * n, 0.0));
 }
 
-__global__ __launch_bounds__(256) void k_rot_zero(double *out, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] = 0.0;
+__device__ inline double rot_g(const double2 *lf, int l, int x) {
+    const int n = (l - x) / 2;
+    double2 e = dd_sub(rot_log_w(lf, x), rot_log_w(lf, x + n));
+    e = dd_sub(e, rot_log_w(lf, n));  // -log2 of the even-step c^2
+    double f = 1.0;
+    if ((l - x) & 1) {
+        f = 1.0 / ((double)(l - x) * (double)(l + x));
+    } else {
+        e.x = -e.x;
+        e.y = -e.y;
+    }
+    const double2 w = rot_log_w(lf, l / 2);
+    if (l & 1) {
+        e = dd_sub(e, make_double2(-w.x, -w.y));
+        f *= l;
+    } else {
+        e = dd_sub(e, w);
+    }
+    const double ei = floor(e.x);
+    return sqrt(2.0 * l + 1.0) * f * ldexp(exp2((e.x - ei) + e.y), (int)ei);
+}
+
+template <int NC> __global__ __launch_bounds__(256) void k_rot_prep(RotArgs A) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    const int l = blockIdx.y;
+    if (k > A.lmax) return;
+    const int64_t row = (int64_t)l * (A.lmax + 1) + k;
+    const double g = k <= l ? rot_g(A.lf, l, k) : 0.0;
+    const double2 e = phase_neg(k, A.gamma);
+    const double sc = sqrt(g / (2.0 * l + 1.0));  // (d b) / (y b') = sqrt(G_l(m)) sc
+    A.G[row] = g;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        double2 v = make_double2(0.0, 0.0);
+        if (k <= l) {
+            const int64_t i = (int64_t)c * A.nalm + rot_alm_index(A.lmax, l, k);
+            double2 a = A.alm[i];
+            if (k == 0) a.y = 0.0;
+            v = make_double2((e.x * a.x - e.y * a.y) * sc, (e.x * a.y + e.y * a.x) * sc);
+            A.out[2 * i] = A.out[2 * i + 1] = 0.0;
+        }
+        A.B[2 * (row * NC + c)] = v.x;
+        A.B[2 * (row * NC + c) + 1] = v.y;
+    }
+}
+
+// lmax = 0: the monopole does not turn
+__global__ void k_rot_monopole(const double2 *in, double *out, int nc) {
+    if ((int)threadIdx.x < nc) {
+        out[2 * threadIdx.x] = in[threadIdx.x].x;
+        out[2 * threadIdx.x + 1] = 0.0;
+    }
 }
 
 // Seed d^{l0}_{m m'}(beta), l0 = max(m, |m'|), m >= 0, from the single
@@ -157,233 +208,227 @@ __device__ inline void rot_rescale(double &cur, double &prev, int &k) {
     k += big ? 1 : 0;
 }
 
-// Factors of the recurrence that depend on the order only, for the step from
-// degree l to l + 1 (A_l(x) = sqrt(l^2 - x^2)):
-//   F1 = (2l+1)(l+1) / A_{l+1}(m),  Q = m / (l(l+1)),  F2 = (l+1) A_l(m) / (l A_{l+1}(m)),
-// zero where the step does not exist (l + 1 <= m) and Q = F2 = 0 at l = 0.
-__device__ inline double4 rot_order_factors(int l, int m) {
-    if (l + 1 <= m) return make_double4(0.0, 0.0, 0.0, 0.0);
-    const double L = l, M = m;
-    const double a1 = sqrt((L + 1) * (L + 1) - M * M);
-    const double f1 = (2 * L + 1) * (L + 1) / a1;
-    if (l == 0) return make_double4(f1, 0.0, 0.0, 0.0);
-    const double a0 = sqrt(L * L - M * M);
-    return make_double4(f1, M / (L * (L + 1)), (L + 1) * a0 / (L * a1), 0.0);
+// f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N - 1>)
+template <int N, typename Fn, int I = 0> __device__ inline void rot_unroll(const Fn &f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        rot_unroll<N, Fn, I + 1>(f);
+    }
 }
 
-// Exchange-halves round on n complex values (re[i], im[i]): lanes with the
-// given lane bit clear keep values 0..n/2-1, the others n/2..n-1, each summed
-// with the partner lane's copy.
-template <int N, int BIT>
-__device__ inline void rot_halve(double *re, double *im, int lane) {
-    constexpr int H = N / 2;
-    if (BIT == 32) {
+// Uniform values of one degree and wavefront as they lie in LDS, whole rows of 16 doubles:
+// b (2 nc per pair), G_l(k) per pair.  Each 16-lane row reads them
+// one per lane and broadcasts.
+template <int NC> struct RotRow {
+    static constexpr int g = 2 * NC * kRotPairs, size = (g + kRotPairs + 15) / 16 * 16;
+};
+
+// Barrier for LDS only: the loads and the atomics in flight are not waited for.
+__device__ inline void rot_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The states of one wavefront.
+struct RotWave {
+    double yp[kRotPairs], ypp[kRotPairs], ym[kRotPairs], ymp[kRotPairs];  // y of k and (-1)^k y of -k, with the previous ones
+    int kp[kRotPairs], km[kRotPairs];                                     // their scales
+};
+
+// Degrees lb .. lb + nsteps - 1.  MODE 2: every state has started and has scale 0.
+// MODE 1: any.  MODE 3: all started, some scaled.  MODE 0: all started, none
+// contributes (scaled, or zero): recurrence only.
+// uni, gms, rls: this wavefront's uniform rows, G_l(m) and 1 / (l (l + 1)) of
+// the chunk.
+template <int NC, int MODE>
+__device__ inline void rot_steps(RotWave &w, double *acc, int acc_stride, const double *uni, int uni_stride,
+                                 const double *gms, const double *rls, int lb, int nsteps, int m, int kw, int lane, double cb) {
+    typedef RotRow<NC> Row;
+    const double dm = m;
+#pragma unroll 1
+    for (int u = 0; u < nsteps; ++u) {
+        const int l = lb + u;
+        double x[Row::size / 16];
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            swap32(re[i], re[i + H]);
-            re[i] += re[i + H];
-            swap32(im[i], im[i + H]);
-            im[i] += im[i + H];
-        }
-    } else if (BIT == 16) {
+        for (int i = 0; i < Row::size / 16; ++i) x[i] = uni[u * uni_stride + 16 * i + (lane & 15)];
+        const double gm = gms[u * 64 + lane];
+        const double tc = gm * cb, tq = gm * (dm * rls[u]);
+        double re[NC], im[NC];
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            swap16(re[i], re[i + H]);
-            re[i] += re[i + H];
-            swap16(im[i], im[i + H]);
-            im[i] += im[i + H];
-        }
-    } else {
-        const bool up = (lane & BIT) != 0;
+        for (int c = 0; c < NC; ++c) re[c] = im[c] = 0.0;
+        rot_unroll<kRotPairs>([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            const int k = kw + p;
+            const double g = row_bcast<(Row::g + p) % 16>(x[(Row::g + p) / 16]);
+            const bool on = MODE != 1 || l >= max(m, k);
+            if (MODE != 0) {
+                double a = w.yp[p], b = w.ym[p];
+                if (MODE == 1 || MODE == 3) {
+                    a = on && w.kp[p] == 0 ? a : 0.0;
+                    b = on && w.km[p] == 0 ? b : 0.0;
+                }
+                const double s = a + b, d = a - b;
+                rot_unroll<NC>([&](auto Cc) {
+                    constexpr int c = decltype(Cc)::value, i = 2 * NC * p + 2 * c;
+                    re[c] = fma(s, row_bcast<i % 16>(x[i / 16]), re[c]);
+                    im[c] = fma(d, row_bcast<(i + 1) % 16>(x[i / 16]), im[c]);
+                });
+            }
+            const double tp = fma(-tq, (double)k, tc) * g, tm = fma(tq, (double)k, tc) * g;
+            const double np = fma(tp, w.yp[p], -w.ypp[p]), nm = fma(tm, w.ym[p], -w.ymp[p]);
+            // a state that has not started keeps its seed, with a previous value of zero
+            w.ypp[p] = on ? w.yp[p] : 0.0;
+            w.ymp[p] = on ? w.ym[p] : 0.0;
+            w.yp[p] = on ? np : w.yp[p];
+            w.ym[p] = on ? nm : w.ym[p];
+        });
+        if (MODE != 0) {
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const double sr = up ? re[i] : re[i + H], si = up ? im[i] : im[i + H];
-            const double kr = up ? re[i + H] : re[i], ki = up ? im[i + H] : im[i];
-            const double rr = BIT == 8 ? lane_xor8(sr) : lane_xor4(sr);
-            const double ri = BIT == 8 ? lane_xor8(si) : lane_xor4(si);
-            re[i] = kr + rr;
-            im[i] = ki + ri;
+            for (int c = 0; c < NC; ++c) {
+                atomicAdd(acc + u * acc_stride + (2 * c) * 64 + lane, re[c]);
+                atomicAdd(acc + u * acc_stride + (2 * c + 1) * 64 + lane, im[c]);
+            }
         }
     }
 }
 
-// Full sum of one complex value over the lanes i ^ b for the remaining bits.
-template <int BIT> __device__ inline void rot_allsum(double &re, double &im) {
-    if (BIT == 4) {
-        re += lane_xor4(re);
-        im += lane_xor4(im);
-    } else if (BIT == 2) {
-        re += quad_xor2(re);
-        im += quad_xor2(im);
-    } else {
-        re += quad_xor1(re);
-        im += quad_xor1(im);
+template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(RotArgs A) {
+    // 8 doubles between the rows of two degrees: the flush reads 8 of them side by side
+    constexpr int kStride = 2 * NC * 64 + 8;
+    typedef RotRow<NC> Row;
+    constexpr int kUni = kRotWaves * Row::size, kThreads = 64 * kRotWaves;
+    __shared__ double acc[kRotSteps * kStride];
+    __shared__ double uni[kRotSteps * kUni];
+    __shared__ double gms[kRotSteps * 64], sqg[2][kRotSteps * 64];  // G_l(m); its root, read by the flush while the next is stored
+    __shared__ double rls[2][kRotSteps];  // 1 / (l (l + 1))
+    __shared__ double2 phase[64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lmax = A.lmax, n = lmax + 1;
+    const int m0 = blockIdx.x * 64, m = m0 + lane;
+    const int kw = blockIdx.y * kRotCols + wave * kRotPairs;
+    const int first = max(m0, (int)blockIdx.y * kRotCols);  // a multiple of 8
+    if (first > lmax) return;
+
+    RotWave w;
+#pragma unroll
+    for (int p = 0; p < kRotPairs; ++p) {
+        w.yp[p] = w.ypp[p] = w.ym[p] = w.ymp[p] = 0.0;
+        w.kp[p] = w.km[p] = 0;
     }
-}
-
-// Reduce NQ = 8 NC complex values over the wavefront; afterwards lane i holds
-// the complete sum of value q = i >> S (S = 2 for NC = 2, 3 for NC = 1).
-template <int NC> __device__ inline void rot_reduce(double *re, double *im, int lane) {
-    constexpr int NQ = kRotK * NC;
-    rot_halve<NQ, 32>(re, im, lane);
-    rot_halve<NQ / 2, 16>(re, im, lane);
-    rot_halve<NQ / 4, 8>(re, im, lane);
-    if (NC == 2) {
-        rot_halve<2, 4>(re, im, lane);
-    } else {
-        rot_allsum<4>(re[0], im[0]);
+#pragma unroll 1
+    for (int i = 0; i < 2 * kRotPairs; ++i) {
+        const int k = kw + (i >> 1);
+        double v = 0.0;
+        int s = 0;
+        if (m <= lmax && k <= lmax && !(k == 0 && (i & 1))) {
+            rot_seed(A, m, (i & 1) ? -k : k, v, s);
+            const int l0 = max(m, k);
+            v *= sqrt((2.0 * l0 + 1.0) / (A.G[(int64_t)l0 * n + m] * A.G[(int64_t)l0 * n + k]));
+            if ((i & 1) && (k & 1)) v = -v;
+        }
+#pragma unroll
+        for (int p = 0; p < kRotPairs; ++p) {
+            if (i == 2 * p) w.yp[p] = v, w.kp[p] = s;
+            if (i == 2 * p + 1) w.ym[p] = v, w.km[p] = s;
+        }
     }
-    rot_allsum<2>(re[0], im[0]);
-    rot_allsum<1>(re[0], im[0]);
-}
+    // flush: value i = tid + h kThreads is part i mod 2 (Re, Im) of degree (i / 2) mod
+    // 8 of order m0 + i / 16: each order's 8 degrees are 128 consecutive bytes
+    constexpr int kFlush = 16 * 64 / kThreads;
+    if (tid < 64) phase[tid] = phase_neg(m0 + tid, A.alpha);
+    for (int i = tid; i < kRotSteps * kStride; i += kThreads) acc[i] = 0.0;
 
-template <int NC> __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_rot_main(RotArgs A) {
-    constexpr int S = (NC == 2) ? 2 : 3;
-    __shared__ double4 fac[8][kRotK];
-    __shared__ double seed_v[kRotK * kRotP][64];
-    __shared__ int seed_k[kRotK * kRotP][64];
-    const int lane = threadIdx.x;
-    const int m0 = blockIdx.x * kRotK;
-    const int col0 = blockIdx.y * kRotCols;
-    const int lmax = A.lmax;
-    const int mpmin = (col0 + 1) / 2;  // smallest |m'| of the wavefront's columns
-    int l = max(m0, mpmin);
-    if (l > lmax || m0 > lmax) return;
+    // The uniform values and the G_l(m) of a chunk of degrees are read from memory
+    // while the chunk before it is computed: one degree at a time, every step
+    // waited for memory (1.8 us a step).
+    constexpr int kNU = (kRotSteps * kUni + kThreads - 1) / kThreads, kNG = kRotSteps * 64 / kThreads;
+    double un[kNU], gn[kNG];
+    const int k0 = blockIdx.y * kRotCols;
+    auto fetch = [&](int lb) {
+#pragma unroll
+        for (int q = 0; q < kNU; ++q) {
+            const int i = tid + q * kThreads, j = i % Row::size, l = min(lb + i / kUni, lmax);
+            const int kb = k0 + (i / Row::size) % kRotWaves * kRotPairs;
+            const int p = j < Row::g ? j / (2 * NC) : j - Row::g;
+            const int64_t row = (int64_t)l * n + min(kb + p, lmax);
+            double v = 0.0;
+            if (j < Row::g) v = A.B[row * (2 * NC) + j % (2 * NC)];
+            else if (j < Row::size) v = A.G[row];
+            un[q] = v;
+        }
+#pragma unroll
+        for (int q = 0; q < kNG; ++q) {
+            const int i = tid + q * kThreads;
+            gn[q] = A.G[(int64_t)min(lb + i / 64, lmax) * n + min(m0 + i % 64, lmax)];
+        }
+    };
+    auto store = [&](int buf, int lb) {
+#pragma unroll
+        for (int q = 0; q < kNU; ++q)
+            if (tid + q * kThreads < kRotSteps * kUni) uni[tid + q * kThreads] = un[q];
+#pragma unroll
+        for (int q = 0; q < kNG; ++q) {
+            gms[tid + q * kThreads] = gn[q];
+            sqg[buf][tid + q * kThreads] = sqrt(gn[q]);
+        }
+        if (tid < kRotSteps) rls[buf][tid] = lb + tid ? 1.0 / ((double)(lb + tid) * (double)(lb + tid + 1)) : 0.0;
+    };
+    fetch(first);
+    store((first / kRotSteps) & 1, first);
+    __syncthreads();
 
-    int mpv[kRotP], amp[kRotP];
-    bool colok[kRotP];
-    double aprev[kRotP];  // A_l(m') of the current degree
+    const int started = max(min(m0 + 63, lmax), min(kw + kRotPairs - 1, lmax));  // the last first degree of the wavefront
+#pragma unroll 1
+    for (int lb = first; lb <= lmax; lb += kRotSteps) {
+        const int nsteps = min(kRotSteps, lmax + 1 - lb);
+        const int cur = (lb / kRotSteps) & 1;
+        fetch(lb + kRotSteps);
+        if (kw <= lmax && lb + nsteps > kw) {
+            bool scaled = false, live = false;
 #pragma unroll
-    for (int p = 0; p < kRotP; ++p) {
-        const int col = col0 + p * 64 + lane;
-        colok[p] = col < A.ncol;
-        mpv[p] = colok[p] ? rot_mp(col) : 0;
-        // columns past the end never start (their first degree lies past lmax)
-        amp[p] = colok[p] ? (mpv[p] < 0 ? -mpv[p] : mpv[p]) : lmax + 1;
-        const double d2 = (double)l * l - (double)mpv[p] * mpv[p];
-        aprev[p] = d2 > 0.0 ? sqrt(d2) : 0.0;
-    }
-    // states (order k, column p): value at the current degree, previous value
-    // and scale; each starts at degree max(m0 + k, |m'|) from its seed, which
-    // waits in LDS
-    double d[kRotK][kRotP], dp[kRotK][kRotP];
-    int kk[kRotK][kRotP];
-#pragma unroll
-    for (int k = 0; k < kRotK; ++k)
-#pragma unroll
-        for (int p = 0; p < kRotP; ++p) {
-            d[k][p] = dp[k][p] = 0.0;
-            kk[k][p] = 0;
-            double sv = 0.0;
-            int sk = 0;
-            if (max(m0 + k, amp[p]) <= lmax) rot_seed(A, m0 + k, mpv[p], sv, sk);
-            seed_v[k * kRotP + p][lane] = sv;
-            seed_k[k * kRotP + p][lane] = sk;
-        }
-    // the lane's output after the reduction: value q = lane >> S = k NC + c
-    const int q = lane >> S, qk = q / NC, qc = q - qk * NC;
-    const int qm = m0 + qk;
-    const bool writer = (lane & ((1 << S) - 1)) == 0 && qm <= lmax;
-    const double2 rphase = phase_neg(qm, A.alpha);
-    const double2 *Bc[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) Bc[c] = A.B + (int64_t)c * (lmax + 1) * A.ncol;
-    double *outq = A.out + 2 * ((int64_t)qc * A.nalm);
-
-    while (l <= lmax) {
-        const int lb = l, nsteps = min(8, lmax + 1 - lb);
-        {
-            const int u = lane >> 3, k = lane & 7;
-            fac[u][k] = rot_order_factors(lb + u, m0 + k);
-        }
-        __syncthreads();
-        bool slow = false;
-#pragma unroll
-        for (int k = 0; k < kRotK; ++k)
-#pragma unroll
-            for (int p = 0; p < kRotP; ++p) {
-                const int l0 = max(m0 + k, amp[p]);
-                slow |= (kk[k][p] < 0) || (l0 >= lb && l0 < lb + nsteps);
+            for (int p = 0; p < kRotPairs; ++p) {
+                scaled |= w.kp[p] < 0 || w.km[p] < 0;
+                live |= (w.kp[p] == 0 && w.yp[p] != 0.0) || (w.km[p] == 0 && w.ym[p] != 0.0);
+                // an underflowed pair of zeros may still wait for its previous value
+                live |= (w.kp[p] == 0 && w.ypp[p] != 0.0) || (w.km[p] == 0 && w.ymp[p] != 0.0);
             }
-        slow = __any(slow);
-        for (int u = 0; u < nsteps; ++u) {
-            l = lb + u;
-            double br[kRotP][NC], bi[kRotP][NC];
+            const bool mixed = lb < started || __any(scaled);
+            auto steps = [&](auto mode) {
+                rot_steps<NC, decltype(mode)::value>(w, acc, kStride, uni + wave * Row::size, kUni, gms, rls[cur], lb,
+                                                     nsteps, m, kw, lane, A.cb);
+            };
+            if (!mixed) steps(std::integral_constant<int, 2>());
+            else if (lb < started) steps(std::integral_constant<int, 1>());
+            else if (__any(live)) steps(std::integral_constant<int, 3>());
+            else steps(std::integral_constant<int, 0>());
+            if (mixed) {
 #pragma unroll
-            for (int p = 0; p < kRotP; ++p)
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    br[p][c] = bi[p][c] = 0.0;
-                    if (colok[p]) {
-                        const double2 v = Bc[c][(int64_t)l * A.ncol + col0 + p * 64 + lane];
-                        br[p][c] = v.x;
-                        bi[p][c] = v.y;
-                    }
-                }
-            double re[kRotK * NC], im[kRotK * NC];
-            if (slow) {
-#pragma unroll
-                for (int k = 0; k < kRotK; ++k)
-#pragma unroll
-                    for (int p = 0; p < kRotP; ++p)
-                        if (l == max(m0 + k, amp[p])) {
-                            d[k][p] = seed_v[k * kRotP + p][lane];
-                            dp[k][p] = 0.0;
-                            kk[k][p] = seed_k[k * kRotP + p][lane];
-                        }
-            }
-#pragma unroll
-            for (int k = 0; k < kRotK; ++k)
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    double sr = 0.0, si = 0.0;
-#pragma unroll
-                    for (int p = 0; p < kRotP; ++p) {
-                        const double dv = (slow && kk[k][p] < 0) ? 0.0 : d[k][p];
-                        sr = fma(dv, br[p][c], sr);
-                        si = fma(dv, bi[p][c], si);
-                    }
-                    re[k * NC + c] = sr;
-                    im[k * NC + c] = si;
-                }
-            rot_reduce<NC>(re, im, lane);
-            if (writer && qm <= l) {
-                double *dst = outq + 2 * rot_alm_index(lmax, l, qm);
-                atomicAdd(dst, rphase.x * re[0] - rphase.y * im[0]);
-                atomicAdd(dst + 1, rphase.x * im[0] + rphase.y * re[0]);
-            }
-            if (l < lmax) {
-                double g1[kRotP], g2[kRotP];
-#pragma unroll
-                for (int p = 0; p < kRotP; ++p) {
-                    const double d2 = (double)(l + 1) * (l + 1) - (double)mpv[p] * mpv[p];
-                    const double an = d2 > 0.0 ? sqrt(d2) : 0.0;
-                    g1[p] = an > 0.0 ? 1.0 / an : 0.0;
-                    g2[p] = aprev[p] * g1[p];
-                    aprev[p] = an;
-                }
-#pragma unroll
-                for (int k = 0; k < kRotK; ++k) {
-                    const double4 f = fac[u][k];
-#pragma unroll
-                    for (int p = 0; p < kRotP; ++p) {
-                        const double t = fma(-f.y, (double)mpv[p], A.cb);
-                        const double a = f.x * g1[p] * t, b = f.z * g2[p];
-                        const double nv = fma(a, d[k][p], -b * dp[k][p]);
-                        dp[k][p] = d[k][p];
-                        d[k][p] = nv;
-                    }
+                for (int p = 0; p < kRotPairs; ++p) {
+                    rot_rescale(w.yp[p], w.ypp[p], w.kp[p]);
+                    rot_rescale(w.ym[p], w.ymp[p], w.km[p]);
                 }
             }
         }
-        if (slow) {
+        rot_barrier();
+        const int fu = (tid >> 1) & (kRotSteps - 1), l = lb + fu;
 #pragma unroll
-            for (int k = 0; k < kRotK; ++k)
+        for (int h = 0; h < kFlush; ++h) {
+            const int j = (tid + h * kThreads) / 16;
+            const bool in = l <= lmax && m0 + j <= l;
+            const double sc = in ? sqg[cur][fu * 64 + j] : 0.0;
+            const double2 ph = phase[j];
+            const double pr = (tid & 1) ? ph.y : ph.x, pi = (tid & 1) ? ph.x : -ph.y;
 #pragma unroll
-                for (int p = 0; p < kRotP; ++p) rot_rescale(d[k][p], dp[k][p], kk[k][p]);
+            for (int c = 0; c < NC; ++c) {
+                // both lanes of a value read before either clears
+                double *src = acc + fu * kStride + 2 * c * 64 + j;
+                const double re = src[0], im = src[64];
+                src[64 * (tid & 1)] = 0.0;
+                if (in && (re != 0.0 || im != 0.0))
+                    atomicAdd(A.out + 2 * ((int64_t)c * A.nalm + rot_alm_index(lmax, l, m0 + j)) + (tid & 1),
+                              (pr * re + pi * im) * sc);
+            }
         }
-        __syncthreads();
-        l = lb + nsteps;
+        store(cur ^ 1, lb + kRotSteps);
+        rot_barrier();
     }
 }
 
@@ -434,23 +479,30 @@ hipError_t launch_rotate_alm(int lmax, int nc, double alpha, double beta, double
                              void *alm_out, void *ws, const double2 *lf, hipStream_t st) {
     RotArgs A;
     A.alm = (const double2 *)alm_in;
-    A.B = (double2 *)ws;
+    // B and G: (nc 16 + 8)(lmax + 1)^2 bytes, within the workspace's nc 16 (lmax + 1)(2 lmax + 1) from lmax = 1 on
+    A.B = (double *)ws;
+    A.G = A.B + 2 * (int64_t)nc * (lmax + 1) * (lmax + 1);
     A.out = (double *)alm_out;
     A.lf = lf;
     A.lmax = lmax;
-    A.ncol = 2 * lmax + 1;
     A.nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
     A.alpha = alpha;
     A.gamma = gamma;
     A.cb = cos(beta);
     A.hc = cos(0.5 * beta);
     A.hs = sin(0.5 * beta);
-    const int64_t nout = 2 * (int64_t)nc * A.nalm;
-    k_rot_zero<<<dim3((unsigned)((nout + 255) / 256)), 256, 0, st>>>(A.out, nout);
-    k_rot_prep<<<dim3((A.ncol + 255) / 256, lmax + 1, nc), 256, 0, st>>>(A, nc);
-    const dim3 grid((lmax + kRotK) / kRotK, (A.ncol + kRotCols - 1) / kRotCols);
-    if (nc == 2) k_rot_main<2><<<grid, 64, 0, st>>>(A);
-    else k_rot_main<1><<<grid, 64, 0, st>>>(A);
+    if (lmax == 0) {
+        k_rot_monopole<<<1, 64, 0, st>>>(A.alm, A.out, nc);
+        return hipGetLastError();
+    }
+    const dim3 prep((lmax + 256) / 256, lmax + 1), grid((lmax + 64) / 64, (lmax + kRotCols) / kRotCols);
+    if (nc == 2) {
+        k_rot_prep<2><<<prep, 256, 0, st>>>(A);
+        k_rot_main<2><<<grid, 64 * kRotWaves, 0, st>>>(A);
+    } else {
+        k_rot_prep<1><<<prep, 256, 0, st>>>(A);
+        k_rot_main<1><<<grid, 64 * kRotWaves, 0, st>>>(A);
+    }
     return hipGetLastError();
 }
 
