@@ -102,8 +102,8 @@ def stage_work(w, info) -> dict:
     }
 
 
-STAGE_KERNEL = {"leg_synth": ("psht::k_leg_synth<", "psht::k_leg_synth_seg<"),
-                "leg_adj": ("psht::k_leg_adj_seg6<", "psht::k_leg_adj_seg4<"),
+STAGE_KERNEL = {"leg_synth": ("psht::k_leg_synth<",),
+                "leg_adj": ("psht::k_leg_adj8<", "psht::k_leg_adj4<"),
                 "theta_synth": ("psht::k_theta_synth<",), "theta_adj": ("psht::k_theta_adjoint<",),
                 "phi_synth": ("psht::k_phi_synth<",), "phi_adj": ("psht::k_phi_adjoint<",),
                 "interp": ("psht::k_interp<",), "spread": ("psht::k_spread<",)}
@@ -423,8 +423,8 @@ def rotation_triples(lmax: int) -> int:
 def patch_frame(lmax: int, npoints: int, steps: int, log) -> dict:
     """Rotation into the patch frame (Sec. II, step 1) at the largest workload's
     size: coefficients of both components at lmax 4096 (FP64 ALU bound:
-    16 FLOP per (l, m, m') step, 8 for the d recurrence and 4 per component
-    for the accumulation) and the points with their spin angle (HBM bound:
+    16 FLOP per (l, m, m') step, 8 for the plain d recurrence and 4 per
+    component for the accumulation) and the points with their spin angle (HBM bound:
     16 bytes read and 24 written per point)."""
     import torch
 
@@ -712,7 +712,7 @@ def main() -> int:
     ap.add_argument("--serve-policy", default="sjf", choices=("fifo", "sjf"),
                     help="admission order: oldest first, or cheapest plan first with an age limit")
     ap.add_argument("--serve-max-batch", type=int, default=8,
-                    help="requests of one kind per launch (8: the maps of one batched Legendre pass)")
+                    help="requests of one kind per launch (maps of one call)")
     ap.add_argument("--serve-fp64-single", type=int, default=300,
                     help="requests of the served mix also run one at a time on FP64 plans")
     ap.add_argument("--full-sky-only", action="store_true", help="only the full-sky vs partial comparison")
