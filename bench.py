@@ -160,6 +160,7 @@ def roofline(w, info, avg: dict) -> dict:
     bound, amount, peak = stage_work(w, info)[dom]
     if bound == "alu":
         per = leg_flops_per_triple(w.spin) if dom.startswith("leg") else nufft_flops_per_point(info["nufft_w"])
+        # every triple of l >= m counts, also those below the ring bands' first degrees, which do not run
         unit_name = "(ring, m, l) triple" if dom.startswith("leg") else "point"
         roof = {"bound": "alu", "achieved": amount / (avg[dom] * 1e-3) / 1e12, "peak": peak / 1e12,
                 "unit": "TFLOP/s", "work": "%.4g FLOP per launch (%d per %s)" % (amount, per, unit_name)}
