@@ -12,6 +12,7 @@
 #include <vector>
 #include <new>
 #include <string>
+#include <tuple>
 
 #include "leg_common.h"
 #include "psht_internal.h"
@@ -85,8 +86,9 @@ template <typename Fn> hipError_t timed(psht_plan_s &p, int stage, hipStream_t s
     return e;
 }
 
-bool make_fft_table(psht_plan_s &p, psht::FftTable &t, int n, hipStream_t st) {
-    if (!psht::fft_factor(n, t.f)) return false;
+// fp32: the table serves transforms of float data (they take other radices).
+bool make_fft_table(psht_plan_s &p, psht::FftTable &t, int n, bool fp32, hipStream_t st) {
+    if (!psht::fft_factor(n, fp32, t.f)) return false;
     t.n = n;
     std::vector<double> tw(2 * (size_t)n);
     const long double pi = 3.141592653589793238462643383279502884L;
@@ -551,10 +553,10 @@ psht_status plan_create_impl(psht_plan *out, int lmax, int spin, int64_t npoints
         (!g.es_poly.empty() && !upload(p, p.d_es_poly, g.es_poly, st)) ||
         (!g.es_poly32.empty() && !upload(p, p.d_es_poly32, g.es_poly32, st)))
         return fail(PSHT_ERR_NOMEM, "uploading kernel tables");
-    if (!make_fft_table(p, p.fft_n2, g.N2, st) || !make_fft_table(p, p.fft_nt, g.Ntheta, st) ||
-        !make_fft_table(p, p.fft_np, g.Nphi, st))
+    if (!make_fft_table(p, p.fft_n2, g.N2, g.fp32, st) || !make_fft_table(p, p.fft_nt, g.Ntheta, g.fp32, st) ||
+        !make_fft_table(p, p.fft_np, g.Nphi, g.fp32, st))
         return fail(PSHT_ERR_NOMEM, "FFT tables");
-    if (g.phi_parts > 1 && !make_fft_table(p, p.fft_np_part, g.Nphi / g.phi_parts, st))
+    if (g.phi_parts > 1 && !make_fft_table(p, p.fft_np_part, g.Nphi / g.phi_parts, g.fp32, st))
         return fail(PSHT_ERR_NOMEM, "FFT tables");
 
     // points: bucket sort into tiles of 16 x 32 stencil origins.  Plans that would
@@ -1045,23 +1047,23 @@ psht_status psht_stage(psht_plan plan, int stage, const void *in, void *out, voi
 
 psht_status psht_fft(int n, int batch, int sign, int fp32, const void *in, void *out, void *hip_stream) {
     static std::mutex mu;
-    static std::map<std::pair<int, int>, psht_plan_s *> tables;  // kept for the process lifetime
+    static std::map<std::tuple<int, int, bool>, psht_plan_s *> tables;  // kept for the process lifetime
     if (n < 1 || batch < 0 || (sign != 1 && sign != -1)) return fail(PSHT_ERR_ARG, "bad n, batch or sign");
     if (batch > 0 && (!in || !out)) return fail(PSHT_ERR_ARG, "in or out is NULL");
     if (n > (fp32 ? psht::kFftMaxLds32 : psht::kFftMaxLds64)) return fail(PSHT_ERR_UNSUPPORTED, "n above the LDS limit");
     psht::FftFactors f;
-    if (!psht::fft_factor(n, f)) return fail(PSHT_ERR_UNSUPPORTED, "n has a prime factor outside 2,3,5,7,11,13");
+    if (!psht::fft_factor(n, fp32 != 0, f)) return fail(PSHT_ERR_UNSUPPORTED, "n has a prime factor outside 2,3,5,7,11,13");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     psht_plan_s *holder;
     {
         std::lock_guard<std::mutex> lock(mu);
         int dev = 0;
         (void)hipGetDevice(&dev);
-        auto key = std::make_pair(n, dev);
+        auto key = std::make_tuple(n, dev, fp32 != 0);
         auto it = tables.find(key);
         if (it == tables.end()) {
             holder = new psht_plan_s();
-            if (!make_fft_table(*holder, holder->fft_np, n, st) || hipStreamSynchronize(st) != hipSuccess) {
+            if (!make_fft_table(*holder, holder->fft_np, n, fp32 != 0, st) || hipStreamSynchronize(st) != hipSuccess) {
                 free_plan(holder);
                 return fail(PSHT_ERR_NOMEM, "FFT table");
             }

@@ -14,7 +14,8 @@
 //   transform, zero-pad to the oversampled length, inverse FFT.
 // The adjoint stages are the exact transposes.
 //
-// The FFT is a mixed-radix (2 .. 11, 13) Stockham transform held in LDS: each
+// The FFT is a mixed-radix (2 .. 11, 13; without 6, 8, 9, 10 for float data)
+// Stockham transform held in LDS: each
 // pass stages its butterfly inputs in registers, synchronises, and writes the
 // outputs in place, so one buffer of n complex values suffices.
 //
@@ -235,6 +236,9 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     typedef typename CT<T>::type C;
     constexpr int NT = fft_threads<T>(MAXN);
     constexpr int NB = (MAXN / R + NT - 1) / NT;
+    // float data multiply by the unit twiddles of the first pass too: without, the
+    // compiler fuses other products and sums (see fft_factor)
+    constexpr bool kPlain = sizeof(T) == 4;
     // opaque, so that the butterfly addresses of every radix are not hoisted out
     // of the loop over the passes and held in registers
     int tid = threadIdx.x;
@@ -242,21 +246,21 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     asm volatile("" : "+v"(tid));
     const int nb = n / R;
     C v[NB][R];
-    double2 w[NB];
+    C w[NB];
     int k[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int b = tid + i * NT;
         k[i] = 0;
         if (b < nb) {
-            if (Ns > 1) {
+            if (kPlain || Ns > 1) {
                 // k = b mod Ns: the quotient of (b + 1/2) and Ns is at least
                 // 1 / (2 Ns) away from a whole number, far more than the
                 // rounding of the float product for b < 2^14
                 k[i] = b - __mul24((int)(((float)b + 0.5f) * inv_ns), Ns);
                 // twiddles w^r (r = 1..R-1) as powers of the one table entry w:
                 // one load per butterfly instead of R - 1 scattered ones
-                w[i] = twiddle<double2>(tw, __mul24(k[i], tws), sign);
+                w[i] = twiddle<C>(tw, __mul24(k[i], tws), sign);
             }
 #pragma unroll
             for (int r = 0; r < R; ++r) v[i][r] = buf[b + r * nb];
@@ -267,19 +271,15 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     for (int i = 0; i < NB; ++i) {
         const int b = tid + i * NT;
         if (b < nb) {
-            if (Ns > 1) {
+            if (kPlain || Ns > 1) {
                 // formed by halving the exponent (r - 1 roundings in a row become
-                // log2 r), in double also for float data: with float powers the
-                // 3360-point transform had an error of 2.0e-7 instead of 1.2e-7
-                double2 wr[R];
+                // log2 r); float data keep the plain chain, see fft_factor
+                C wr[R];
                 wr[1] = w[i];
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-                    if (r > 1) wr[r] = cmul(wr[r / 2], wr[r - r / 2]);
-                    C f;
-                    f.x = (T)wr[r].x;
-                    f.y = (T)wr[r].y;
-                    v[i][r] = cmul(v[i][r], f);
+                    if (r > 1) wr[r] = sizeof(T) == 8 ? cmul(wr[r / 2], wr[r - r / 2]) : cmul(wr[r - 1], w[i]);
+                    v[i][r] = cmul(v[i][r], wr[r]);
                 }
             }
             butterfly<C, R>(v[i], sign);
@@ -291,6 +291,9 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     __syncthreads();
 }
 
+// The radices of float transforms.
+__host__ __device__ constexpr bool fft_plain_radix(int r) { return r == 4 || r == 2 || (r % 2 == 1 && r != 9); }
+
 // In-place FFT of buf[0..n) in LDS, n <= MAXN; the caller synchronises before the call.
 template <typename T, int MAXN>
 __device__ void lds_fft(typename CT<T>::type *buf, const FftDev &f, int sign, const double2 *tw) {
@@ -301,9 +304,11 @@ __device__ void lds_fft(typename CT<T>::type *buf, const FftDev &f, int sign, co
         switch (R) {
 #define PSHT_PASS(r) \
     case r: \
-        tws /= r; \
-        fft_pass<T, r, MAXN>(buf, f.n, Ns, inv_ns, tws, sign, tw); \
-        inv_ns *= 1.0f / r; \
+        if constexpr (sizeof(T) == 8 || fft_plain_radix(r)) { \
+            tws /= r; \
+            fft_pass<T, r, MAXN>(buf, f.n, Ns, inv_ns, tws, sign, tw); \
+            inv_ns *= 1.0f / r; \
+        } \
         break;
             PSHT_PASS(2) PSHT_PASS(3) PSHT_PASS(4) PSHT_PASS(5) PSHT_PASS(6) PSHT_PASS(7)
             PSHT_PASS(8) PSHT_PASS(9) PSHT_PASS(10) PSHT_PASS(11) PSHT_PASS(13)
@@ -922,6 +927,8 @@ static hipError_t fft_rows_t(const FftTable &t, int batch, int sign, const void 
 hipError_t launch_fft_rows(const FftTable &t, int batch, int sign, bool fp32, const void *in, void *out,
                            hipStream_t st) {
     if (batch == 0) return hipSuccess;
+    for (int i = 0; fp32 && i < t.f.npass; ++i)
+        if (!fft_plain_radix(t.f.radix[i])) return hipErrorInvalidValue;  // a table made for double data
     const hipError_t e = fp32 ? fft_rows_t<float>(t, batch, sign, in, out, st) : fft_rows_t<double>(t, batch, sign, in, out, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();

@@ -38,19 +38,37 @@ static int fewest_passes(int n, int largest) {
     return best;
 }
 
-bool fft_factor(int n, FftFactors &f) {
+// Transforms of float data keep the prime radices and 4, in this order: their
+// rounding (2e-7) is seen in an FP32 plan's results, and another order of the
+// same sums would move them by as much.
+static bool factor_plain(int n, FftFactors &f) {
+    static const int order[] = {4, 2, 3, 5, 7, 11, 13};
+    int r = n;
+    for (int q : order) {
+        while (r % q == 0) {
+            if (f.npass >= 16) return false;  // the device code holds at most 16 passes (4 bits each)
+            f.radix[f.npass++] = q;
+            r /= q;
+        }
+    }
+    return r == 1;
+}
+
+bool fft_factor(int n, bool fp32, FftFactors &f) {
     f.n = n;
     f.npass = 0;
     if (n < 1) return false;
+    if (fp32) return factor_plain(n, f);
     static const int primes[] = {2, 3, 5, 7, 11, 13};
     if (!is_smooth(n, primes, 6)) return false;
     int largest = 2;
     const int passes = fewest_passes(n, 13);
     while (fewest_passes(n, largest) > passes) ++largest;
-    if (passes > 16) return false;  // the device code holds at most 16 passes (4 bits each)
+    if (passes > 16) return false;
     for (int r = n; r > 1;) {
         int q = largest;
-        while (r % q != 0 || fewest_passes(r / q, q) >= fewest_passes(r, q)) --q;
+        // (no kernel has radix 12)
+        while (q == 12 || r % q != 0 || fewest_passes(r / q, q) >= fewest_passes(r, q)) --q;
         f.radix[f.npass++] = q;
         r /= q;
         largest = q;

@@ -76,7 +76,7 @@ struct FftFactors {
     int n = 0, npass = 0;
     int radix[16];
 };
-bool fft_factor(int n, FftFactors &f);
+bool fft_factor(int n, bool fp32, FftFactors &f);
 bool is_smooth(int n, const int *primes, int np);
 
 // ------------------------------------------------ Legendre recurrence tables

@@ -1,5 +1,5 @@
-"""LDS transforms of every radix (2 .. 11, 13, composites 6, 8, 9, 10 included) and
-at both sides of the length tiers, against numpy."""
+"""LDS transforms of every radix (2 .. 11, 13; the composites 6, 8, 9, 10 for double
+data) and at both sides of the length tiers, against numpy."""
 import numpy as np
 import pytest
 
@@ -10,8 +10,8 @@ from paper_2603_17166_amd.plan import fft
 pytestmark = pytest.mark.gpu
 
 SINGLE = [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 13]  # one pass
-MIXED = [14, 16, 18, 64, 81, 90, 143, 169, 182, 350, 512, 520, 1000, 1024, 1029, 1859, 2025, 2048, 2058, 2310, 2366,
-         2430, 2560, 2574, 4050, 4095, 4096, 4116, 5376, 7203, 8192, 8232, 10000, 10240]
+MIXED = [14, 16, 18, 64, 81, 90, 143, 156, 169, 182, 350, 512, 520, 1000, 1024, 1029, 1859, 2025, 2048, 2058, 2310, 2366,
+         2430, 2560, 2574, 3744, 4050, 4095, 4096, 4116, 5376, 7203, 8192, 8232, 10000, 10240]
 
 
 @pytest.mark.parametrize("fp32", [False, True])
