@@ -236,9 +236,6 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     typedef typename CT<T>::type C;
     constexpr int NT = fft_threads<T>(MAXN);
     constexpr int NB = (MAXN / R + NT - 1) / NT;
-    // float data multiply by the unit twiddles of the first pass too: without, the
-    // compiler fuses other products and sums (see fft_factor)
-    constexpr bool kPlain = sizeof(T) == 4;
     // opaque, so that the butterfly addresses of every radix are not hoisted out
     // of the loop over the passes and held in registers
     int tid = threadIdx.x;
@@ -253,7 +250,7 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
         const int b = tid + i * NT;
         k[i] = 0;
         if (b < nb) {
-            if (kPlain || Ns > 1) {
+            if (Ns > 1) {
                 // k = b mod Ns: the quotient of (b + 1/2) and Ns is at least
                 // 1 / (2 Ns) away from a whole number, far more than the
                 // rounding of the float product for b < 2^14
@@ -271,19 +268,62 @@ __device__ void fft_pass(typename CT<T>::type *buf, int n, int Ns, float inv_ns,
     for (int i = 0; i < NB; ++i) {
         const int b = tid + i * NT;
         if (b < nb) {
-            if (kPlain || Ns > 1) {
+            if (Ns > 1) {
                 // formed by halving the exponent (r - 1 roundings in a row become
-                // log2 r); float data keep the plain chain, see fft_factor
+                // log2 r)
                 C wr[R];
                 wr[1] = w[i];
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-                    if (r > 1) wr[r] = sizeof(T) == 8 ? cmul(wr[r / 2], wr[r - r / 2]) : cmul(wr[r - 1], w[i]);
+                    if (r > 1) wr[r] = cmul(wr[r / 2], wr[r - r / 2]);
                     v[i][r] = cmul(v[i][r], wr[r]);
                 }
             }
             butterfly<C, R>(v[i], sign);
             const int d = __mul24(b - k[i], R) + k[i];
+#pragma unroll
+            for (int r = 0; r < R; ++r) buf[d + r * Ns] = v[i][r];
+        }
+    }
+    __syncthreads();
+}
+
+// The pass of float data: the same butterfly with the products and sums in the
+// order that FP32 plans have always had (see fft_factor).
+template <typename T, int R, int MAXN>
+__device__ void fft_pass_plain(typename CT<T>::type *buf, int n, int Ns, int sign, const double2 *tw) {
+    typedef typename CT<T>::type C;
+    constexpr int NT = fft_threads<T>(MAXN);
+    constexpr int NB = (MAXN / R + NT - 1) / NT;
+    const int nb = n / R;
+    const int tws = n / (Ns * R);
+    C v[NB][R];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        int b = threadIdx.x + i * NT;
+        if (b < nb) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[i][r] = buf[b + r * nb];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        int b = threadIdx.x + i * NT;
+        if (b < nb) {
+            int k = b % Ns;
+            // twiddles w^r (r = 1..R-1) as powers of the one table entry w:
+            // one load per butterfly instead of R - 1 scattered ones
+            const C w1 = twiddle<C>(tw, k * tws, sign);
+            C wr = w1;
+            v[i][1] = cmul(v[i][1], w1);
+#pragma unroll
+            for (int r = 2; r < R; ++r) {
+                wr = cmul(wr, w1);
+                v[i][r] = cmul(v[i][r], wr);
+            }
+            dft<C, R>(v[i], sign);
+            int d = (b - k) * R + k;
 #pragma unroll
             for (int r = 0; r < R; ++r) buf[d + r * Ns] = v[i][r];
         }
@@ -304,10 +344,12 @@ __device__ void lds_fft(typename CT<T>::type *buf, const FftDev &f, int sign, co
         switch (R) {
 #define PSHT_PASS(r) \
     case r: \
-        if constexpr (sizeof(T) == 8 || fft_plain_radix(r)) { \
+        if constexpr (sizeof(T) == 8) { \
             tws /= r; \
             fft_pass<T, r, MAXN>(buf, f.n, Ns, inv_ns, tws, sign, tw); \
             inv_ns *= 1.0f / r; \
+        } else if constexpr (fft_plain_radix(r)) { \
+            fft_pass_plain<T, r, MAXN>(buf, f.n, Ns, sign, tw); \
         } \
         break;
             PSHT_PASS(2) PSHT_PASS(3) PSHT_PASS(4) PSHT_PASS(5) PSHT_PASS(6) PSHT_PASS(7)
