@@ -15,9 +15,9 @@
 // The adjoint stages are the exact transposes.
 //
 // The FFT is a mixed-radix (2 .. 11, 13; without 6, 8, 9, 10 for float data)
-// Stockham transform held in LDS: each
-// pass stages its butterfly inputs in registers, synchronises, and writes the
-// outputs in place, so one buffer of n complex values suffices.
+// Stockham transform held in LDS: each pass stages its butterfly inputs in
+// registers, synchronises, and writes the outputs in place, so one buffer of n
+// complex values suffices.
 //
 // What bounds the stages: the passes' instructions and LDS round trips, beside
 // the memory traffic (FP64 plan of 21.6 M points at lmax 4096, us per stage with
