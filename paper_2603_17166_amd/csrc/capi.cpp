@@ -250,7 +250,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     std::vector<int32_t> bs(nbands);
     ScopedDevFree d_init, d_lost;
     hipError_t e = hipMalloc(&d_init.p, sizeof(psht::LegBand) * (size_t)std::max(nbands, 1));
-    if (e == hipSuccess) e = hipMalloc(&d_lost.p, sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc(&d_lost.p, 2 * sizeof(int32_t));
     if (e != hipSuccess) return device(e, "Legendre bands");
     auto *init = static_cast<psht::LegBand *>(d_init.p);
     if (!dalloc(p, p.d_band_bs, nbands) || !upload(p, p.d_orders, orders, st)) return nomem("Legendre bands");
@@ -287,9 +287,12 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     p.syn_seg = synth_segment_length(g, ncu, first, last);
     if (p.syn_seg > 0) S = std::min(S, p.syn_seg);
 
-    // stored states; a state that leaves the double range although it matters
-    // later in its segment (never seen below spins in the hundreds) shortens
-    // the segments to 64 degrees, in which no value grows from 2^-960 to 2^-64
+    // stored states; one that leaves the double range although it matters before
+    // the next (seen at spins in the hundreds only, in the weaker sign) shortens the
+    // segments of the adjoint, whose items run from state to state, to 64 degrees,
+    // in which no value grows from 2^-960 to 2^-64.  The items of the synthesis run
+    // on over several states: where one that leaves the range matters at any later
+    // degree, they reload at every state (syn_reload)
     std::vector<psht::LegBand> bands(nbands);
     if (!dalloc(p, p.d_bands, nbands)) return nomem("Legendre bands");
     for (;;) {
@@ -306,17 +309,18 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
         const size_t held = p.allocations.size(), resident = p.resident;
         if (!dalloc(p, p.d_st_p, (size_t)blk * 128) || (s > 0 && !dalloc(p, p.d_st_m, (size_t)blk * 128)))
             return nomem("Legendre recurrence states");
-        int32_t lost = 0;
+        int32_t lost[2] = {0, 0};
         if (nbands > 0) {
             e = hipMemcpy(p.d_bands, bands.data(), sizeof(bands[0]) * nbands, hipMemcpyHostToDevice);
-            if (e == hipSuccess) e = psht::launch_fill_zero(d_lost.p, sizeof(int32_t), st);
+            if (e == hipSuccess) e = psht::launch_fill_zero(d_lost.p, sizeof(lost), st);
             if (e == hipSuccess)
                 e = psht::launch_leg_states(p, nbands, static_cast<int32_t *>(d_lost.p), st);
-            if (e == hipSuccess) e = hipMemcpyAsync(&lost, d_lost.p, sizeof(lost), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipMemcpyAsync(lost, d_lost.p, sizeof(lost), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) e = hipStreamSynchronize(st);
             if (e != hipSuccess) return device(e, "Legendre recurrence states");
         }
-        if (lost == 0) break;
+        p.syn_reload = lost[1] > 0;
+        if (lost[0] == 0) break;
         if (S == 64) {
             err = {PSHT_ERR_UNSUPPORTED, "Legendre recurrence leaves the double range within 64 degrees"};
             return false;
@@ -419,13 +423,14 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
                 }
         }
     };
-    const int fixed = psht::leg_bands_per_wave();
+    const int rmax_synth = p.syn_reload ? psht::kSynthReloadBands : 4;
+    const int fixed = std::min(rmax_synth, psht::leg_bands_per_wave());  // 0: not fixed
     // segmented lists: syn_seg degrees; and for calls of several maps, which fill
     // the GPU with fewer items, four times as many (fewer copies of F to add; 8
     // maps at lmax 2048 on a 5-degree disc: 146 -> 115 us) with two bands per wave
     p.syn_parts = 0;
     if (p.syn_seg > 0) {
-        p.syn_r = fixed ? fixed : 4;
+        p.syn_r = fixed ? fixed : rmax_synth;
         // copies for every segment of the longest order
         p.syn_parts = (lmax + 1 - s + p.syn_seg - 1) / p.syn_seg - 1;
         p.multi_seg = 4 * p.syn_seg < lmax + 1 - s ? 4 * p.syn_seg : 0;
@@ -444,7 +449,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     }
     // plain list: the items of an order on one XCD (blocks are dealt round-robin
     // to the eight), so that they share its L2, each XCD's longest first
-    p.leg_r = fixed ? fixed : (nbands >= 10 * slots ? 4 : nbands >= slots ? 2 : 1);
+    p.leg_r = fixed ? fixed : (nbands >= 10 * slots ? rmax_synth : nbands >= slots ? 2 : 1);
     std::vector<psht::SynthItem> per[8], plain;
     size_t most = 0;
     for (int x = 0; x < 8; ++x) {

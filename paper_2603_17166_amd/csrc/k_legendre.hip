@@ -20,7 +20,9 @@
 // reaches 2^-64 (kLegStartExp): the terms left out lie below the rounding of the
 // sums.  The recurrence of each band starts from a state stored at plan time
 // (mu_l, mu_{l-1}; in the double range, see k_leg_states), so the kernels carry
-// no exponents.  A wave holds several bands (registers) and takes them in one
+// no exponents.  (At spins in the hundreds the weaker sign of a ring can lie below
+// the double range at that degree and matter later: such plans take every band's
+// next stored state in as l passes it, see synth_run.)  A wave holds several bands (registers) and takes them in one
 // after the other as l passes their starts.  At lmax 4096 (35 degree cap) the
 // bands start at 0.73 of the (ring, m, l) triples of l >= m, at lmax 2048 0.78.
 //
@@ -231,8 +233,10 @@ template <int NM> struct SynthStage {
 
 // The chunks from c while R bands have entered, then those with one more (one
 // loop per R, so that the bands stay in their registers).  The next band is
-// loaded during the last chunk before it enters.
-template <int R, int RMAX, int NM, bool SPIN>
+// loaded during the last chunk before it enters.  RELOAD: the bands take in the
+// state stored for each segment start they pass, since the one they entered with
+// may have lost a value that matters from there on (k_leg_states).
+template <int R, int RMAX, int NM, bool SPIN, bool RELOAD>
 __device__ __forceinline__ void synth_run(const SynthWave<NM> &w, BandState<RMAX> &S, double4 (*f)[RMAX], int c,
                                           int slot) {
     const bool more = R < RMAX && R < w.nb;
@@ -251,6 +255,16 @@ __device__ __forceinline__ void synth_run(const SynthWave<NM> &w, BandState<RMAX
             if (has_next) next.load(w, c + kStage);
             if constexpr (R < RMAX)
                 if (more && c + kStage >= cend) load();
+            if constexpr (RELOAD)
+                if (((c - w.l0) & (w.a.seg - 1)) == 0) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const LegBand b = w.bands[r];
+                        if (c > band_enter(b, w.la))
+                            band_load<RMAX, SPIN>(w.a, r, band_ring(b, w.lane),
+                                                  band_state(b, c, w.l0, w.a.seg, w.lane), S);
+                    }
+                }
             synth_chunk<R, RMAX, NM, SPIN>(S, f, w.buf[slot], min(kStage, (w.lb - c + 3) & ~3));
             if (has_next) next.store(w.buf[slot ^ 1], w.lane);
             __syncthreads();
@@ -258,12 +272,12 @@ __device__ __forceinline__ void synth_run(const SynthWave<NM> &w, BandState<RMAX
         }
     }
     if constexpr (R < RMAX) {
-        if (c < w.lb) synth_run<R + 1, RMAX, NM, SPIN>(w, S, f, c, slot);
+        if (c < w.lb) synth_run<R + 1, RMAX, NM, SPIN, RELOAD>(w, S, f, c, slot);
     }
 }
 
 // Maps NM blockIdx.y .. + NM - 1 share the recurrence.
-template <int RMAX, int NM, bool SPIN>
+template <int RMAX, int NM, bool SPIN, bool RELOAD = false>
 __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
     __shared__ SynthChunk<NM> buf[2];
     const LegArgs &a = A.a;
@@ -291,7 +305,7 @@ __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
         first.store(buf[0], lane);
     }
     __syncthreads();
-    synth_run<0, RMAX, NM, SPIN>(w, S, f, c, 0);
+    synth_run<0, RMAX, NM, SPIN, RELOAD>(w, S, f, c, 0);
 
     const double sgn_neg = (s & 1) ? 1.0 : -1.0;  // -(-1)^s
     const int64_t op = (int64_t)(a.mmax + m) * a.nring, om = (int64_t)(a.mmax - m) * a.nring;
@@ -690,9 +704,12 @@ __global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *ban
 // at the band's start bs and at every segment start l0 + k seg above it (in
 // blocks of 64 from blk).  The values are stored in the double range: a value
 // below 2^-960 there (a ring far inside its band, or the weaker sign at high
-// spin) would lose digits; *lost counts the rings in which such a value grows
-// past the start threshold before the next stored state (the plan then takes
-// shorter segments).
+// spin) would lose digits.  lost[0] counts the rings in which such a value grows
+// past the start threshold before the next stored state: the adjoint's items,
+// which run from one stored state to the next, then need shorter segments.
+// lost[1] counts those in which it does so at any later degree: the items of the
+// synthesis run over several stored states, up to lmax (the plain list), and
+// then have to take them in on the way.
 template <bool SPIN>
 __global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double2 *st_p, double2 *st_m,
                                                    int32_t *lost) {
@@ -711,7 +728,8 @@ __global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double
     }
     const double4 *T4 = a.coef + (int64_t)m * (2 * lmax + 1 - m) / 2;
     const int lsteps = lmax - l0;
-    bool lp = false, lm = false, bad = false;
+    bool lp = false, lm = false, bad = false;       // since the last stored state
+    bool anyp = false, anym = false, late = false;  // since any
     // l advances in steps of 32 between the points that may store (bs and the
     // segment starts are multiples of 32 from l0); seg is a multiple of 64
     int64_t q = (int64_t)w.blk * 64 + lane;
@@ -725,19 +743,25 @@ __global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double
                 st_m[q] = make_double2(vm, ldexp(ump, kScaleStep * km));
                 lm = um != 0.0 && fabs(vm) < low;
             }
+            anyp |= lp;
+            anym |= lm;
             q += 64;
         }
-        if (c > w.bs && c - l0 >= klast * a.seg && !(lp || lm)) break;
+        if (c > w.bs && c - l0 >= klast * a.seg && !(anyp || anym)) break;
         const int n = min(kStage, lmax + 1 - c);
 #pragma unroll 8
         for (int t = 0; t < n; ++t) {
             const double4 f = T4[c + t];
-            bad |= lp && kp == 0 && fabs(f.w * up) >= thr;
+            const bool on = kp == 0 && fabs(f.w * up) >= thr;
+            bad |= lp && on;
+            late |= anyp && on;
             double v = fma(fma(f.x, y, f.y), up, -upp);
             upp = up;
             up = v;
             if (SPIN) {
-                bad |= lm && km == 0 && fabs(f.w * um) >= thr;
+                const bool om = km == 0 && fabs(f.w * um) >= thr;
+                bad |= lm && om;
+                late |= anym && om;
                 v = fma(fma(f.x, y, f.z), um, -ump);
                 ump = um;
                 um = v;
@@ -749,6 +773,7 @@ __global__ __launch_bounds__(64) void k_leg_states(LegArgs a, int nbands, double
         }
     }
     if (bad) atomicAdd(lost, 1);
+    if (late) atomicAdd(lost + 1, 1);
 }
 
 static LegArgs leg_args(const psht_plan_s &p, const void *alm_in, void *alm_out, void *F, const MapBatch &mb) {
@@ -833,6 +858,15 @@ static hipError_t leg_synth_list(const psht_plan_s &p, SynthArgs &A, const Synth
     if (nitems == 0) return hipSuccess;
     A.items = items;
     A.nitems = nitems;
+    if (p.syn_reload) {
+        // one kernel for such plans (lists of at most two bands, one map per wave)
+        const dim3 grid(nitems, A.a.nmaps), block(64);
+        if (p.g.spin)
+            hipLaunchKernelGGL((k_leg_synth<kSynthReloadBands, 1, true, true>), grid, block, 0, st, A);
+        else
+            hipLaunchKernelGGL((k_leg_synth<kSynthReloadBands, 1, false, true>), grid, block, 0, st, A);
+        return hipGetLastError();
+    }
     if (R == 4) return leg_synth_maps<4>(A, p.g.spin, st);
     if (R == 2) return leg_synth_maps<2>(A, p.g.spin, st);
     return leg_synth_maps<1>(A, p.g.spin, st);

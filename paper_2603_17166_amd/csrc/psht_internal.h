@@ -166,6 +166,7 @@ struct psht_plan_s {
     int n_syn_items = 0, syn_r = 2;
     int syn_seg = 0;    // 0: not segmented
     int syn_parts = 0;  // partial copies of F (segments beyond the first of the longest order)
+    bool syn_reload = false;  // the synthesis takes the stored states in along an item (see k_leg_states)
     // the list of calls with three or more maps (multi_seg = 0: the plain one)
     psht::SynthItem *d_multi_items = nullptr;
     int n_multi_items = 0, multi_r = 2, multi_seg = 0;
@@ -218,9 +219,10 @@ hipError_t launch_leg_adjoint(const psht_plan_s &p, const void *F, void *alm, co
                               hipStream_t st);
 constexpr int kAdjMaxWaves = 4;  // waves per workgroup of the adjoint
 constexpr int kAdjMaxBands = 8;  // bands per wave of the adjoint
+constexpr int kSynthReloadBands = 2;  // bands per wave of the synthesis of plans with syn_reload
 // Plan time: start degrees of the bands, then the states p.d_bands start from
-// (*lost counts states that do not fit the
-// double range although they matter later, see k_leg_states).
+// (lost[0], lost[1] count states that do not fit the double range although they
+// matter before the next one or at any later degree, see k_leg_states).
 hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
                              hipStream_t st);
 hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st);
