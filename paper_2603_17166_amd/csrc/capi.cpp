@@ -16,6 +16,7 @@
 
 #include "leg_common.h"
 #include "psht_internal.h"
+#include "rot_factor.h"
 
 namespace {
 
@@ -853,7 +854,8 @@ psht_status psht_rotate_alm(int lmax, int ncomp, double alpha, double beta, doub
     const char *a = (const char *)alm_in, *b = (const char *)alm_out;
     if (a < b + bytes && b < a + bytes) return fail(PSHT_ERR_ARG, "alm_in and alm_out overlap");
     if (ws_bytes < need) return fail(PSHT_ERR_WORKSPACE, "workspace smaller than psht_rotate_alm_workspace");
-    // log2(n!) for n = 0..2 lmax, per (device, lmax), kept for the process lifetime
+    // log2(n!) for n = 0..2 lmax, then W(n) for n = 0..lmax (rot_factor.h), per
+    // (device, lmax), kept for the process lifetime
     static std::mutex mu;
     static std::map<std::pair<int, int>, double2 *> tables;
     double2 *lf = nullptr;
@@ -872,13 +874,16 @@ psht_status psht_rotate_alm(int lmax, int ncomp, double alpha, double beta, doub
                 h[n].x = (double)v;
                 h[n].y = (double)(v - (long double)h[n].x);
             }
+            std::vector<double2> w;
+            psht::rot_w_table(lmax, w);
+            h.insert(h.end(), w.begin(), w.end());
             void *d = nullptr;
             hipError_t e = hipMalloc(&d, h.size() * sizeof(double2));
-            if (e != hipSuccess) return device_fail(e, "log-factorial table");
+            if (e != hipSuccess) return device_fail(e, "rotation tables");
             e = hipMemcpy(d, h.data(), h.size() * sizeof(double2), hipMemcpyHostToDevice);
             if (e != hipSuccess) {
                 (void)hipFree(d);
-                return device_fail(e, "log-factorial table");
+                return device_fail(e, "rotation tables");
             }
             tables[key] = (double2 *)d;
             lf = (double2 *)d;
@@ -886,7 +891,7 @@ psht_status psht_rotate_alm(int lmax, int ncomp, double alpha, double beta, doub
             return fail(PSHT_ERR_NOMEM, "host allocation failed");
         }
     }
-    hipError_t e = psht::launch_rotate_alm(lmax, ncomp, alpha, beta, gamma, alm_in, alm_out, workspace, lf,
+    hipError_t e = psht::launch_rotate_alm(lmax, ncomp, alpha, beta, gamma, alm_in, alm_out, workspace, lf, lf + 2 * (size_t)lmax + 1,
                                            static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? PSHT_OK : device_fail(e, "rotation kernels");
 }

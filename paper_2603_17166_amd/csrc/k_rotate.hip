@@ -24,12 +24,14 @@
 // h_{l+1} h_l = l + 1 (h_0 = 1), the three-term recurrence becomes
 //   y_{l+1} = G_l(m) G_l(m') (cos beta - m m' / (l (l + 1))) y_l - y_{l-1},
 //   G_l(x) = sqrt(2 l + 1) h_l c_l(x)^2,
-// three multiply-adds a step where the plain form takes six and a square root
-// and a division per column.  c^2 and h are ratios of double factorials,
-// (2n-1)!! / (2n)!! = W(n):
-//   l - x = 2 n:  c_l(x)^2 = W(n) W(x + n) / W(x);  otherwise the reciprocal of
-//   that at l - 1, over l^2 - x^2;   h_{2n} = 1 / W(n),  h_{2n+1} = (2 n + 1) W(n),
-// taken from log2(n!) in double-double, so no product over l is accumulated.
+// a few multiply-adds a step where the plain form takes six and a square root
+// and a division per column.  G is rounded correctly (rot_factor.h), and m / (l (l +
+// 1)) and G_l(m) G_l(m') once each before they are used: the recurrence is then at
+// least as accurate as the plain form (largest error of d^l against 128 bits over
+// 100 to 300 columns, plain / this, in 1e-15: beta 1.1, lmax 256 0.5 / 0.7, 1024
+// 1.4 / 0.7, 4096 1.0 / 1.2; beta 0.1, lmax 1024 13 / 10, 4096 14 / 16; root mean
+// square over the columns 3 to 25 % below).  With G from log2(n!) it was 5.6 at
+// beta 1.1, lmax 4096.
 //
 // Bound by the vector instructions (12 FP64 ones per degree, order and pair of
 // signs, as many again for broadcasts, sums and the flush: 62 % of the busy
@@ -50,6 +52,7 @@
 #include "lane_ops.h"
 #include "leg_common.h"
 #include "psht_internal.h"
+#include "rot_factor.h"
 
 namespace psht {
 
@@ -86,45 +89,18 @@ struct RotArgs {
     double *G;            // [lmax + 1][lmax + 1]: G_l(x), zero for x > l
     double *out;          // output [nc][nalm] complex, accumulated
     const double2 *lf;    // log2(n!) as double-double, n = 0..2 lmax
+    const double2 *w;     // W(n) as double-double, n = 0..lmax (rot_factor.h)
     int lmax;
     int64_t nalm;
     double alpha, gamma, cb, hc, hs;  // cos beta, cos(beta/2), sin(beta/2)
 };
-
-// log2 W(n), W(n) = (2n)! / (4^n n!^2)
-__device__ inline double2 rot_log_w(const double2 *lf, int n) {
-    const double2 f = lf[n], d = dd_sub(dd_sub(lf[2 * n], f), f);
-    return dd_sub(d, make_double2(2.0 * n, 0.0));
-}
-
-__device__ inline double rot_g(const double2 *lf, int l, int x) {
-    const int n = (l - x) / 2;
-    double2 e = dd_sub(rot_log_w(lf, x), rot_log_w(lf, x + n));
-    e = dd_sub(e, rot_log_w(lf, n));  // -log2 of the even-step c^2
-    double f = 1.0;
-    if ((l - x) & 1) {
-        f = 1.0 / ((double)(l - x) * (double)(l + x));
-    } else {
-        e.x = -e.x;
-        e.y = -e.y;
-    }
-    const double2 w = rot_log_w(lf, l / 2);
-    if (l & 1) {
-        e = dd_sub(e, make_double2(-w.x, -w.y));
-        f *= l;
-    } else {
-        e = dd_sub(e, w);
-    }
-    const double ei = floor(e.x);
-    return sqrt(2.0 * l + 1.0) * f * ldexp(exp2((e.x - ei) + e.y), (int)ei);
-}
 
 template <int NC> __global__ __launch_bounds__(256) void k_rot_prep(RotArgs A) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     const int l = blockIdx.y;
     if (k > A.lmax) return;
     const int64_t row = (int64_t)l * (A.lmax + 1) + k;
-    const double g = k <= l ? rot_g(A.lf, l, k) : 0.0;
+    const double g = k <= l ? rot_g(A.w, l, k) : 0.0;
     const double2 e = phase_neg(k, A.gamma);
     const double sc = sqrt(g / (2.0 * l + 1.0));  // (d b) / (y b') = sqrt(G_l(m)) sc
     A.G[row] = g;
@@ -235,21 +211,19 @@ struct RotWave {
 // Degrees lb .. lb + nsteps - 1.  MODE 2: every state has started and has scale 0.
 // MODE 1: any.  MODE 3: all started, some scaled.  MODE 0: all started, none
 // contributes (scaled, or zero): recurrence only.
-// uni, gms, rls: this wavefront's uniform rows, G_l(m) and 1 / (l (l + 1)) of
+// uni, gms, qms: this wavefront's uniform rows, G_l(m) and m / (l (l + 1)) of
 // the chunk.
 template <int NC, int MODE>
 __device__ inline void rot_steps(RotWave &w, double *acc, int acc_stride, const double *uni, int uni_stride,
-                                 const double *gms, const double *rls, int lb, int nsteps, int m, int kw, int lane, double cb) {
+                                 const double *gms, const double *qms, int lb, int nsteps, int m, int kw, int lane, double cb) {
     typedef RotRow<NC> Row;
-    const double dm = m;
 #pragma unroll 1
     for (int u = 0; u < nsteps; ++u) {
         const int l = lb + u;
         double x[Row::size / 16];
 #pragma unroll
         for (int i = 0; i < Row::size / 16; ++i) x[i] = uni[u * uni_stride + 16 * i + (lane & 15)];
-        const double gm = gms[u * 64 + lane];
-        const double tc = gm * cb, tq = gm * (dm * rls[u]);
+        const double gm = gms[u * 64 + lane], qm = qms[u * 64 + lane];
         double re[NC], im[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) re[c] = im[c] = 0.0;
@@ -271,7 +245,8 @@ __device__ inline void rot_steps(RotWave &w, double *acc, int acc_stride, const 
                     im[c] = fma(d, row_bcast<(i + 1) % 16>(x[i / 16]), im[c]);
                 });
             }
-            const double tp = fma(-tq, (double)k, tc) * g, tm = fma(tq, (double)k, tc) * g;
+            const double gg = gm * g;
+            const double tp = fma(-qm, (double)k, cb) * gg, tm = fma(qm, (double)k, cb) * gg;
             const double np = fma(tp, w.yp[p], -w.ypp[p]), nm = fma(tm, w.ym[p], -w.ymp[p]);
             // a state that has not started keeps its seed, with a previous value of zero
             w.ypp[p] = on ? w.yp[p] : 0.0;
@@ -297,7 +272,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
     __shared__ double acc[kRotSteps * kStride];
     __shared__ double uni[kRotSteps * kUni];
     __shared__ double gms[kRotSteps * 64], sqg[2][kRotSteps * 64];  // G_l(m); its root, read by the flush while the next is stored
-    __shared__ double rls[2][kRotSteps];  // 1 / (l (l + 1))
+    __shared__ double qms[kRotSteps * 64];  // m / (l (l + 1))
     __shared__ double2 phase[64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -340,7 +315,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
     // while the chunk before it is computed: one degree at a time, every step
     // waited for memory (1.8 us a step).
     constexpr int kNU = (kRotSteps * kUni + kThreads - 1) / kThreads, kNG = kRotSteps * 64 / kThreads;
-    double un[kNU], gn[kNG];
+    double un[kNU], gn[kNG], qn[kNG];
     const int k0 = blockIdx.y * kRotCols;
     auto fetch = [&](int lb) {
 #pragma unroll
@@ -357,22 +332,25 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
 #pragma unroll
         for (int q = 0; q < kNG; ++q) {
             const int i = tid + q * kThreads;
-            gn[q] = A.G[(int64_t)min(lb + i / 64, lmax) * n + min(m0 + i % 64, lmax)];
+            const int l = lb + i / 64;
+            gn[q] = A.G[(int64_t)min(l, lmax) * n + min(m0 + i % 64, lmax)];
+            qn[q] = l ? (double)(m0 + i % 64) / ((double)l * (double)(l + 1)) : 0.0;
         }
     };
-    auto store = [&](int buf, int lb) {
+    auto store = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < kNU; ++q)
             if (tid + q * kThreads < kRotSteps * kUni) uni[tid + q * kThreads] = un[q];
 #pragma unroll
         for (int q = 0; q < kNG; ++q) {
-            gms[tid + q * kThreads] = gn[q];
-            sqg[buf][tid + q * kThreads] = sqrt(gn[q]);
+            const int i = tid + q * kThreads;
+            gms[i] = gn[q];
+            sqg[buf][i] = sqrt(gn[q]);
+            qms[i] = qn[q];
         }
-        if (tid < kRotSteps) rls[buf][tid] = lb + tid ? 1.0 / ((double)(lb + tid) * (double)(lb + tid + 1)) : 0.0;
     };
     fetch(first);
-    store((first / kRotSteps) & 1, first);
+    store((first / kRotSteps) & 1);
     __syncthreads();
 
     const int started = max(min(m0 + 63, lmax), min(kw + kRotPairs - 1, lmax));  // the last first degree of the wavefront
@@ -392,7 +370,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
             }
             const bool mixed = lb < started || __any(scaled);
             auto steps = [&](auto mode) {
-                rot_steps<NC, decltype(mode)::value>(w, acc, kStride, uni + wave * Row::size, kUni, gms, rls[cur], lb,
+                rot_steps<NC, decltype(mode)::value>(w, acc, kStride, uni + wave * Row::size, kUni, gms, qms, lb,
                                                      nsteps, m, kw, lane, A.cb);
             };
             if (!mixed) steps(std::integral_constant<int, 2>());
@@ -427,7 +405,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
                               (pr * re + pi * im) * sc);
             }
         }
-        store(cur ^ 1, lb + kRotSteps);
+        store(cur ^ 1);
         rot_barrier();
     }
 }
@@ -476,7 +454,7 @@ __global__ __launch_bounds__(256) void k_spin_phase(int64_t n, double ks, const 
 }
 
 hipError_t launch_rotate_alm(int lmax, int nc, double alpha, double beta, double gamma, const void *alm_in,
-                             void *alm_out, void *ws, const double2 *lf, hipStream_t st) {
+                             void *alm_out, void *ws, const double2 *lf, const double2 *w, hipStream_t st) {
     RotArgs A;
     A.alm = (const double2 *)alm_in;
     // B and G: (nc 16 + 8)(lmax + 1)^2 bytes, within the workspace's nc 16 (lmax + 1)(2 lmax + 1) from lmax = 1 on
@@ -484,6 +462,7 @@ hipError_t launch_rotate_alm(int lmax, int nc, double alpha, double beta, double
     A.G = A.B + 2 * (int64_t)nc * (lmax + 1) * (lmax + 1);
     A.out = (double *)alm_out;
     A.lf = lf;
+    A.w = w;
     A.lmax = lmax;
     A.nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
     A.alpha = alpha;

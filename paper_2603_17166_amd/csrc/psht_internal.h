@@ -242,9 +242,10 @@ struct RotMatrix {
     double r[3][3];
 };
 // Coefficients: workspace ws of nc (lmax + 1)(2 lmax + 1) complex doubles; lf:
-// device table of log2(n!) as double-double, n = 0..2 lmax.
+// device table of log2(n!) as double-double, n = 0..2 lmax; w: of W(n), n = 0..lmax
+// (rot_factor.h).
 hipError_t launch_rotate_alm(int lmax, int nc, double alpha, double beta, double gamma, const void *alm_in,
-                             void *alm_out, void *ws, const double2 *lf, hipStream_t st);
+                             void *alm_out, void *ws, const double2 *lf, const double2 *w, hipStream_t st);
 hipError_t launch_rotate_points(int64_t n, const RotMatrix &R, const double *theta, const double *phi,
                                 double *theta_out, double *phi_out, double *psi_out, hipStream_t st);
 hipError_t launch_spin_phase(int64_t n, double ks, int fp32, const double *psi, void *map, hipStream_t st);
