@@ -33,14 +33,14 @@
 // square over the columns 3 to 25 % below).  With G from log2(n!) it was 5.6 at
 // beta 1.1, lmax 4096.
 //
-// Bound by the vector instructions (12 FP64 ones per degree, order and pair of
+// Bound by the vector instructions (13 FP64 ones per degree, order and pair of
 // signs, as many again for broadcasts, sums and the flush: 62 % of the busy
 // cycles) and by the atomics (without them 0.74 ms of the 1.6 ms that separate
 // atomics for Re and Im took at lmax 1024; 128 consecutive bytes per order and
 // flush: 0.97 ms).  us per call, before (8 orders x 128 columns per wavefront,
-// summed over lanes at every degree) / now: lmax 64, two components 137 / 60;
-// lmax 256, one component 355 / 138; lmax 1024, two components 2031 / 891; lmax
-// 2048, two components 9218 / 5630.  Eight wavefronts per workgroup: 800 at lmax
+// summed over lanes at every degree) / now: lmax 64, two components 137 / 63;
+// lmax 256, one component 355 / 136; lmax 1024, two components 2031 / 866; lmax
+// 2048, two components 9218 / 5860.  Eight wavefronts per workgroup: 800 at lmax
 // 1024, but 76, 172 and 6220 at the other sizes.
 // k_rot_points, k_spin_phase  points and the spin basis angle.
 #include <hip/hip_runtime.h>
@@ -315,7 +315,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
     // while the chunk before it is computed: one degree at a time, every step
     // waited for memory (1.8 us a step).
     constexpr int kNU = (kRotSteps * kUni + kThreads - 1) / kThreads, kNG = kRotSteps * 64 / kThreads;
-    double un[kNU], gn[kNG], qn[kNG];
+    double un[kNU], gn[kNG];
     const int k0 = blockIdx.y * kRotCols;
     auto fetch = [&](int lb) {
 #pragma unroll
@@ -332,25 +332,23 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
 #pragma unroll
         for (int q = 0; q < kNG; ++q) {
             const int i = tid + q * kThreads;
-            const int l = lb + i / 64;
-            gn[q] = A.G[(int64_t)min(l, lmax) * n + min(m0 + i % 64, lmax)];
-            qn[q] = l ? (double)(m0 + i % 64) / ((double)l * (double)(l + 1)) : 0.0;
+            gn[q] = A.G[(int64_t)min(lb + i / 64, lmax) * n + min(m0 + i % 64, lmax)];
         }
     };
-    auto store = [&](int buf) {
+    auto store = [&](int buf, int lb) {
 #pragma unroll
         for (int q = 0; q < kNU; ++q)
             if (tid + q * kThreads < kRotSteps * kUni) uni[tid + q * kThreads] = un[q];
 #pragma unroll
         for (int q = 0; q < kNG; ++q) {
-            const int i = tid + q * kThreads;
+            const int i = tid + q * kThreads, l = lb + i / 64;
             gms[i] = gn[q];
             sqg[buf][i] = sqrt(gn[q]);
-            qms[i] = qn[q];
+            qms[i] = l ? (double)(m0 + i % 64) / ((double)l * (double)(l + 1)) : 0.0;
         }
     };
     fetch(first);
-    store((first / kRotSteps) & 1);
+    store((first / kRotSteps) & 1, first);
     __syncthreads();
 
     const int started = max(min(m0 + 63, lmax), min(kw + kRotPairs - 1, lmax));  // the last first degree of the wavefront
@@ -405,7 +403,7 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
                               (pr * re + pi * im) * sc);
             }
         }
-        store(cur ^ 1);
+        store(cur ^ 1, lb + kRotSteps);
         rot_barrier();
     }
 }
