@@ -248,21 +248,27 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     }
     orders[M + 1] = psht::LegOrder{-1, (int32_t)geo.size()};
     const int nbands = (int)geo.size();
-    std::vector<int32_t> bs(nbands);
-    ScopedDevFree d_init, d_lost;
+    std::vector<int32_t> bs(nbands), live(nbands);
+    ScopedDevFree d_init, d_live, d_lost;
     hipError_t e = hipMalloc(&d_init.p, sizeof(psht::LegBand) * (size_t)std::max(nbands, 1));
+    if (e == hipSuccess) e = hipMalloc(&d_live.p, sizeof(int32_t) * (size_t)std::max(nbands, 1));
     if (e == hipSuccess) e = hipMalloc(&d_lost.p, 2 * sizeof(int32_t));
     if (e != hipSuccess) return device(e, "Legendre bands");
     auto *init = static_cast<psht::LegBand *>(d_init.p);
+    auto *d_lv = static_cast<int32_t *>(d_live.p);
     if (!dalloc(p, p.d_band_bs, nbands) || !upload(p, p.d_orders, orders, st)) return nomem("Legendre bands");
     if (nbands > 0) {
         e = hipMemcpy(init, geo.data(), sizeof(geo[0]) * nbands, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = psht::launch_leg_starts(p, init, nbands, p.d_band_bs, st);
+        if (e == hipSuccess) e = psht::launch_leg_starts(p, init, nbands, p.d_band_bs, d_lv, st);
         if (e == hipSuccess)
             e = hipMemcpyAsync(bs.data(), p.d_band_bs, sizeof(int32_t) * nbands, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(live.data(), d_lv, sizeof(int32_t) * nbands, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return device(e, "Legendre start degrees");
     }
+    // by order: the first degree at which a ring is in the unscaled range
+    std::vector<int32_t> olive(M + 1, lmax + 1);
+    for (int i = 0; i < nbands; ++i) olive[geo[i].order] = std::min(olive[geo[i].order], live[i]);
     // by start degree within each order
     std::vector<int> by(nbands);
     for (int i = 0; i < nbands; ++i) by[i] = i;
@@ -342,7 +348,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     for (int m = 0; m <= M; ++m) {
         const int l0 = std::max(m, s), b0 = orders[m].band0, nb = orders[m + 1].band0 - b0;
         if (nb == 0) {
-            if (m <= lmax) items.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1}), cost.push_back(0.0);
+            if (m <= lmax) items.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1, 0, 0, 0}), cost.push_back(0.0);
             continue;
         }
         accumulate |= nb > group_max;
@@ -357,7 +363,8 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
                 for (int i = 0; i < n; ++i) c += lb - std::max(la, bands[b0 + q + i].bs);
                 c /= waves;
                 if (n > 0) c += 1.6 * (lb - std::max(la, bands[b0 + q].bs));
-                items.push_back(psht::AdjItem{m, k == 0 ? m : la, lb, b0 + q, n, waves});
+                items.push_back(psht::AdjItem{m, k == 0 ? m : la, lb, b0 + q, n, waves, olive[m], q == 0 ? bands[b0].bs : 0,
+                                              last[m]});
                 cost.push_back(c);
                 rused = std::max(rused, (n + waves - 1) / waves);
             }
@@ -366,7 +373,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     // orders above mmax have no ring: their outputs are zero
     std::vector<psht::AdjItem> zeros;
     if (!accumulate)
-        for (int m = M + 1; m <= lmax; ++m) zeros.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1});
+        for (int m = M + 1; m <= lmax; ++m) zeros.push_back(psht::AdjItem{m, m, lmax + 1, 0, 0, 1, 0, 0, 0});
     // longest first (blocks are issued in order and dealt round-robin to the XCDs)
     auto longest_first = [](auto &list, const std::vector<double> &c) {
         std::vector<int> at(list.size());
@@ -397,7 +404,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
             if (it.waves == 1) put(group, it);
         }
         for (auto *g : {&group, &zgroup})
-            while (!g->empty()) put(*g, psht::AdjItem{0, 0, 0, 0, 0, 1});
+            while (!g->empty()) put(*g, psht::AdjItem{0, 0, 0, 0, 0, 1, 0, 0, 0});
         items.swap(waves);
     }
     p.adj_waves = G;
@@ -411,6 +418,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
         for (int m = x < 0 ? 0 : x; m <= M; m += x < 0 ? 1 : 8) {
             const int l0 = std::max(m, s), b0 = orders[m].band0, nb = orders[m + 1].band0 - b0;
             const int len = seg > 0 ? seg : lmax + 1;
+            const size_t at = list.size();
             for (int q = 0; q < nb; q += R)
                 for (int k = 0; l0 + k * len <= lmax; ++k) {
                     const int la = l0 + k * len, lb = std::min(lmax + 1, la + len);
@@ -419,9 +427,14 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
                     while (n < std::min(R, nb - q) && bands[b0 + q + n].bs < lb)
                         w += lb - std::max(la, bands[b0 + q + n++].bs);
                     if (n == 0) continue;
-                    list.push_back(psht::SynthItem{m, la, lb, b0 + q, n, k});
+                    list.push_back(psht::SynthItem{m, la, lb, b0 + q, n, k, 0, 0});
                     c.push_back(w + 0.3 * (lb - std::max(la, bands[b0 + q].bs)));
                 }
+            if (list.size() == at) continue;
+            const size_t least = std::min_element(c.begin() + at, c.end()) - c.begin();
+            list[least].live = olive[m];
+            list[least].start = bands[b0].bs;
+            c[least] += 0.2 * (bands[b0].bs - olive[m]);
         }
     };
     const int rmax_synth = p.syn_reload ? psht::kSynthReloadBands : 4;
@@ -461,7 +474,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     }
     for (size_t i = 0; i < most; ++i)
         for (int x = 0; x < 8; ++x)
-            plain.push_back(i < per[x].size() ? per[x][i] : psht::SynthItem{0, 0, 0, 0, 0, 0});
+            plain.push_back(i < per[x].size() ? per[x][i] : psht::SynthItem{0, 0, 0, 0, 0, 0, 0, 0});
     p.n_leg_items = (int)plain.size();
     if (!upload(p, p.d_leg_items, plain, st)) return nomem("uploading the synthesis work list");
     return true;

@@ -18,7 +18,9 @@
 // the lambda of a ring fall off faster than exponentially towards l = m, so a
 // band starts at the first degree (on a grid of 32) at which any of its rings
 // reaches 2^-64 (kLegStartExp): the terms left out lie below the rounding of the
-// sums.  The recurrence of each band starts from a state stored at plan time
+// sums.  (Values that are not finite are looked for among those terms and put
+// into the results, from the degree on at which a ring of the order reaches
+// 2^-312: coefficients by the synthesis, ring values by the adjoint.)  The recurrence of each band starts from a state stored at plan time
 // (mu_l, mu_{l-1}; in the double range, see k_leg_states), so the kernels carry
 // no exponents.  (At spins in the hundreds the weaker sign of a ring can lie below
 // the double range at that degree and matter later: such plans take every band's
@@ -276,6 +278,35 @@ __device__ __forceinline__ void synth_run(const SynthWave<NM> &w, BandState<RMAX
     }
 }
 
+// Whether a coefficient combination of the degrees [from, to) is not finite, by
+// map (bit k), in every lane: two rounds of loads in flight.
+template <int NM> __device__ inline unsigned synth_non_finite(const SynthWave<NM> &w, int from, int to) {
+    bool bad[NM] = {};
+    for (int l0 = from; l0 < to; l0 += 128) {
+        double4 q[2][NM];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < NM; ++k) {
+                const int l = min(l0 + 64 * i + w.lane, to - 1);
+                const int map = min(w.map0 + k, w.a.nmaps - 1);
+                const double2 *g = reinterpret_cast<const double2 *>(w.a.alm_in + map * w.a.alm_stride);
+                q[i][k] = synth_combo(g, g + w.a.nalm, 1.0, w.base + l, w.m, 1.0);
+            }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < NM; ++k) {
+                const double4 v = q[i][k];
+                bad[k] |= !(isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w));
+            }
+    }
+    unsigned mask = 0;
+#pragma unroll
+    for (int k = 0; k < NM; ++k) mask |= __any(bad[k]) ? 1u << k : 0u;
+    return mask;
+}
+
 // Maps NM blockIdx.y .. + NM - 1 share the recurrence.
 template <int RMAX, int NM, bool SPIN, bool RELOAD = false>
 __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
@@ -299,9 +330,13 @@ __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
         for (int k = 0; k < NM; ++k) f[k][r] = make_double4(0.0, 0.0, 0.0, 0.0);
     }
     const int c = band_enter(bands[0], it.la);
+    unsigned poison = 0;
     {
         SynthStage<NM> first;
         first.load(w, c);
+        // the terms that the order leaves out, in one of its items (a value that is
+        // not finite in one ring spreads to the whole map)
+        if (it.live < it.start) poison = synth_non_finite<NM>(w, it.live, it.start);
         first.store(buf[0], lane);
     }
     __syncthreads();
@@ -320,6 +355,7 @@ __global__ __launch_bounds__(64) void k_leg_synth(SynthArgs A) {
             const bool first = b.bs >= it.la;  // the band starts in this segment
             double2 *F = reinterpret_cast<double2 *>(a.F + (w.map0 + k) * a.F_stride +
                                                      (first ? 0 : (int64_t)it.part * A.part_stride));
+            if (r == 0 && ((poison >> k) & 1)) f[k][r].x = f[k][r].y = f[k][r].z = f[k][r].w = NAN;
             if (j >= 0) {
                 F[op + j] = make_double2(-f[k][r].x, -f[k][r].y);
                 if (m != 0) F[om + j] = make_double2(sgn_neg * f[k][r].z, sgn_neg * f[k][r].w);
@@ -614,10 +650,10 @@ __device__ __forceinline__ void adj_run(const AdjWave &w, BandState<RMAX> &S, do
 // of one wave each (orders or segments with at most RMAX started bands: more
 // bands per wave, no barriers).
 template <bool SPIN, int RMAX>
-__device__ inline void adj_item(const AdjArgs &A) {
+__device__ inline void adj_item(const AdjArgs &A, int w0) {
     extern __shared__ __align__(16) double2 redbase[];  // per wave: kRed1, then kRed2 of every wave
     const LegArgs &a = A.a;
-    const int wg = blockDim.x >> 6, w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wg = blockDim.x >> 6, lane = threadIdx.x & 63;
     if ((int)blockIdx.x * wg + w0 >= A.nitems) return;
     const AdjItem it = A.items[blockIdx.x * wg + w0];
     const int G = it.waves, wave = G == 1 ? 0 : w0;
@@ -648,18 +684,51 @@ __device__ inline void adj_item(const AdjArgs &A) {
     adj_run<0, RMAX, SPIN>(w, S, fpr, fpi, fmr, fmi, T, Tn, c0);
 }
 
+// The item's outputs in [live, start), whose terms adj_item left out: NaN in place
+// of the zeros it wrote where the order's ring values are not finite (each thread
+// overwrites its own).  After the sums and from the item again, with the lane from
+// mbcnt: what it needs would otherwise be held in registers through them (k_leg_adj8
+// spills).  One ring stands for the order: the transforms before spread a value
+// that is not finite over all of them.
+__device__ inline void adj_non_finite(const AdjArgs &A, int w0) {
+    const LegArgs &a = A.a;
+    const int64_t at = (int64_t)blockIdx.x * (blockDim.x >> 6) + w0;
+    if (at >= A.nitems) return;
+    const AdjItem it = A.items[at];
+    const int from = max(it.live, it.la), to = min(it.start, it.lb);
+    if (from >= to) return;
+    const double2 *F = reinterpret_cast<const double2 *>(a.F + blockIdx.y * a.F_stride) + it.ring;
+    const double2 vp = F[(int64_t)(a.mmax + it.m) * a.nring], vm = F[(int64_t)(a.mmax - it.m) * a.nring];
+    if (isfinite(vp.x) && isfinite(vp.y) && isfinite(vm.x) && isfinite(vm.y)) return;
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    double2 *out = reinterpret_cast<double2 *>(a.alm_out + blockIdx.y * a.alm_stride) +
+                   (int64_t)it.m * (2 * a.lmax + 1 - it.m) / 2;
+    for (int l = it.la + (it.waves > 1 ? 64 * w0 : 0) + lane; l < to; l += 64 * it.waves)
+        if (l >= from) out[l] = out[a.nalm + l] = make_double2(NAN, it.m ? NAN : 0.0);
+}
+
 template <bool SPIN>
-__global__ __launch_bounds__(256, 2) void k_leg_adj8(AdjArgs A) { adj_item<SPIN, 8>(A); }
+__global__ __launch_bounds__(256, 2) void k_leg_adj8(AdjArgs A) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    adj_item<SPIN, 8>(A, wave);
+    adj_non_finite(A, wave);
+}
 template <bool SPIN>
-__global__ __launch_bounds__(256, 2) void k_leg_adj4(AdjArgs A) { adj_item<SPIN, 4>(A); }
+__global__ __launch_bounds__(256, 2) void k_leg_adj4(AdjArgs A) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    adj_item<SPIN, 4>(A, wave);
+    adj_non_finite(A, wave);
+}
 
 // ------------------------------------------------------- starts and states
 
 // Plan time, one wave per band: the degree l0 + 32 i of the chunk in which a
 // ring of the band first has |lambda+-| >= 2^kLegStartExp (at most the last
-// chunk of the order).
+// chunk of the order), and the degree l0 + 8 i from which on one has a value
+// in the unscaled range (at or above 2^-312, or a seed above 2^-600).
 template <bool SPIN>
-__global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *bands, int nbands, int32_t *bs) {
+__global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *bands, int nbands, int32_t *bs,
+                                                   int32_t *live) {
     if ((int)blockIdx.x >= nbands) return;
     const LegBand b = bands[blockIdx.x];
     const int lane = threadIdx.x, m = b.order, s = a.spin, lmax = a.lmax;
@@ -674,9 +743,11 @@ __global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *ban
         leg_seed(a.kmant[m], a.kexp[m], m, s, a.ring_ch[j], a.ring_sh[j], up, kp, um, km);
     }
     const double4 *T4 = a.coef + (int64_t)m * (2 * lmax + 1 - m) / 2;
-    int c = l0;
+    auto unscaled = [&] { return __any(act && (kp == 0 || (SPIN && km == 0))); };
+    int c = l0, from = -1;
     for (; c + kStage <= lmax; c += kStage) {
         bool hit = false;
+        if (from < 0 && unscaled()) from = c;
 #pragma unroll 8
         for (int t = 0; t < kStage; ++t) {
             const double4 f = T4[c + t];
@@ -693,11 +764,15 @@ __global__ __launch_bounds__(64) void k_leg_starts(LegArgs a, const LegBand *ban
             if ((t & 7) == 7) {  // 8 steps grow a value by far less than the headroom above 2^200
                 leg_rescale(up, upp, kp);
                 if (SPIN) leg_rescale(um, ump, km);
+                if (from < 0 && unscaled()) from = c + t + 1;
             }
         }
         if (__any(hit)) break;
     }
-    if (lane == 0) bs[blockIdx.x] = c;
+    if (lane == 0) {
+        bs[blockIdx.x] = c;
+        live[blockIdx.x] = from < 0 || from > c ? c : from;
+    }
 }
 
 // Plan time, one wave per band: stores the state (mu_l, mu_{l-1}) of both signs
@@ -891,12 +966,12 @@ hipError_t launch_leg_synth(const psht_plan_s &p, const void *alm, void *F, bool
     return hipGetLastError();
 }
 
-hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
+hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs, int32_t *live,
                              hipStream_t st) {
     if (nbands == 0) return hipSuccess;
     const LegArgs a = leg_args(p, nullptr, nullptr, nullptr, MapBatch());
-    if (p.g.spin) hipLaunchKernelGGL(k_leg_starts<true>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
-    else hipLaunchKernelGGL(k_leg_starts<false>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs);
+    if (p.g.spin) hipLaunchKernelGGL(k_leg_starts<true>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs, live);
+    else hipLaunchKernelGGL(k_leg_starts<false>, dim3(nbands), dim3(64), 0, st, a, bands, nbands, bs, live);
     return hipGetLastError();
 }
 

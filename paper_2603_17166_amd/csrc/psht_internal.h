@@ -116,16 +116,20 @@ struct LegOrder {
 constexpr int kLegStartExp = -64;
 
 // Work item of the synthesis: degrees [la, lb) of order m for the bands b0 ..
-// b0 + nb - 1 (sorted by start degree); segment number `part` of the order.
+// b0 + nb - 1 (sorted by start degree); segment number `part` of the order.  One
+// item of each order, its shortest, also looks for coefficients that are not
+// finite in the degrees [live, start) before the order's first band starts.
 struct SynthItem {
-    int32_t m, la, lb, b0, nb, part;
+    int32_t m, la, lb, b0, nb, part, live, start;
 };
 // Work item of the adjoint: the outputs l in [la, lb) of order m from the bands
 // b0 .. b0 + nb - 1 (all that start below lb, or one group of them), held by
 // `waves` waves.  nb = 0: the outputs are zero.  One entry per wave of the
-// launch: an item of several waves is repeated.
+// launch: an item of several waves is repeated.  The outputs in [live, start),
+// where start is the order's first band's (no terms are summed there), are NaN if
+// the value of ring `ring` is not finite.
 struct AdjItem {
-    int32_t m, la, lb, b0, nb, waves;
+    int32_t m, la, lb, b0, nb, waves, live, start, ring;
 };
 
 // ------------------------------------------------------------------- plan
@@ -220,10 +224,10 @@ hipError_t launch_leg_adjoint(const psht_plan_s &p, const void *F, void *alm, co
 constexpr int kAdjMaxWaves = 4;  // waves per workgroup of the adjoint
 constexpr int kAdjMaxBands = 8;  // bands per wave of the adjoint
 constexpr int kSynthReloadBands = 2;  // bands per wave of the synthesis of plans with syn_reload
-// Plan time: start degrees of the bands, then the states p.d_bands start from
+// Plan time: start and live degrees of the bands, then the states p.d_bands start from
 // (lost[0], lost[1] count states that do not fit the double range although they
 // matter before the next one or at any later degree, see k_leg_states).
-hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs,
+hipError_t launch_leg_starts(const psht_plan_s &p, const LegBand *bands, int nbands, int32_t *bs, int32_t *live,
                              hipStream_t st);
 hipError_t launch_leg_states(const psht_plan_s &p, int nbands, int32_t *lost, hipStream_t st);
 

@@ -1,0 +1,76 @@
+"""Coefficients and maps that are not finite: they show in the result also where
+their terms lie between the double range's lower part and the start of the
+Legendre bands (2^-64), and nowhere else does anything change."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2603_17166_amd import synthetic as syn
+from paper_2603_17166_amd.plan import Plan, legendre_column, plan_geometry
+
+pytestmark = pytest.mark.gpu
+DEG = math.pi / 180
+# lmax, spin, cap radius (deg), precision: one list of work items each (plain, segmented, several maps)
+CASES = [(96, 2, 12.0, "fp64"), (900, 0, 3.0, "fp64"), (1024, 2, 5.0, "fp32"), (1500, 2, 30.0, "fp64")]
+
+
+def _weak_degree(lmax, spin, info, m):
+    """A degree at which every ring's |lambda+-| of order m lies below 2^-70 and
+    some ring's above 2^-250."""
+    _, th, _, cut = plan_geometry(lmax, spin, info["theta_star"], info["epsilon"],
+                                  "fp32" if info["map_is_fp32"] else "fp64")
+    big = np.zeros(lmax + 1)
+    for j in np.nonzero(cut >= m)[0]:
+        lp, lm = legendre_column(lmax, spin, m, th[j])
+        big = np.maximum(big, np.maximum(np.abs(lp), np.abs(lm)))
+    at = np.nonzero((big < 2.0 ** -70) & (big > 2.0 ** -250))[0]
+    return int(at[len(at) // 2]) if len(at) else None
+
+
+@pytest.mark.parametrize("lmax,spin,rad,prec", CASES)
+def test_non_finite_values_are_seen(lmax, spin, rad, prec):
+    th, ph = syn.uniform_cap(300, rad * DEG, 16000 + lmax)
+    eps = 1e-5 if prec == "fp32" else 1e-10
+    p = Plan(th, ph, lmax, spin, eps, prec)
+    weak = []
+    for m in range(p.info["mmax"], 0, -max(1, p.info["mmax"] // 12)):
+        l = _weak_degree(lmax, spin, p.info, m)
+        if l is not None:
+            weak.append((m, l))
+    print("lmax %d spin %d: weak coefficients %s" % (lmax, spin, weak), flush=True)
+    assert len(weak) >= 2
+    a = torch.as_tensor(syn.gaussian_alm(lmax, spin, 16100)).cuda()
+    three = torch.stack([a, 2 * a, 3 * a])
+    clean = p.synth(three)
+    assert bool(torch.isfinite(torch.view_as_real(clean)).all())
+    for m, l in weak:
+        i = m * (2 * lmax + 1 - m) // 2 + l
+        for bad in (float("nan"), float("inf")):
+            b = a.clone()
+            b[1, i] = complex(0.0, bad)
+            f = p.synth(b)
+            assert not bool(torch.isfinite(torch.view_as_real(f)).any()), (m, l, bad)
+            # one map of several: the others stay as they are
+            t = three.clone()
+            t[1, 0, i] = bad
+            g = p.synth(t)
+            assert not bool(torch.isfinite(torch.view_as_real(g[1])).any())
+            for k in (0, 2):
+                assert float(torch.linalg.norm(g[k] - clean[k]) / torch.linalg.norm(clean[k])) <= (
+                    1e-12 if prec == "fp64" else 1e-6)
+    # adjoint: a map value that is not finite shows in these outputs too
+    f = clean[0].clone()
+    f[7] = float("nan")
+    at = p.adjoint(f)
+    for m, l in weak:
+        assert bool(torch.isnan(torch.view_as_real(at[:, m * (2 * lmax + 1 - m) // 2 + l])).any(dim=1).all())
+    # a finite one leaves them negligible
+    at = p.adjoint(clean[0])
+    assert bool(torch.isfinite(torch.view_as_real(at)).all())
+    top = float(at.abs().max())
+    for m, l in weak:
+        assert float(at[:, m * (2 * lmax + 1 - m) // 2 + l].abs().max()) <= 1e-15 * top
+    p.close()
