@@ -41,6 +41,8 @@ import random
 import time
 from typing import Callable
 
+import numpy as np
+
 OPS = ("synth", "adjoint")
 
 
@@ -386,6 +388,36 @@ def latency_stats(reqs: list, skip: int = 0) -> dict:
 
 # -- device executor ----------------------------------------------------------
 
+def legendre_state_bytes(info: dict, ncu: int = 256) -> int:
+    """Estimate of the recurrence states a plan of these host-side parameters
+    stores: for every order its rings in bands of 64, one state (16 bytes, 32
+    with a spin) per ring at the band's start and at every segment start above
+    it.  The rings of an order are counted by lmax sin(theta) and a margin for
+    the polar cut-off, the segment length follows the plan's balance rule (the
+    longest item at most a third of the mean work of the GPU's wave slots), and
+    the bands are taken to start after a quarter of their degrees.  Against the
+    plans of 18 sizes from lmax 128 to 8192 and caps of 1 to 65 degrees: 1.03 to
+    1.43 times the states stored."""
+    lmax, spin = info["lmax"], info["spin"]
+    theta = 2.0 * info["theta_max"] / info["n2"] * np.arange(info["Lmax"] + 1)
+    x = lmax * np.sin(np.minimum(theta, 0.5 * math.pi))
+    cut = np.maximum.accumulate(np.minimum(lmax, np.floor(x + 14.0 * np.cbrt(x) + spin)))
+    m = np.arange(int(cut[-1]) + 1)
+    rings = len(theta) - np.searchsorted(cut, m)
+    bands = (rings + 63) // 64
+    degrees = bands * (lmax + 1 - np.maximum(m, spin))
+    most, waves = int(rings.max()), 1
+    while waves < 4 and 512 * waves < most:
+        waves *= 2
+    per_wave = -(-min(-(-most // 64), 8 * waves) // waves)
+    seg = 64
+    while 2 * seg <= lmax + 1 and 2 * seg * per_wave <= 0.7 * float(degrees.sum()) / (ncu * 8) / 3:
+        seg *= 2
+    states = 64 * (float(bands.sum()) + 0.75 * float(degrees.sum()) / seg)
+    return int(1.1 * states) * (32 if spin else 16)
+
+
+
 class TorchExecutor:
     """Runs batches through the library on `n_slots` HIP streams of `device`
     (default priority).  Patches are registered as host or device coordinate
@@ -413,17 +445,15 @@ class TorchExecutor:
     def plan_bytes_estimate(self, key: PlanKey) -> int:
         """Bytes a plan will hold, from the host-side parameters: per point the
         sorted coordinates and permutation (20 B) and the creation scratch
-        (24 B); the adjoint's recurrence states (40 B per ring and segment, at
-        most one segment per 64 degrees); the shared Legendre table; 1 MiB of
-        ring and FFT tables."""
+        (24 B); the Legendre recurrence states; the shared Legendre table;
+        1 MiB of ring and FFT tables and work lists."""
         from .plan import plan_geometry
 
         th, _ = self.patches[key.patch]
         n = int(len(th))
         ts = float(th.max()) if n else 0.0
         info = plan_geometry(key.lmax, key.spin, ts, key.epsilon, key.precision, rings=False)[0]
-        states = (info["Lmax"] + 1) * ((key.lmax + 64) // 64) * 40
-        return n * 44 + states + self.shared_of(key)[1] + (1 << 20)
+        return n * 44 + legendre_state_bytes(info) + self.shared_of(key)[1] + (1 << 20)
 
     def create_plan(self, key: PlanKey):
         from .plan import Plan
@@ -439,12 +469,13 @@ class TorchExecutor:
         plan.close(sync=False)
 
     def cost_estimate(self, plan, op: str) -> float:
-        """Seconds of GPU time of one request on `plan`: its Legendre work at
-        about 25 TFLOP/s (18 FLOP per ring, order and degree) and its NUFFT at
-        about 15 ps (FP32) or 40 ps (FP64) per point, as measured on the served
-        discs; both operations alike."""
-        per_point = 1.5e-11 if plan.info["map_is_fp32"] else 4e-11
-        return plan.info["legendre_triples"] * 18 / 25e12 + plan.npoints * per_point
+        """Seconds of GPU time of one request on `plan`: 35 us of launches and
+        latency, its Legendre work at 45 TFLOP/s (18 FLOP per ring, order and
+        degree) and its NUFFT at 14 ps (FP32) or 45 ps (FP64) per point; fitted
+        to the served discs' requests run alone, where it is 0.4 to 1.4 times
+        the time.  Both operations alike."""
+        per_point = 1.4e-11 if plan.info["map_is_fp32"] else 4.5e-11
+        return 3.5e-5 + plan.info["legendre_triples"] * 18 / 45e12 + plan.npoints * per_point
 
     def footprint(self, plan, op: str, n: int) -> int:
         from .plan import nalm
