@@ -419,13 +419,17 @@ static bool leg_significant(int lmax, int s, int m, ld theta, ld tau, const Degr
 // well above lmax sin(theta) are irrelevant on the ring, Sec. II.A), searched
 // from a guess: the neighbouring ring's cut-off, shifted by the change of
 // lmax sin(theta), lies within a few orders of the boundary, so a handful of
-// tests replace a bisection over [lmax sin(theta), lmax].
+// tests replace a bisection over [lmax sin(theta), lmax].  The significant orders
+// are those around s |cos(theta)|, about sqrt(lmax^2 - s^2) sin(theta) to either
+// side: a narrow band at spins near lmax, which a walk down from above it could
+// step over, so the walk ends at that centre.
 static int ring_cutoff(int lmax, int s, ld theta, ld tau, const DegreeRoots &R, int guess) {
     if (theta == 0) return std::min(s, lmax);
     auto sig = [&](int m) { return leg_significant(lmax, s, m, theta, tau, R); };
     // bracket the boundary by steps doubling away from the guess: lo significant
     // (or -1), hi not (or lmax + 1); then bisect
-    int lo, hi, g = std::max(0, std::min(guess, lmax));
+    const int centre = std::min(lmax, (int)lroundl(s * fabsl(cosl(theta))));
+    int lo, hi, g = std::max(centre, std::min(guess, lmax));
     if (sig(g)) {
         lo = g;
         for (int step = 1;; step *= 2) {
@@ -443,7 +447,7 @@ static int ring_cutoff(int lmax, int s, ld theta, ld tau, const DegreeRoots &R, 
     } else {
         hi = g;
         for (int step = 1;; step *= 2) {
-            const int t = hi - step;
+            const int t = hi > centre ? std::max(centre, hi - step) : hi - step;
             if (t < 0) {
                 lo = -1;
                 break;
