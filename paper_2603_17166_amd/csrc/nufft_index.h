@@ -13,6 +13,7 @@
 #pragma once
 
 #include <cmath>
+#include <cstdint>
 
 #if defined(__HIPCC__)
 #define PSHT_HD __host__ __device__
@@ -78,6 +79,36 @@ PSHT_HD inline void tile_local(const TileGeom &a, double X, double Y, int t, int
 
 PSHT_HD inline bool in_tile(const TileGeom &a, int li, int lj) {
     return li >= 0 && li < a.tile_x && lj >= 0 && lj < a.tile_y;
+}
+
+// Tile shape of a plan: 16 x 32 stencil origins, halved (columns first) down to
+// 8 x 8 for plans of few tiles, so that the points are shared by more workgroups
+//  - as long as there are fewer than 256 tiles, one per CU;
+//  - up to 1024 tiles where the points are dense, that is where the halo cells
+//    that the smaller tiles add (each read once in the interpolation and added
+//    once in the spreading) are at most 0.4 per point.
+// us of spreading and interpolation at 16x32 / 16x16 / 8x16 / 8x8 (FP64, W = 11):
+//   50 x 350 grid rows and columns, 30 000 points:   55.7 / 38.0 / 33.5 / 25.2 (chosen: 8x8)
+//   111 x 840, 300 000 points:                      106.6 / 71.4 / 61.5 / 66.2 (8x16)
+//   111 x 840, 30 000 points:                        34.7 / 29.1 / 28.1 / 36.9 (16x16)
+//   165 x 540, 30 000 points:                        33.6 / 28.7 / 28.2 / 37.0 (16x16)
+//   237 x 810, 30 000 points:                        32.8 / 32.3 / 41.3 / 52.3 (16x32)
+//   328 x 2240, 300 000 points:                      86.4 / 101.5 / 126.5 / 161.2 (16x32)
+// Of 105 such plans (W 4 to 14, 24 to 350 rows, 2000 to 300 000 points) none
+// takes more than 1.07 times the sum of its best shape and 1.02 times that of 16x32;
+// with 1024 tiles for every density the sum was up to 1.5 times that of 16x32.
+inline void tile_shape(int rows_used, int Nphi, int W, int64_t npts, int &tx, int &ty) {
+    auto tiles = [&](int x, int y) { return (int64_t)((rows_used + x - 1) / x) * ((Nphi + y - 1) / y); };
+    auto cells = [&](int x, int y) { return tiles(x, y) * (x + W - 1) * (y + W - 1); };
+    tx = 16;
+    ty = 32;
+    while (tx * ty > 64) {
+        const int64_t n = tiles(tx, ty);
+        const int x = ty > tx ? tx : tx / 2, y = ty > tx ? ty / 2 : ty;
+        if (n >= 1024 || (n >= 256 && (double)(cells(x, y) - cells(tx, ty)) > 0.4 * (double)npts)) break;
+        tx = x;
+        ty = y;
+    }
 }
 
 }  // namespace psht
