@@ -162,28 +162,25 @@ struct ScopedDevFree {
 // of less than 256 degrees are not segmented (the partial-sum launch costs what
 // they gain: lmax 128 cap 10.3 against 9.7 us); longer ones are, from two
 // segments on (lmax 3000, 1000 deg^2: 0.45 -> 0.32 ms; lmax 4096, 1500 deg^2:
-// 1.00 -> 0.97 ms), unless their copies would enlarge the workspace.  The work is counted over all
-// degrees l >= m, in steps of 128 rings, so that the size of the workspace does
-// not depend on where the bands start.  Returns 0 for no segments.
+// 1.00 -> 0.97 ms), unless their copies would enlarge the workspace.  A length of
+// 2048 and more that holds a whole order is halved to give two segments (us of the
+// stage, segments of 1024 or 2048 / none, spin 2: lmax 2000, 45 degrees 300 / 317;
+// lmax 3000, 40 degrees 647 / 672; lmax 4096, 34 degrees 1068 / 1093, but 60 degrees
+// 2530 / 2467 and lmax 6000, 30 degrees 2341 / 2290); shorter ones are not, since
+// orders of up to 1024 degrees lose by two segments (lmax 1000, 60 degrees, 512
+// degrees each 104 / 97).  The work is counted over all degrees l >= m, in steps
+// of 128 rings, so that the size of the workspace does not depend on where the
+// bands start.  Returns 0 for no segments.
 int synth_segment_length(const psht::Geometry &g, int ncu, const std::vector<int> &first, const std::vector<int> &last) {
     const int lmax = g.lmax, s = g.spin, M = g.mmax;
-    double total = 0.0, adj_total = 0.0;
-    int nrmax = 1, G = 1, rmax = 1;
-    for (int m = 0; m <= M; ++m)
-        if (first[m] >= 0) nrmax = std::max(nrmax, last[m] - first[m] + 1);
-    while (G < 4 && 384 * G < nrmax) G *= 2;
+    double total = 0.0;
     for (int m = 0; m <= M; ++m) {
         if (first[m] < 0 || std::max(m, s) > lmax) continue;
         const int steps = lmax + 1 - std::max(m, s), nr = last[m] - first[m] + 1;
         for (int r = nr; r > 0; r -= 128) total += r <= 64 ? 0.5 * steps : steps;
-        const int groups = (nr + 384 * G - 1) / (384 * G), gsize = (nr + groups - 1) / groups;
-        const int R = (gsize + 64 * G - 1) / (64 * G);
-        rmax = std::max(rmax, R);
-        adj_total += (double)steps * R * G;
     }
     const double slots = (double)std::max(ncu, 1) * 4 * 2;
     int S = 64;
-    while (S * 2 <= lmax + 1 && (double)(S * 2) * rmax <= adj_total / slots / 3.0) S *= 2;
     while ((double)S * 2 <= total / slots / 3.0) S *= 2;
     while ((int64_t)33 * S < (int64_t)lmax + 1 - s) S *= 2;
     if (const char *e = getenv("PSHT_SYN_SEG")) {  // tests and tuning runs: a power of two, at least 64; 0 for none
@@ -386,7 +383,7 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     };
     longest_first(items, cost);
     {
-        // one entry per wave: single-wave items fill workgroups of G with their neighbours in cost
+        // one entry per wave: single-wave items fill workgroups of G with their neighbours
         // in cost; the zeros are spread evenly among them, so that their stores run
         // beside the sums (as fills of their own they took 40 of 221 us at lmax
         // 4000 on a 7-degree disc)
@@ -441,8 +438,13 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
     const int rmax_synth = p.syn_reload ? psht::kSynthReloadBands : 4;
     const int fixed = std::min(rmax_synth, psht::leg_bands_per_wave());  // 0: not fixed
     // segmented lists: syn_seg degrees; and for calls of several maps, which fill
-    // the GPU with fewer items, four times as many (fewer copies of F to add; 8
-    // maps at lmax 2048 on a 5-degree disc: 146 -> 115 us) with two bands per wave
+    // the GPU with fewer items, four times as many (fewer copies of F to add) with two
+    // bands per wave.  us of the stage, spin 2, 8 maps, the list of single maps / 1, 2, 4,
+    // 8 times its segments: 5-degree disc at lmax 2048 174 / 151, 121, 118, 139; 10 degrees
+    // 298 / 279, 252, 248, 275; 3 degrees at lmax 4096 346 / 289, 262, 268, 289; 18 degrees
+    // at lmax 3000 1193 / 1128, 1089, 1083, 1132.  Short transforms and few maps would
+    // want fewer (5 degrees at lmax 1024, 8 maps 54 / 49, 48, 61, 94; 3 maps 33 / 30, 36, 49,
+    // 81; 3 degrees at lmax 512, 3 maps 16 / 19, 22, 32, 51).
     p.syn_parts = 0;
     if (p.syn_seg > 0) {
         p.syn_r = fixed ? fixed : rmax_synth;
@@ -697,9 +699,6 @@ psht_status psht_plan_query(psht_plan plan, psht_plan_info *info) {
 
 }  // extern "C"
 
-namespace {
-
-}  // namespace
 
 // Synthesis of nmaps maps with the given workspace (shared by psht_synth,
 // psht_synth_grad and the entry point without allocation).
