@@ -371,9 +371,20 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
                 rot_steps<NC, decltype(mode)::value>(w, acc, kStride, uni + wave * Row::size, kUni, gms, qms, lb,
                                                      nsteps, m, kw, lane, A.cb);
             };
+            // a value of b that is not finite reaches every order of its degree, also
+            // those that nothing else contributes to
+            auto bad_b = [&] {
+                bool bad = false;
+#pragma unroll
+                for (int q = 0; q < kRotSteps * Row::size / 64; ++q) {
+                    const int i = q * 64 + lane;
+                    bad |= !isfinite(uni[i / Row::size * kUni + wave * Row::size + i % Row::size]);
+                }
+                return bad;
+            };
             if (!mixed) steps(std::integral_constant<int, 2>());
             else if (lb < started) steps(std::integral_constant<int, 1>());
-            else if (__any(live)) steps(std::integral_constant<int, 3>());
+            else if (__any(live || bad_b())) steps(std::integral_constant<int, 3>());
             else steps(std::integral_constant<int, 0>());
             if (mixed) {
 #pragma unroll

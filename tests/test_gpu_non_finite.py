@@ -74,3 +74,21 @@ def test_non_finite_values_are_seen(lmax, spin, rad, prec):
     for m, l in weak:
         assert float(at[:, m * (2 * lmax + 1 - m) // 2 + l].abs().max()) <= 1e-15 * top
     p.close()
+
+
+@pytest.mark.parametrize("nc", [1, 2])
+@pytest.mark.parametrize("beta", [0.2, 1.1])
+def test_rotation_of_a_degree_that_is_not_finite(nc, beta):
+    """Every order of the degree, also those whose d^l_{m m'} is negligible, and no other degree."""
+    from paper_2603_17166_amd import rotate as rot
+
+    lmax, l, k = 400, 390, 350
+    m, ls = (torch.as_tensor(x).cuda() for x in syn.alm_m_l(lmax))
+    a = torch.as_tensor(syn.gaussian_alm(lmax, 0, 16200)[:nc].copy()).cuda()
+    for bad in (float("nan"), float("inf")):
+        b = a.clone()
+        b[nc - 1, (ls == l) & (m == k)] = complex(bad, 0.0)
+        got = torch.view_as_real(rot.rotate_alm(b, lmax, 0.3, beta, -0.4))
+        finite = torch.isfinite(got).all(dim=2)
+        assert not bool(finite[nc - 1, ls == l].any())
+        assert bool(finite[nc - 1, ls != l].all()) and bool(finite[: nc - 1].all())
