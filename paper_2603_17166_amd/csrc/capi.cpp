@@ -171,7 +171,8 @@ struct ScopedDevFree {
 // degrees each 104 / 97).  The work is counted over all degrees l >= m, in steps
 // of 128 rings, so that the size of the workspace does not depend on where the
 // bands start.  Returns 0 for no segments.
-int synth_segment_length(const psht::Geometry &g, int ncu, const std::vector<int> &first, const std::vector<int> &last) {
+int synth_segment_length(const psht::Geometry &g, int ncu, const std::vector<int> &first,
+                         const std::vector<int> &last) {
     const int lmax = g.lmax, s = g.spin, M = g.mmax;
     double total = 0.0;
     for (int m = 0; m <= M; ++m) {
@@ -361,8 +362,8 @@ bool build_legendre(psht_plan_s &p, int ncu, hipStream_t st, psht::Error &err) {
                 for (int i = 0; i < n; ++i) c += lb - std::max(la, bands[b0 + q + i].bs);
                 c /= waves;
                 if (n > 0) c += 1.6 * (lb - std::max(la, bands[b0 + q].bs));
-                items.push_back(psht::AdjItem{m, k == 0 ? m : la, lb, b0 + q, n, waves, olive[m], q == 0 ? bands[b0].bs : 0,
-                                              last[m]});
+                items.push_back(psht::AdjItem{m, k == 0 ? m : la, lb, b0 + q, n, waves, olive[m],
+                                              q == 0 ? bands[b0].bs : 0, last[m]});
                 cost.push_back(c);
                 rused = std::max(rused, (n + waves - 1) / waves);
             }
@@ -763,7 +764,8 @@ psht_status adjoint_impl(psht_plan plan, int nmaps, const void *map, void *alm, 
         void *a = static_cast<char *>(alm) + i * alm_bytes;
         hipError_t e = timed(P, PSHT_T_GRID_ZERO, st, [&] { return psht::launch_grid_zero(P, U, mb, st); });
         if (e == hipSuccess) e = timed(P, PSHT_T_SPREAD, st, [&] { return psht::launch_spread(P, m, U, mb, st); });
-        if (e == hipSuccess) e = timed(P, PSHT_T_PHI_ADJ, st, [&] { return psht::launch_phi_adjoint(P, U, V, mb, st); });
+        if (e == hipSuccess)
+            e = timed(P, PSHT_T_PHI_ADJ, st, [&] { return psht::launch_phi_adjoint(P, U, V, mb, st); });
         if (e == hipSuccess)
             e = timed(P, PSHT_T_THETA_ADJ, st, [&] { return psht::launch_theta_adjoint(P, V, F, mb, st); });
         if (e == hipSuccess)
@@ -899,8 +901,8 @@ psht_status psht_rotate_alm(int lmax, int ncomp, double alpha, double beta, doub
             return fail(PSHT_ERR_NOMEM, "host allocation failed");
         }
     }
-    hipError_t e = psht::launch_rotate_alm(lmax, ncomp, alpha, beta, gamma, alm_in, alm_out, workspace, lf, lf + 2 * (size_t)lmax + 1,
-                                           static_cast<hipStream_t>(hip_stream));
+    hipError_t e = psht::launch_rotate_alm(lmax, ncomp, alpha, beta, gamma, alm_in, alm_out, workspace, lf,
+                                           lf + 2 * (size_t)lmax + 1, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? PSHT_OK : device_fail(e, "rotation kernels");
 }
 

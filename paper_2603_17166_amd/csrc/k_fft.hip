@@ -424,7 +424,8 @@ template <typename T, int MAXN> struct ThetaHalves {
 // All of a thread's loads are issued before the first is used (in a plain loop
 // each trip waited for memory); positions past the end reread the last one.
 template <typename T, int MAXN>
-__device__ inline void load_column(typename CT<T>::type *buf, const StageArgs &a, const double2 *Fm, int am, double sig) {
+__device__ inline void load_column(typename CT<T>::type *buf, const StageArgs &a, const double2 *Fm, int am,
+                                   double sig) {
     constexpr int NTHR = fft_threads<T>(MAXN), NQ = (MAXN + NTHR - 1) / NTHR, G = NQ < 4 ? NQ : 4;
     const int L = a.L, N2 = a.N2;
 #pragma unroll 1
@@ -847,7 +848,8 @@ template <typename Fn> static void tier_dispatch(int n, Fn fn) {
 }
 
 template <typename T>
-static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const double2 *F, void *V, hipStream_t st) {
+static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const double2 *F, void *V,
+                               hipStream_t st) {
     typedef typename CT<T>::type C;
     const int n = p.theta_split ? p.g.N2 : p.g.Ntheta;
     const size_t lds = (size_t)n * sizeof(C);
@@ -868,7 +870,8 @@ static hipError_t theta_synth_t(const psht_plan_s &p, const StageArgs &a, int nm
 }
 
 template <typename T>
-static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, double2 *F, hipStream_t st) {
+static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, double2 *F,
+                               hipStream_t st) {
     typedef typename CT<T>::type C;
     const int n = p.theta_split ? p.g.N2 : p.g.Ntheta;
     const size_t lds = (size_t)n * sizeof(C);
@@ -889,7 +892,8 @@ static hipError_t theta_adjoint_t(const psht_plan_s &p, const StageArgs &a, int 
 }
 
 template <typename T>
-static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, void *U, hipStream_t st) {
+static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *V, void *U,
+                               hipStream_t st) {
     typedef typename CT<T>::type C;
     const int nh = p.g.Nphi / p.g.phi_parts;
     const size_t lds = (size_t)nh * sizeof(C);
@@ -905,7 +909,8 @@ static hipError_t phi_synth_t(const psht_plan_s &p, const StageArgs &a, int nmap
 }
 
 template <typename T>
-static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *U, void *V, hipStream_t st) {
+static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nmaps, const void *U, void *V,
+                               hipStream_t st) {
     typedef typename CT<T>::type C;
     const int nh = p.g.Nphi / p.g.phi_parts;
     const size_t lds = (size_t)nh * sizeof(C);
@@ -923,7 +928,8 @@ static hipError_t phi_adjoint_t(const psht_plan_s &p, const StageArgs &a, int nm
 hipError_t launch_theta_synth(const psht_plan_s &p, const void *F, void *V, const MapBatch &mb, hipStream_t st) {
     const StageArgs a = stage_args(p, mb);
     const double2 *F2 = static_cast<const double2 *>(F);
-    const hipError_t e = p.g.fp32 ? theta_synth_t<float>(p, a, mb.n, F2, V, st) : theta_synth_t<double>(p, a, mb.n, F2, V, st);
+    const hipError_t e =
+        p.g.fp32 ? theta_synth_t<float>(p, a, mb.n, F2, V, st) : theta_synth_t<double>(p, a, mb.n, F2, V, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
@@ -931,21 +937,24 @@ hipError_t launch_theta_synth(const psht_plan_s &p, const void *F, void *V, cons
 hipError_t launch_theta_adjoint(const psht_plan_s &p, const void *V, void *F, const MapBatch &mb, hipStream_t st) {
     const StageArgs a = stage_args(p, mb);
     double2 *F2 = static_cast<double2 *>(F);
-    const hipError_t e = p.g.fp32 ? theta_adjoint_t<float>(p, a, mb.n, V, F2, st) : theta_adjoint_t<double>(p, a, mb.n, V, F2, st);
+    const hipError_t e =
+        p.g.fp32 ? theta_adjoint_t<float>(p, a, mb.n, V, F2, st) : theta_adjoint_t<double>(p, a, mb.n, V, F2, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
 hipError_t launch_phi_synth(const psht_plan_s &p, const void *V, void *U, const MapBatch &mb, hipStream_t st) {
     const StageArgs a = stage_args(p, mb);
-    const hipError_t e = p.g.fp32 ? phi_synth_t<float>(p, a, mb.n, V, U, st) : phi_synth_t<double>(p, a, mb.n, V, U, st);
+    const hipError_t e =
+        p.g.fp32 ? phi_synth_t<float>(p, a, mb.n, V, U, st) : phi_synth_t<double>(p, a, mb.n, V, U, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 
 hipError_t launch_phi_adjoint(const psht_plan_s &p, const void *U, void *V, const MapBatch &mb, hipStream_t st) {
     const StageArgs a = stage_args(p, mb);
-    const hipError_t e = p.g.fp32 ? phi_adjoint_t<float>(p, a, mb.n, U, V, st) : phi_adjoint_t<double>(p, a, mb.n, U, V, st);
+    const hipError_t e =
+        p.g.fp32 ? phi_adjoint_t<float>(p, a, mb.n, U, V, st) : phi_adjoint_t<double>(p, a, mb.n, U, V, st);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }

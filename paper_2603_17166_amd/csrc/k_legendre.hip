@@ -18,15 +18,18 @@
 // the lambda of a ring fall off faster than exponentially towards l = m, so a
 // band starts at the first degree (on a grid of 32) at which any of its rings
 // reaches 2^-64 (kLegStartExp): the terms left out lie below the rounding of the
-// sums.  (Values that are not finite are looked for among those terms and put
-// into the results, from the degree on at which a ring of the order reaches
-// 2^-312: coefficients by the synthesis, ring values by the adjoint.)  The recurrence of each band starts from a state stored at plan time
+// sums.  The recurrence of each band starts from a state stored at plan time
 // (mu_l, mu_{l-1}; in the double range, see k_leg_states), so the kernels carry
-// no exponents.  (At spins in the hundreds the weaker sign of a ring can lie below
-// the double range at that degree and matter later: such plans take every band's
-// next stored state in as l passes it, see synth_run.)  A wave holds several bands (registers) and takes them in one
+// no exponents.  A wave holds several bands (registers) and takes them in one
 // after the other as l passes their starts.  At lmax 4096 (35 degree cap) the
 // bands start at 0.73 of the (ring, m, l) triples of l >= m, at lmax 2048 0.78.
+// Two things need more than that:
+//  - at spins in the hundreds the weaker sign of a ring can lie below the double
+//    range where its band starts and matter later: the synthesis of such plans
+//    takes every band's next stored state in as l passes it (synth_run);
+//  - values that are not finite are looked for among the terms left out, from the
+//    degree on at which a ring of the order reaches 2^-312, and put into the
+//    results: coefficients by the synthesis, ring values by the adjoint.
 //
 // The per-(l, m) recurrence coefficients and coefficient combinations are
 // wave-uniform: they are staged through LDS one chunk of 32 degrees ahead.
@@ -179,10 +182,11 @@ __device__ inline void synth_chunk(BandState<RMAX> &S, double4 (*f)[RMAX], const
 // Synthesis: one wave per item, the degrees [la, lb) of order m for up to RMAX
 // bands.  Segment 0 of an order, and for each band the segment it starts in,
 // writes F; later segments write the partial copy of F of their segment
-// (k part_stride bytes after F), which k_synth_parts_sum then adds into F.  RMAX = 4 reads each staged coefficient once for four
-// bands: 18 cycles of the CU's LDS pipe per step (four 16-byte broadcasts at
-// 4.4 cycles) against 32 FMAs (39 cycles over the four SIMDs); with two bands
-// the two are level and neither overlaps fully.
+// (k part_stride bytes after F), which k_synth_parts_sum then adds into F.
+// RMAX = 4 reads each staged coefficient once for four bands: 18 cycles of the
+// CU's LDS pipe per step (four 16-byte broadcasts at 4.4 cycles) against 32 FMAs
+// (39 cycles over the four SIMDs); with two bands the two are level and neither
+// overlaps fully.
 struct SynthArgs {
     LegArgs a;
     const SynthItem *items;

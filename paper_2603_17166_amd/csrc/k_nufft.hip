@@ -408,8 +408,8 @@ static hipError_t launch_interp_w(const psht_plan_s &p, const void *U, void *map
     typedef typename CplxT<T>::type C;
     NufftArgs a = nufft_args(p, mb);
     size_t lds = (size_t)(p.tile_x + W - 1) * tile_row_stride(p.tile_y, W) * sizeof(C);
-    hipLaunchKernelGGL((k_interp<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds, st, a,
-                       static_cast<const C *>(U), static_cast<C *>(map));
+    hipLaunchKernelGGL((k_interp<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds,
+                       st, a, static_cast<const C *>(U), static_cast<C *>(map));
     return hipGetLastError();
 }
 
@@ -418,8 +418,8 @@ static hipError_t launch_spread_w(const psht_plan_s &p, const void *map, void *U
     typedef typename CplxT<T>::type C;
     NufftArgs a = nufft_args(p, mb);
     size_t lds = (size_t)(p.tile_x + W - 1) * tile_row_stride(p.tile_y, W) * 2 * sizeof(double);
-    hipLaunchKernelGGL((k_spread<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds, st, a,
-                       static_cast<const C *>(map), static_cast<T *>(U));
+    hipLaunchKernelGGL((k_spread<T, W>), dim3(xcd_tile_blocks(p.ntiles, a.xcd_group), mb.n), dim3(kTileThreads), lds,
+                       st, a, static_cast<const C *>(map), static_cast<T *>(U));
     return hipGetLastError();
 }
 

@@ -204,7 +204,8 @@ __device__ inline void rot_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 
 // The states of one wavefront.
 struct RotWave {
-    double yp[kRotPairs], ypp[kRotPairs], ym[kRotPairs], ymp[kRotPairs];  // y of k and (-1)^k y of -k, with the previous ones
+    // y of k and (-1)^k y of -k, with the previous ones
+    double yp[kRotPairs], ypp[kRotPairs], ym[kRotPairs], ymp[kRotPairs];
     int kp[kRotPairs], km[kRotPairs];                                     // their scales
 };
 
@@ -215,7 +216,8 @@ struct RotWave {
 // the chunk.
 template <int NC, int MODE>
 __device__ inline void rot_steps(RotWave &w, double *acc, int acc_stride, const double *uni, int uni_stride,
-                                 const double *gms, const double *qms, int lb, int nsteps, int m, int kw, int lane, double cb) {
+                                 const double *gms, const double *qms, int lb, int nsteps, int m, int kw, int lane,
+                                 double cb) {
     typedef RotRow<NC> Row;
 #pragma unroll 1
     for (int u = 0; u < nsteps; ++u) {
@@ -271,7 +273,8 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
     constexpr int kUni = kRotWaves * Row::size, kThreads = 64 * kRotWaves;
     __shared__ double acc[kRotSteps * kStride];
     __shared__ double uni[kRotSteps * kUni];
-    __shared__ double gms[kRotSteps * 64], sqg[2][kRotSteps * 64];  // G_l(m); its root, read by the flush while the next is stored
+    // G_l(m); its root, read by the flush while the next is stored
+    __shared__ double gms[kRotSteps * 64], sqg[2][kRotSteps * 64];
     __shared__ double qms[kRotSteps * 64];  // m / (l (l + 1))
     __shared__ double2 phase[64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -351,7 +354,8 @@ template <int NC> __global__ __launch_bounds__(64 * kRotWaves) void k_rot_main(R
     store((first / kRotSteps) & 1, first);
     __syncthreads();
 
-    const int started = max(min(m0 + 63, lmax), min(kw + kRotPairs - 1, lmax));  // the last first degree of the wavefront
+    // the last first degree of the wavefront
+    const int started = max(min(m0 + 63, lmax), min(kw + kRotPairs - 1, lmax));
 #pragma unroll 1
     for (int lb = first; lb <= lmax; lb += kRotSteps) {
         const int nsteps = min(kRotSteps, lmax + 1 - lb);
