@@ -33,7 +33,8 @@ def test_full_sky_rings(lmax, spin):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("lmax,spin,deg", [(128, 100, 20.0), (256, 255, 20.0), (256, 64, 5.0)])
+@pytest.mark.parametrize("lmax,spin,deg", [(128, 100, 20.0), (256, 255, 20.0), (256, 64, 5.0),
+                                           (331, 38, 1.1)])
 def test_transforms_at_high_spin(lmax, spin, deg):
     import torch
 
